@@ -123,10 +123,13 @@ pss_status pss_plan_describe(pss_key_t key, pss_val_t val, uint64_t n, uint32_t 
 /*
  * Sort n keys (and, with PSS_VAL_U32, their uint32 payloads) ascending.
  *
- *   n_blocks = n_parts = 0: automatic plan.  The input is cut into LDS-sized
- *     blocks (tiles); step 1 sorts each tile; steps 2-4 are then applied level
- *     by level, each level merging groups of sorted runs with exact splitting
- *     into LDS-sized partitions, until one run remains.
+ *   n_blocks = n_parts = 0: automatic plan.  Short inputs are cut into
+ *     LDS-sized blocks (tiles); step 1 sorts each tile; steps 2-4 are then
+ *     applied level by level, each level merging groups of sorted runs with
+ *     exact splitting into LDS-sized partitions, until one run remains.  Longer
+ *     inputs are cut into buckets by sampled splitters, level by level, until
+ *     each bucket fits one workgroup, which sorts it in LDS.  The output is the
+ *     same either way.
  *   n_blocks > 0 and n_parts > 0: the paper's single-level method with those
  *     n_B and n_P: n_B blocks of ceil(N/n_B) keys are sorted, exact splitters
  *     P_1..P_{n_P-1} cut every block, and partition k of all blocks is merged

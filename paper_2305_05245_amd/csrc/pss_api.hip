@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../include/pss.h"
+#include "pss_dist.hpp"
 #include "pss_internal.hpp"
 
 struct pss_prof_rec {
@@ -49,6 +50,12 @@ uint64_t ceil_div(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 
 // Largest table (rows x fan entries of uint32) the library allocates.
 constexpr uint64_t kMaxTableEntries = (uint64_t)1 << 28;
+
+// Shortest array the automatic plan distributes into buckets.  Below it the few
+// launches of one or two merge passes cost less than sampling (30011 f32 pairs:
+// 68 us merged, 81 us distributed); above it distributing wins (10^6 int64: 82
+// against 178 us).
+constexpr uint64_t kDistMinKeys = 65537;
 
 // Merge passes that sort every segment of seg_len keys, starting from sorted
 // tiles of `tile` keys: the number of doublings needed is split as evenly as
@@ -111,6 +118,9 @@ struct Plan {
   size_t off_table = 0, off_sizes = 0, off_offsets = 0;
   size_t off_samples = 0, off_skeys = 0, off_sruns = 0, off_stable = 0, off_prefix = 0;
   size_t total = 0;
+  // automatic plan: the distribution sort, whose arrays take the place of the
+  // merge passes' tables (used when they fit there)
+  pss::DistPlan dist;
 };
 
 pss_status make_plan(pss_key_t key, pss_val_t val, uint64_t n, uint32_t n_blocks,
@@ -208,6 +218,10 @@ pss_status make_plan(pss_key_t key, pss_val_t val, uint64_t n, uint32_t n_blocks
     p->off_offsets = take(((size_t)n_parts + 1) * sizeof(uint64_t));
   }
   p->total = off;
+  if (!p->paper && n >= kDistMinKeys && pss::launch_dist_sample) {
+    p->dist = pss::dist_plan(n, p->kb, p->kv, p->off_table);
+    p->dist.on = p->dist.end <= p->total;
+  }
   return PSS_OK;
 }
 
@@ -412,12 +426,60 @@ pss_status paper_partition_search(pss_ctx *ctx, const Plan &p, int kt, const voi
   return PSS_OK;
 }
 
+// Distribution sort of p.n keys (and values) from keys_in into keys_out: the
+// levels alternate between the workspace and the output, the leaves are sorted
+// from wherever their level left them into the output.
+pss_status run_dist_sort(pss_ctx *ctx, const Plan &p, int kt, const void *keys_in,
+                         const uint32_t *vals_in, void *keys_out, uint32_t *vals_out, char *w,
+                         hipStream_t s) {
+  const pss::DistPlan &d = p.dist;
+  const uint64_t kbytes = p.n * (uint64_t)p.kb;
+  const uint64_t sweep = 2 * p.n * ((uint64_t)p.kb + (p.kv ? 4 : 0));
+  const pss::DistBufs b{keys_in, vals_in, w + p.off_keys0, (uint32_t *)(w + p.off_vals0),
+                        keys_out, vals_out};
+  for (int l = 1; l <= d.levels; ++l) {
+    {
+      LaunchTimer t(ctx, "dist_sample", 0, s);
+      PSS_LAUNCH(pss::launch_dist_sample(kt, d, l, b, p.n, w, s), "sample launch");
+    }
+    if (l < d.levels) {
+      {
+        LaunchTimer t(ctx, "dist_count", kbytes, s);
+        PSS_LAUNCH(pss::launch_dist_count(kt, d, l, b, w, s), "count launch");
+      }
+      {
+        LaunchTimer t(ctx, "dist_scan", 0, s);
+        PSS_LAUNCH(pss::launch_dist_scan(kt, d, l, w, s), "scan launch");
+      }
+      LaunchTimer t(ctx, "dist_scatter", sweep, s);
+      PSS_LAUNCH(pss::launch_dist_scatter(kt, p.kv, d, l, b, w, s), "scatter launch");
+    } else {
+      {
+        LaunchTimer t(ctx, "dist_partition", sweep, s);
+        PSS_LAUNCH(pss::launch_dist_partition(kt, p.kv, d, b, w, s), "partition launch");
+      }
+      LaunchTimer t(ctx, "dist_scan", 0, s);
+      PSS_LAUNCH(pss::launch_dist_scan(kt, d, l, w, s), "scan launch");
+    }
+  }
+  {
+    LaunchTimer t(ctx, "dist_leaves", sweep, s);
+    PSS_LAUNCH(pss::launch_dist_leaves(kt, p.kv, d, b, w, s), "leaf sort launch");
+  }
+  {
+    LaunchTimer t(ctx, "dist_rest", 0, s);
+    PSS_LAUNCH(pss::launch_dist_rest(kt, p.kv, d, b, w, s), "rest sort launch");
+  }
+  return PSS_OK;
+}
+
 // Automatic-plan sort of p.n keys (and values) from keys_in into keys_out:
 // tile sort and merge passes alternate between keys_out and the workspace so
 // that the last pass lands in keys_out.
 pss_status run_auto_sort(pss_ctx *ctx, const Plan &p, int kt, const void *keys_in,
                          const uint32_t *vals_in, void *keys_out, uint32_t *vals_out, char *w,
                          hipStream_t s) {
+  if (p.dist.on) return run_dist_sort(ctx, p, kt, keys_in, vals_in, keys_out, vals_out, w, s);
   const size_t P = p.passes.size();
   KeyBufs kb;
   ValBufs vb;

@@ -1,0 +1,1293 @@
+// Distribution sort for gfx950: arrays longer than one LDS tile.
+//
+// The merge passes of the single level move every key through HBM once per
+// factor of 32 and through log2(F) rounds of LDS merges each time.  Here a
+// level cuts a node (a stretch of keys) into up to 512 buckets instead:
+//
+//   sample     a few thousand stratified random keys of the node, sorted in
+//              LDS; every (S/p)-th is a splitter.  A key seen twice at a
+//              splitter also gives the next larger key, so that a frequent key
+//              has a bucket of its own, which needs no further work.
+//   count      (before the last level) keys per bucket of every range
+//   scan       where the buckets start; they become leaves (fit one workgroup,
+//              or hold one key value only), nodes of the next level, or - if the
+//              last level left one too large - entries of the rest list
+//   scatter    (before the last level) the same ranges, tile by tile: a tile is
+//              ordered by bucket in LDS and leaves in runs of consecutive
+//              addresses, each bucket's at its own place
+//   partition  (last level, in place of count and scatter) every tile is ordered
+//              by bucket in LDS and written back as one piece, with a table of
+//              where each bucket starts in it; no counts are needed first, and
+//              no partial cache lines are written
+//
+// and a leaf is sorted by one workgroup, which gathers it from its piece of
+// every tile of the node.  Samples are taken at hashed positions, so the order
+// of the input does not matter, and any distribution of keys gives buckets of
+// about the same size.  Nothing depends on the sizes being met: a bucket left
+// too large is sorted by merging through memory.
+//
+// At 2^28 int64 uniform keys (ms): samples 0.22, count 0.43, scatter 1.48,
+// partition 0.90, leaves 1.77; the sort 4.80, against 7.31 for the merge plan's
+// tile sort (1.71) and three merge passes (1.88 each with their searches).
+//
+// Key-value sorts place equal keys in input order at every step (the ranges
+// are in order, and a tile's ranks follow it), keys-only sorts need not:
+// equal keys are bit-identical.
+#include "pss_device.hpp"
+#include "pss_dist.hpp"
+
+namespace pss {
+namespace {
+
+constexpr uint32_t kLutBins = 1024;
+
+// DistLeaf::len_flags
+constexpr uint32_t kLeafLenMask = 0xffffu;
+constexpr uint32_t kLeafEqual = 1u << 16;  // one key value: unmapped, not sorted
+constexpr uint32_t kLeafMove = 1u << 17;   // part of a rest entry: moved to the output
+constexpr uint32_t kLeafInner = 1u << 18;  // the splitters around it bound its keys
+constexpr int kLeafSrcShift = 19;          // where its keys are:
+constexpr uint32_t kSrcWs = 0, kSrcOut = 1, kSrcPieces = 2;
+
+// Arguments of one level's kernels.
+struct Level {
+  DistCounters *ctr;
+  DistNode *nodes, *next_nodes;
+  DistRange *ranges, *next_ranges;
+  void *spl;
+  uint32_t *start;
+  void *table;
+  DistLeaf *leaves;
+  uint64_t *rest;  // offset | length << 32, mapped keys in the output
+  uint32_t level, levels, cap, target, rl, next_rl;
+  uint32_t src;  // kSrc* of this level's leaves
+  uint32_t max_next_nodes, max_next_ranges, max_cols, max_next_table, max_leaves, max_rest;
+  uint32_t root_len, root_p;  // level 1 of a single array (0: nodes are given)
+};
+
+// Inclusive sum over the wave's lanes, in DPP moves: shifts by 1, 2, 4 and 8
+// lanes within rows of 16, then the last lane of row 0 to row 1 and of row 2
+// to row 3, then that of row 1 to rows 2 and 3.
+__device__ __forceinline__ uint32_t wave_sum_scan(uint32_t x) {
+  int y = (int)x;
+  y += __builtin_amdgcn_update_dpp(0, y, 0x111, 0xF, 0xF, false);
+  y += __builtin_amdgcn_update_dpp(0, y, 0x112, 0xF, 0xF, false);
+  y += __builtin_amdgcn_update_dpp(0, y, 0x114, 0xF, 0xF, false);
+  y += __builtin_amdgcn_update_dpp(0, y, 0x118, 0xF, 0xF, false);
+  y += __builtin_amdgcn_update_dpp(0, y, 0x142, 0xA, 0xF, false);
+  y += __builtin_amdgcn_update_dpp(0, y, 0x143, 0xC, 0xF, false);
+  return (uint32_t)y;
+}
+
+// Exclusive sum over the workgroup's threads; `wsum` needs NT / 64 entries and
+// may be used again after the next barrier.
+template <int NT>
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *wsum, uint32_t &total) {
+  const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const uint32_t x = wave_sum_scan(v);
+  if (lane == 63) wsum[wid] = x;
+  __syncthreads();
+  uint32_t before = 0;
+  total = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < NT / 64; ++w) {
+    const uint32_t c = wsum[w];
+    before += w < wid ? c : 0u;
+    total += c;
+  }
+  return before + x - v;
+}
+
+// p of a node: its share of the buckets the remaining levels have to reach.
+__device__ __forceinline__ uint32_t node_picks(uint32_t len, uint32_t target, int remaining) {
+  const uint32_t units = (len + target - 1) / target;
+  uint32_t p = units;
+  if (remaining == 2) p = (uint32_t)ceilf(sqrtf((float)units));
+  else if (remaining >= 3) p = (uint32_t)ceilf(cbrtf((float)units));
+  return p < 2 ? 2 : (p > kDistMaxPicks ? kDistMaxPicks : p);
+}
+
+__device__ __forceinline__ uint32_t node_cols(uint32_t p) {
+  return 2 * p < kDistSlots ? 2 * p : kDistSlots;
+}
+
+// Table entries per bucket: one a range, or (last level) one a tile, padded so
+// that every bucket's entries start on 16 bytes.
+__device__ __forceinline__ uint32_t node_stride(uint32_t len, uint32_t nr, bool last) {
+  return last ? ((len + kDistTile - 1) / kDistTile + 7) / 8 * 8 : nr;
+}
+
+// ------------------------------------------------------------- sampling ---
+// One workgroup per node; latency-bound (a few random loads a thread, then
+// one LDS sort).  The picks come from S sorted samples, S a power of two of at
+// least 20 per bucket, at most one tile.
+template <int KT, int NT>
+__global__ __launch_bounds__(NT) void dist_sample_kernel(const typename Key<KT>::U *__restrict__ src,
+                                                         Level L) {
+  using U = typename Key<KT>::U;
+  constexpr uint32_t TILE = NT * kTileItems;
+  __shared__ U sk[TileLds<false, NT>::SLOTS];
+  __shared__ uint32_t wsum[NT / 64];
+  const uint32_t tid = threadIdx.x;
+  DistNode nd;
+  if (L.root_len) {
+    nd.off = 0;
+    nd.len = L.root_len;
+    nd.p = L.root_p;
+    nd.nr = (nd.len + L.rl - 1) / L.rl;
+    nd.cols = node_cols(nd.p);
+    nd.sbase = 0;
+    nd.tbase = 0;
+    nd.stride = node_stride(nd.len, nd.nr, L.levels == 1);
+    uint32_t *c = (uint32_t *)L.ctr;
+    for (uint32_t i = tid; i < sizeof(DistCounters) / 4; i += NT) c[i] = 0;
+    for (uint32_t r = tid; r < nd.nr; r += NT) L.ranges[r] = DistRange{0u, r};
+    __syncthreads();
+    if (tid == 0) {
+      L.ctr->nodes[1] = 1;
+      L.ctr->ranges[1] = nd.nr;
+    }
+  } else {
+    if (blockIdx.x >= L.ctr->nodes[L.level]) return;
+    nd = L.nodes[blockIdx.x];
+  }
+  uint32_t want = 64 * nd.p < TILE ? 64 * nd.p : TILE;
+  want = nd.len / 2 < want ? nd.len / 2 : want;
+  const uint32_t lg = 31 - __clz(want), S = 1u << lg;
+  U rk[kTileItems];
+#pragma unroll
+  for (int i = 0; i < kTileItems; ++i) {
+    const uint32_t j = i * NT + tid;
+    uint32_t h = (j + 1) * 0x9E3779B1u ^ (nd.off + L.level) * 0x85EBCA6Bu;
+    h ^= h >> 15;
+    h *= 0x2C1B3C6Du;
+    h ^= h >> 12;
+    h *= 0x297A2D39u;
+    h ^= h >> 15;
+    // a hashed position of the j-th of S equal strata
+    const uint64_t pos = ((uint64_t)j * nd.len + (((uint64_t)h * nd.len) >> 32)) >> lg;
+    rk[i] = j < S ? Key<KT>::map(src[nd.off + pos]) : key_max<U>();
+  }
+  lds_sort_keys<U, NT>(rk, sk);
+  // splitters of p picks; when frequent keys double them beyond the slots,
+  // half the picks do
+  U *spl = (U *)L.spl + nd.sbase;
+  uint32_t ns = 0;
+  for (uint32_t p = nd.p;; p = (p + 1) / 2) {
+    const uint32_t last_pick = p - 2;  // picks 0 .. p-2
+    U v = 0;
+    uint32_t e = 0;
+    bool first = false, next = false;
+    if (tid <= last_pick) {
+      const uint32_t at = (tid + 1) * S / p;
+      v = sk[at];
+      const U before = tid > 0 ? sk[tid * S / p] : U(0);
+      const U after = tid < last_pick ? sk[(tid + 2) * S / p] : U(0);
+      first = tid == 0 || before != v;
+      const bool last = tid == last_pick || after != v;
+      const bool dup = !(first && last) || (at > 0 && sk[at - 1] == v) ||
+                       (at + 1 < S && sk[at + 1] == v);
+      next = last && dup && v != key_max<U>() && !(tid < last_pick && after == v + 1);
+      e = (first ? 1u : 0u) + (next ? 1u : 0u);
+    }
+    uint32_t total;
+    const uint32_t at = block_scan<NT>(e, wsum, total);
+    if (total < nd.cols || p <= 2) {
+      if (first) spl[at] = v;
+      if (next) spl[at + (first ? 1u : 0u)] = v + 1;
+      ns = total;
+      break;
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    nd.nb = ns + 1;
+    L.nodes[blockIdx.x] = nd;
+  }
+}
+
+// ------------------------------------------------------- classification ---
+// Bucket of a key: the number of splitters <= it.  A table over 1024 equal
+// steps of the splitters' span gives the candidates of a key's step (none or
+// one for keys spread evenly), a binary search the rest.
+template <typename U> struct Classifier {
+  U spl[kDistSlots + 1];
+  uint32_t lut[kLutBins];  // splitters below the step | those up to its end << 16
+};
+
+template <typename U> struct ClassifierRegs {
+  U first;
+  uint32_t shift;
+};
+
+template <typename U>
+__device__ __forceinline__ ClassifierRegs<U> classifier_load(Classifier<U> &c, const U *g,
+                                                             uint32_t ns) {
+  const uint32_t tid = threadIdx.x;
+  for (uint32_t i = tid; i <= kDistSlots; i += blockDim.x) c.spl[i] = i < ns ? g[i] : key_max<U>();
+  __syncthreads();
+  ClassifierRegs<U> r;
+  r.first = c.spl[0];
+  const uint64_t span = (uint64_t)(c.spl[ns - 1] - r.first);
+  const int bits = span ? 64 - __clzll((long long)span) : 0;
+  r.shift = bits > 10 ? (uint32_t)(bits - 10) : 0u;
+  auto below = [&](uint32_t x) {  // splitters in steps before x
+    uint32_t lo = 0, hi = ns;
+    while (lo < hi) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if ((uint64_t)((c.spl[mid] - r.first) >> r.shift) < x) lo = mid + 1;
+      else hi = mid;
+    }
+    return lo;
+  };
+  for (uint32_t x = tid; x < kLutBins; x += blockDim.x)
+    c.lut[x] = below(x) | (x + 1 < kLutBins ? below(x + 1) : ns) << 16;
+  __syncthreads();
+  return r;
+}
+
+template <typename U, int N>
+__device__ __forceinline__ void classify(const Classifier<U> &c, const ClassifierRegs<U> &r,
+                                         const U (&k)[N], uint32_t (&b)[N]) {
+  uint32_t hi[N];
+  bool more = false;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const U d = k[i] - r.first;
+    const U s = d >> r.shift;
+    const uint32_t x = s < (U)(kLutBins - 1) ? (uint32_t)s : kLutBins - 1;
+    const uint32_t e = c.lut[x];
+    const bool under = k[i] < r.first;
+    b[i] = under ? 0u : e & 0xffffu;
+    hi[i] = under ? 0u : e >> 16;
+    more |= b[i] < hi[i];
+  }
+  while (__any(more)) {
+    more = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const uint32_t mid = (b[i] + hi[i]) >> 1;
+      const bool act = b[i] < hi[i], le = c.spl[mid] <= k[i];
+      b[i] = act && le ? mid + 1 : b[i];
+      hi[i] = act && !le ? mid : hi[i];
+      more |= b[i] < hi[i];
+    }
+  }
+}
+
+// ---------------------------------------------------------------- count ---
+// One workgroup per range: reads every key once (HBM-bound).
+constexpr int kCountItems = 8;
+
+template <int KT>
+__global__ __launch_bounds__(kDistThreads) void dist_count_kernel(
+    const typename Key<KT>::U *__restrict__ src, Level L) {
+  using U = typename Key<KT>::U;
+  __shared__ Classifier<U> cl;
+  __shared__ uint32_t hist[kDistSlots];
+  const uint32_t tid = threadIdx.x;
+  if (blockIdx.x >= L.ctr->ranges[L.level]) return;
+  const DistRange rg = L.ranges[blockIdx.x];
+  const DistNode nd = L.nodes[rg.node];
+  for (uint32_t i = tid; i < kDistSlots; i += kDistThreads) hist[i] = 0;
+  const ClassifierRegs<U> cr = classifier_load(cl, (const U *)L.spl + nd.sbase, nd.nb - 1);
+  const uint32_t end = rg.r * L.rl + L.rl < nd.len ? rg.r * L.rl + L.rl : nd.len;
+  const U *p = src + nd.off;
+  for (uint32_t base = rg.r * L.rl; base < end; base += kDistThreads * kCountItems) {
+    U k[kCountItems];
+    uint32_t b[kCountItems];
+#pragma unroll
+    for (int i = 0; i < kCountItems; ++i) {
+      const uint32_t idx = base + i * kDistThreads + tid;
+      k[i] = p[idx < end ? idx : end - 1];
+    }
+#pragma unroll
+    for (int i = 0; i < kCountItems; ++i) k[i] = Key<KT>::map(k[i]);
+    classify(cl, cr, k, b);
+#pragma unroll
+    for (int i = 0; i < kCountItems; ++i) {
+      const bool ok = base + i * kDistThreads + tid < end;
+      // one bucket for the whole wave (ordered input): one addition, not 64
+      // to the same address
+      const uint32_t b0 = __builtin_amdgcn_readfirstlane(b[i]);
+      if (__all(ok && b[i] == b0)) {
+        if ((tid & 63) == 0) atomicAdd(&hist[b0], 64u);
+      } else if (ok) {
+        atomicAdd(&hist[b[i]], 1u);
+      }
+    }
+  }
+  __syncthreads();
+  uint32_t *table = (uint32_t *)L.table + nd.tbase;
+  for (uint32_t b = tid; b < nd.nb; b += kDistThreads) table[b * nd.stride + rg.r] = hist[b];
+}
+
+// ----------------------------------------------------------------- scan ---
+// One wave per bucket of the root node, whose hundreds of ranges are too many
+// for one thread: exclusive sums over the ranges in place, the total to start.
+__global__ __launch_bounds__(256) void dist_columns_kernel(Level L) {
+  const DistNode nd = L.nodes[0];
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t b = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (b >= nd.nb) return;
+  uint32_t *col = (uint32_t *)L.table + nd.tbase + b * nd.stride;
+  uint32_t run = 0;
+  for (uint32_t r0 = 0; r0 < nd.nr; r0 += 64) {
+    const uint32_t r = r0 + lane;
+    const uint32_t v = r < nd.nr ? col[r] : 0u;
+    const uint32_t x = wave_sum_scan(v);
+    if (r < nd.nr) col[r] = run + x - v;
+    run += __shfl(x, 63, 64);
+  }
+  if (lane == 0) L.start[nd.sbase + b] = run;
+}
+
+// One workgroup per node, one thread per bucket.  Last level: a bucket's start
+// is the sum of its starts in the node's tiles.
+template <typename U>
+__global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summed) {
+  __shared__ uint32_t wsum[kDistSlots / 64], wsum2[kDistSlots / 64];
+  __shared__ uint32_t starts[kDistSlots + 1];
+  __shared__ uint32_t leaf0;
+  const uint32_t b = threadIdx.x;
+  if (blockIdx.x >= L.ctr->nodes[L.level]) return;
+  const DistNode nd = L.nodes[blockIdx.x];
+  const bool last = L.level == L.levels;
+  uint32_t len = 0, off = nd.off;
+  if (last) {
+    if (b < nd.nb) {
+      const uint16_t *col = (const uint16_t *)L.table + nd.tbase + b * nd.stride;
+      const uint32_t tiles = (nd.len + kDistTile - 1) / kDistTile;
+      for (uint32_t t = 0; t < tiles; t += 8) {  // entries past the tiles count nothing
+        const uint4 q = *reinterpret_cast<const uint4 *>(col + t);
+        const uint32_t wd[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i)
+          off += t + i < tiles ? (wd[i >> 1] >> (16 * (i & 1))) & 0xffffu : 0u;
+      }
+      starts[b] = off;
+    }
+    if (b == 0) starts[nd.nb] = nd.off + nd.len;
+    __syncthreads();
+    if (b < nd.nb) len = starts[b + 1] - off;
+  } else {
+    if (b < nd.nb) {
+      if (summed) {
+        len = L.start[nd.sbase + b];
+      } else {
+        uint32_t *col = (uint32_t *)L.table + nd.tbase + b * nd.stride;
+        for (uint32_t r0 = 0; r0 < nd.nr; r0 += 8) {
+          uint32_t v[8];
+#pragma unroll
+          for (uint32_t i = 0; i < 8; ++i) v[i] = r0 + i < nd.nr ? col[r0 + i] : 0u;
+#pragma unroll
+          for (uint32_t i = 0; i < 8; ++i) {
+            if (r0 + i < nd.nr) col[r0 + i] = len;
+            len += v[i];
+          }
+        }
+      }
+    }
+    uint32_t total;
+    off = nd.off + block_scan<kDistSlots>(len, wsum, total);
+    if (b < nd.nb) L.start[nd.sbase + b] = off;
+  }
+  const uint32_t ns = nd.nb - 1;
+  const bool next_last = L.level + 1 == L.levels;
+  bool equal = false;  // the bucket can hold one key value only
+  bool node = false, rest = false;
+  uint32_t pieces = 0;
+  U lo = 0, hi = 0;
+  if (b < nd.nb && len) {
+    const U *spl = (const U *)L.spl + nd.sbase;
+    lo = b > 0 ? spl[b - 1] : U(0);
+    hi = b < ns ? spl[b] : U(0);
+    equal = b < ns ? hi - lo == 1 : lo == key_max<U>();
+    const bool fits = len <= L.cap;
+    node = !last && !equal && !fits && !(next_last && len > kDistNodeTiles * kDistTile);
+    rest = !equal && !fits && !node;
+    // (before the last level a rest entry already lies in the output)
+    pieces = node || (rest && !last) ? 0u : (len + L.cap - 1) / L.cap;
+  }
+  uint32_t npieces;
+  const uint32_t at = block_scan<kDistSlots>(pieces, wsum2, npieces);
+  if (b == 0) leaf0 = npieces ? atomicAdd(&L.ctr->leaves, npieces) : 0u;
+  __syncthreads();
+  for (uint32_t q = 0; q < pieces; ++q) {
+    const uint32_t o = q * L.cap, l = len - o < L.cap ? len - o : L.cap;
+    const uint32_t to = leaf0 + at + q;
+    if (to < L.max_leaves) {
+      const uint32_t row = nd.tbase + b * nd.stride;
+      L.leaves[to] = DistLeaf{off + o,
+                              l | L.src << kLeafSrcShift | (equal ? kLeafEqual : 0u) |
+                                  (rest ? kLeafMove : 0u) | (b > 0 && b < ns ? kLeafInner : 0u),
+                              nd.off, nd.len, o, row, b < ns ? row + nd.stride : ~0u, 0u, (uint64_t)lo,
+                              (uint64_t)hi};
+    }
+  }
+  if (rest) {
+    const uint32_t to = atomicAdd(&L.ctr->rest, 1u);
+    if (to < L.max_rest) L.rest[to] = (uint64_t)off | (uint64_t)len << 32;
+  }
+  if (node) {
+    DistNode c;
+    c.off = off;
+    c.len = len;
+    c.p = node_picks(len, L.target, (int)(L.levels - L.level));
+    c.nr = (len + L.next_rl - 1) / L.next_rl;
+    c.cols = node_cols(c.p);
+    c.stride = node_stride(len, c.nr, next_last);
+    c.nb = 0;
+    const uint32_t lv = L.level + 1;
+    const uint32_t at_node = atomicAdd(&L.ctr->nodes[lv], 1u);
+    const uint32_t at_range = atomicAdd(&L.ctr->ranges[lv], c.nr);
+    c.sbase = atomicAdd(&L.ctr->cols[lv], c.cols);
+    c.tbase = atomicAdd(&L.ctr->table[lv], c.cols * c.stride);
+    // (the plan's bounds hold for any lengths; this keeps writes inside them)
+    if (at_node < L.max_next_nodes && at_range + c.nr <= L.max_next_ranges &&
+        c.sbase + c.cols <= L.max_cols && c.tbase + c.cols * c.stride <= L.max_next_table) {
+      L.next_nodes[at_node] = c;
+      for (uint32_t r = 0; r < c.nr; ++r) L.next_ranges[at_range + r] = DistRange{at_node, r};
+    }
+  }
+}
+
+// ----------------------------------------------------------- tile ranks ---
+// Position in its tile of a thread's i-th key.  Key-value: a wave's keys are
+// consecutive, row by row, as the ranks follow that order.
+template <bool KV> __device__ __forceinline__ uint32_t tile_at(int i) {
+  const uint32_t tid = threadIdx.x;
+  return KV ? (tid >> 6) * (64 * kDistItems) + i * 64 + (tid & 63) : i * kDistThreads + tid;
+}
+
+// Ranks of a tile's keys within their buckets: pos[i] gets the key's rank
+// (key-value: among its wave's keys of the bucket; wh then holds how many keys
+// of the bucket earlier waves have).  Returns the tile's keys of bucket tid.
+template <bool KV>
+__device__ __forceinline__ uint32_t tile_ranks(const uint32_t (&b)[kDistItems],
+                                               uint32_t (&pos)[kDistItems], uint32_t count,
+                                               uint32_t nbits, uint16_t *wh, uint32_t *hist) {
+  constexpr int NT = kDistThreads, NI = kDistItems, NW = NT / 64;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  if constexpr (KV) {
+    for (uint32_t i = tid; i < NW * kDistSlots / 2; i += NT) reinterpret_cast<uint32_t *>(wh)[i] = 0;
+    __syncthreads();
+    uint16_t *my = wh + wid * kDistSlots;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const bool ok = tile_at<KV>(i) < count;
+      uint64_t peers = __ballot(ok);
+      for (uint32_t bit = 0; bit < nbits; ++bit) {
+        const bool one = (b[i] >> bit) & 1u;
+        const uint64_t m = __ballot(one);
+        peers &= one ? m : ~m;
+      }
+      const uint32_t below = __popcll(peers & (((uint64_t)1 << lane) - 1));
+      const uint32_t seen = my[b[i]];
+      wave_sync();
+      if (ok && below == 0) my[b[i]] = (uint16_t)(seen + __popcll(peers));
+      wave_sync();
+      pos[i] = seen + below;
+    }
+    __syncthreads();
+    uint32_t mine = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const uint32_t c = wh[w * kDistSlots + tid];
+      wh[w * kDistSlots + tid] = (uint16_t)mine;
+      mine += c;
+    }
+    return mine;
+  } else {
+    hist[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const bool ok = tile_at<KV>(i) < count;
+      // one bucket for the whole wave (ordered input): one addition
+      const uint32_t b0 = __builtin_amdgcn_readfirstlane(b[i]);
+      if (__all(ok && b[i] == b0)) {
+        uint32_t r = 0;
+        if (lane == 0) r = atomicAdd(&hist[b0], 64u);
+        pos[i] = __builtin_amdgcn_readfirstlane(r) + lane;
+      } else if (ok) {
+        pos[i] = atomicAdd(&hist[b[i]], 1u);
+      }
+    }
+    __syncthreads();
+    return hist[tid];
+  }
+}
+
+// -------------------------------------------------------------- scatter ---
+// One workgroup per range, tile by tile in order.  A tile's keys are placed
+// in LDS in bucket order, so that a bucket's share of the tile (24 keys at 256
+// buckets) leaves as one run of addresses; the next tile continues the same
+// runs, and L2 joins the lines they share.  76 KB of LDS: two workgroups a CU.
+template <int KT, bool KV>
+__global__ __launch_bounds__(kDistThreads, 4) void dist_scatter_kernel(
+    const typename Key<KT>::U *__restrict__ src, const uint32_t *__restrict__ vsrc,
+    typename Key<KT>::U *__restrict__ dst, uint32_t *__restrict__ vdst, Level L) {
+  using U = typename Key<KT>::U;
+  constexpr int NT = kDistThreads, NI = kDistItems, NW = NT / 64;
+  __shared__ Classifier<U> cl;
+  __shared__ U sk[kDistTile];
+  __shared__ uint16_t sb[kDistTile];
+  __shared__ uint32_t hist[kDistSlots], lofs[kDistSlots], gofs[kDistSlots], wsum[NW];
+  // key-value: per-wave bucket counts, dead before the keys are placed
+  uint16_t *wh = reinterpret_cast<uint16_t *>(sk);
+  static_assert(NW * kDistSlots * 2 <= sizeof(sk), "wave counts fit the key area");
+  static_assert(NT == (int)kDistSlots, "one thread per bucket");
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  if (blockIdx.x >= L.ctr->ranges[L.level]) return;
+  const DistRange rg = L.ranges[blockIdx.x];
+  const DistNode nd = L.nodes[rg.node];
+  const ClassifierRegs<U> cr = classifier_load(cl, (const U *)L.spl + nd.sbase, nd.nb - 1);
+  uint32_t cursor = 0;
+  if (tid < nd.nb)
+    cursor = L.start[nd.sbase + tid] + ((const uint32_t *)L.table)[nd.tbase + tid * nd.stride + rg.r];
+  const uint32_t end = rg.r * L.rl + L.rl < nd.len ? rg.r * L.rl + L.rl : nd.len;
+  const U *p = src + nd.off;
+  const uint32_t *vp = KV ? vsrc + nd.off : nullptr;
+  const uint32_t nbits = 32 - __clz(nd.nb - 1);
+  for (uint32_t base = rg.r * L.rl; base < end; base += kDistTile) {
+    const uint32_t count = end - base < kDistTile ? end - base : kDistTile;
+    U k[NI];
+    uint32_t v[KV ? NI : 1], b[NI], pos[NI];
+    auto at = [](int i) { return tile_at<KV>(i); };
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const uint32_t j = at(i) < count ? at(i) : count - 1;
+      k[i] = __builtin_nontemporal_load(&p[base + j]);
+      if constexpr (KV) v[i] = __builtin_nontemporal_load(&vp[base + j]);
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) k[i] = Key<KT>::map(k[i]);
+    classify(cl, cr, k, b);
+    const uint32_t mine = tile_ranks<KV>(b, pos, count, nbits, wh, hist);
+    uint32_t total;
+    const uint32_t lo = block_scan<NT>(mine, wsum, total);
+    lofs[tid] = lo;
+    gofs[tid] = cursor - lo;  // modulo 2^32: the sum below is in range
+    cursor += mine;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      pos[i] += lofs[b[i]];
+      if constexpr (KV) pos[i] += wh[wid * kDistSlots + b[i]];
+    }
+    if constexpr (KV) __syncthreads();  // wh is read before the keys overwrite it
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      if (at(i) < count) {
+        sk[pos[i]] = k[i];
+        sb[pos[i]] = (uint16_t)b[i];
+      }
+    }
+    __syncthreads();
+    uint32_t to[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const uint32_t j = i * NT + tid;
+      if (j < count) {
+        to[i] = gofs[sb[j]] + j;
+        dst[to[i]] = sk[j];
+      }
+    }
+    if constexpr (KV) {
+      __syncthreads();
+      uint32_t *sv = reinterpret_cast<uint32_t *>(sk);
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        if (at(i) < count) sv[pos[i]] = v[i];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const uint32_t j = i * NT + tid;
+        if (j < count) vdst[to[i]] = sv[j];
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// ------------------------------------------------------------ partition ---
+// Last level: one workgroup per range; every tile is ordered by bucket in LDS
+// and written to its own place in the output array, so stores are whole lines
+// and nothing has to be counted first.  The starts of the buckets in the
+// range's tiles are collected in LDS and leave as one short run per bucket.
+template <int KT, bool KV>
+__global__ __launch_bounds__(kDistThreads, 4) void dist_partition_kernel(
+    const typename Key<KT>::U *__restrict__ src, const uint32_t *__restrict__ vsrc,
+    typename Key<KT>::U *__restrict__ dst, uint32_t *__restrict__ vdst, Level L) {
+  using U = typename Key<KT>::U;
+  constexpr int NT = kDistThreads, NI = kDistItems, NW = NT / 64;
+  __shared__ Classifier<U> cl;
+  __shared__ U sk[kDistTile];
+  __shared__ uint32_t hist[kDistSlots], lofs[kDistSlots], wsum[NW];
+  __shared__ uint16_t rows[kDistRangeTiles][kDistSlots];
+  // key-value: per-wave bucket counts, dead before the keys are placed
+  uint16_t *wh = reinterpret_cast<uint16_t *>(sk);
+  const uint32_t tid = threadIdx.x, wid = tid >> 6;
+  if (blockIdx.x >= L.ctr->ranges[L.level]) return;
+  const DistRange rg = L.ranges[blockIdx.x];
+  const DistNode nd = L.nodes[rg.node];
+  const ClassifierRegs<U> cr = classifier_load(cl, (const U *)L.spl + nd.sbase, nd.nb - 1);
+  const uint32_t begin = rg.r * L.rl, end = begin + L.rl < nd.len ? begin + L.rl : nd.len;
+  const U *p = src + nd.off;
+  const uint32_t *vp = KV ? vsrc + nd.off : nullptr;
+  U *q = dst + nd.off;
+  uint32_t *vq = KV ? vdst + nd.off : nullptr;
+  const uint32_t nbits = 32 - __clz(nd.nb - 1);
+  uint32_t tile = 0;
+  for (uint32_t base = begin; base < end; base += kDistTile, ++tile) {
+    const uint32_t count = end - base < kDistTile ? end - base : kDistTile;
+    auto at = [](int i) { return tile_at<KV>(i); };
+    U k[NI];
+    uint32_t v[KV ? NI : 1], b[NI], pos[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const uint32_t j = at(i) < count ? at(i) : count - 1;
+      k[i] = __builtin_nontemporal_load(&p[base + j]);
+      if constexpr (KV) v[i] = __builtin_nontemporal_load(&vp[base + j]);
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) k[i] = Key<KT>::map(k[i]);
+    classify(cl, cr, k, b);
+    const uint32_t mine = tile_ranks<KV>(b, pos, count, nbits, wh, hist);
+    uint32_t total;
+    const uint32_t lo = block_scan<NT>(mine, wsum, total);
+    lofs[tid] = lo;
+    rows[tile][tid] = (uint16_t)lo;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      pos[i] += lofs[b[i]];
+      if constexpr (KV) pos[i] += wh[wid * kDistSlots + b[i]];
+    }
+    if constexpr (KV) __syncthreads();  // wh is read before the keys overwrite it
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      if (at(i) < count) sk[pos[i]] = k[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const uint32_t j = i * NT + tid;
+      if (j < count) q[base + j] = sk[j];
+    }
+    if constexpr (KV) {
+      __syncthreads();
+      uint32_t *sv = reinterpret_cast<uint32_t *>(sk);
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        if (at(i) < count) sv[pos[i]] = v[i];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const uint32_t j = i * NT + tid;
+        if (j < count) vq[base + j] = sv[j];
+      }
+    }
+    __syncthreads();
+  }
+  if (tid < nd.nb) {
+    uint16_t *to = (uint16_t *)L.table + nd.tbase + tid * nd.stride + begin / kDistTile;
+    for (uint32_t t = 0; t < tile; ++t) to[t] = rows[t][tid];
+  }
+}
+
+// --------------------------------------------------------------- leaves ---
+// The same entry in every lane, in scalar registers.
+__device__ __forceinline__ DistLeaf uniform(const DistLeaf &f) {
+  DistLeaf u;
+  const uint32_t *a = reinterpret_cast<const uint32_t *>(&f);
+  uint32_t *b = reinterpret_cast<uint32_t *>(&u);
+#pragma unroll
+  for (uint32_t i = 0; i < sizeof(DistLeaf) / 4; ++i) b[i] = __builtin_amdgcn_readfirstlane(a[i]);
+  return u;
+}
+
+// One workgroup sorts one leaf of at most CAP = 16 NT keys.  The keys are
+// binned by interpolation between the bounds of the leaf (CAP bins, one key in
+// two bins when the leaf has its target size), placed in bin order in LDS, and
+// each key's final place is counted within its bin.  A leaf with a crowded bin
+// (a key of rank kCrowded or more: many equal keys, or keys spread over many
+// magnitudes) is left to the rest list.
+//
+// Keys of the last level are gathered: the leaf's piece of every tile of the
+// node is found in the table, and a bit mask over the leaf's positions, set
+// where a piece starts, tells every position its piece.
+constexpr uint32_t kCrowded = 24;
+
+template <int KT, bool KV, int NT>
+__global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
+    const typename Key<KT>::U *__restrict__ ws, const uint32_t *__restrict__ vws,
+    typename Key<KT>::U *out, uint32_t *vout, Level L) {
+  using U = typename Key<KT>::U;
+  constexpr uint32_t CAP = NT * kTileItems, NBIN = CAP, NW = NT / 64;
+  static_assert(NBIN / 4 / NT == 4, "one 16-byte word of bin counts a thread");
+  // (the counting loop reads up to kCrowded keys past a bin's start)
+  __shared__ U sk[CAP + 32];
+  __shared__ uint16_t sidx[KV ? CAP + 32 : 1];
+  // bin counts, a byte each (a count past 255 runs into its neighbours, but
+  // the leaf is crowded by then), and the keys before every four bins
+  __shared__ __attribute__((aligned(16))) uint32_t bins[NBIN / 4];
+  __shared__ __attribute__((aligned(8))) uint16_t bin4[NBIN / 4];
+  __shared__ U smin[NW], smax[NW];
+  __shared__ uint32_t wsum[NW];
+  // the gather's tables, dead before the keys are placed
+  uint32_t *piece = reinterpret_cast<uint32_t *>(sk);  // address - position
+  uint32_t *mask = bins;                               // CAP bits: a piece starts at the next position
+  uint16_t *row_piece = reinterpret_cast<uint16_t *>(bins + CAP / 32);  // piece of position 64 r
+  static_assert(kDistNodeTiles * 4 <= sizeof(sk), "pieces fit the key area");
+  static_assert(CAP / 8 + CAP / 32 <= sizeof(bins), "mask and rows fit the bins");
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const uint32_t nl = L.ctr->leaves < L.max_leaves ? L.ctr->leaves : L.max_leaves;
+  const uint16_t *table = (const uint16_t *)L.table;
+
+  if (blockIdx.x >= nl) return;
+  const DistLeaf leaf = uniform(L.leaves[blockIdx.x]);
+  // The leaf's piece of tile t: its first position in the tile and its end.
+  auto piece_of = [&](uint32_t t, uint32_t &s, uint32_t &e) {
+    s = e = 0;
+    if (t * kDistTile < leaf.node_len) {
+      const uint32_t rem = leaf.node_len - t * kDistTile, whole = rem < kDistTile ? rem : kDistTile;
+      s = table[leaf.row + t];
+      e = leaf.next_row != ~0u ? table[leaf.next_row + t] : whole;
+    }
+  };
+
+  const uint32_t off = leaf.off, len = leaf.len_flags & kLeafLenMask;
+  const uint32_t from = (leaf.len_flags >> kLeafSrcShift) & 3u;
+  const bool inner = from == kSrcPieces && (leaf.len_flags & kLeafInner);
+  const U *p = from == kSrcOut ? (const U *)out : ws;
+  const uint32_t *vp = from == kSrcOut ? (const uint32_t *)vout : vws;
+  U k[kTileItems];
+  uint32_t v[KV ? kTileItems : 1];
+  uint32_t addr[kTileItems];
+  if (from == kSrcPieces) {
+    if (!KV && (leaf.len_flags & kLeafEqual)) {
+      // one key value, known from the splitters: nothing to read
+      const U x = (U)leaf.below;
+      for (uint32_t i = tid; i < len; i += NT)
+        __builtin_nontemporal_store(Key<KT>::unmap(x), &out[off + i]);
+      return;
+    }
+    const uint32_t tiles = (leaf.node_len + kDistTile - 1) / kDistTile;
+    for (uint32_t i = tid; i < CAP / 32; i += NT) mask[i] = 0;
+    uint32_t np = 0, run = 0;
+    for (uint32_t t0 = 0; t0 < tiles && run < leaf.first + len; t0 += NT) {
+      const uint32_t t = t0 + tid;
+      uint32_t s, c;
+      piece_of(t, s, c);
+      c -= s;
+      // keys (at most 512 tiles of 6144: 22 bits) and non-empty pieces before
+      uint32_t total;
+      const uint32_t x = block_scan<NT>(c | (c ? 1u << 22 : 0u), wsum, total);
+      const uint32_t first = run + (x & 0x3fffffu), at = np + (x >> 22);
+      if (c) {
+        // position of the piece's first key in the leaf; a piece that starts
+        // before the leaf holds position 0
+        const uint32_t pos = first > leaf.first ? first - leaf.first : 0u;
+        const uint32_t stop = first + c > leaf.first ? first + c - leaf.first : 0u;
+        piece[at] = leaf.node_off + t * kDistTile + s + leaf.first - first;  // modulo 2^32
+        if (stop && pos < len) {
+          if (pos & 63u) {
+            const uint32_t bit = (pos & 63u) - 1;
+            atomicOr(&mask[(pos >> 6) * 2 + (bit >> 5)], 1u << (bit & 31u));
+          }
+          for (uint32_t r = (pos + 63) / 64; r * 64 < stop && r * 64 < len; ++r)
+            row_piece[r] = (uint16_t)at;
+        }
+      }
+      run += total & 0x3fffffu;
+      np += total >> 22;
+      __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < kTileItems; ++i) {
+      if (i * NT < len) {  // (positions past the end: the last key)
+        const uint32_t j = i * NT + tid < len ? i * NT + tid : len - 1;
+        const uint32_t r = j >> 6;
+        const uint64_t m = (uint64_t)mask[r * 2] | (uint64_t)mask[r * 2 + 1] << 32;
+        const uint32_t started = __popcll(m & (((uint64_t)1 << (j & 63u)) - 1));
+        addr[i] = piece[row_piece[r] + started] + j;
+      }
+    }
+    __syncthreads();
+  } else {
+#pragma unroll
+    for (int i = 0; i < kTileItems; ++i) addr[i] = off + (i * NT + tid < len ? i * NT + tid : len - 1);
+  }
+  // the loads are all issued before any is used: clamped, not conditional;
+  // steps of NT keys past the end are skipped throughout
+#pragma unroll
+  for (int i = 0; i < kTileItems; ++i) {
+    if (i * NT < len) {
+      k[i] = __builtin_nontemporal_load(&p[addr[i]]);
+      if constexpr (KV) v[i] = __builtin_nontemporal_load(&vp[addr[i]]);
+    }
+  }
+  if (leaf.len_flags & (kLeafEqual | kLeafMove)) {
+    const bool equal = leaf.len_flags & kLeafEqual;
+#pragma unroll
+    for (int i = 0; i < kTileItems; ++i) {
+      const uint32_t idx = i * NT + tid;
+      if (idx < len) {
+        out[off + idx] = equal ? Key<KT>::unmap(k[i]) : k[i];
+        if constexpr (KV) vout[off + idx] = v[i];
+      }
+    }
+    return;
+  }
+  reinterpret_cast<uint4 *>(bins)[tid] = uint4{0, 0, 0, 0};
+  // Bounds of the keys: the splitters around the bucket, or (a node's first
+  // and last bucket, and leaves of earlier levels) the smallest and largest
+  // key.
+  U mn, mx;
+  if (inner) {
+    mn = (U)leaf.below;
+    mx = (U)leaf.above - 1;
+    __syncthreads();
+  } else {
+    mn = mx = k[0];  // (clamped loads repeat the last key)
+#pragma unroll
+    for (int i = 1; i < kTileItems; ++i) {
+      if (i * NT < len) {
+        mn = k[i] < mn ? k[i] : mn;
+        mx = k[i] > mx ? k[i] : mx;
+      }
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+      const U a = __shfl_xor(mn, d, 64), c = __shfl_xor(mx, d, 64);
+      mn = a < mn ? a : mn;
+      mx = c > mx ? c : mx;
+    }
+    if (lane == 0) {
+      smin[wid] = mn;
+      smax[wid] = mx;
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t w = 0; w < NW; ++w) {
+      const U a = smin[w], c = smax[w];
+      mn = a < mn ? a : mn;
+      mx = c > mx ? c : mx;
+    }
+  }
+  // bin = floor(x * scale / 2^32) of x, the top 32 bits of the key's distance
+  // from mn; the scale is a little below NBIN 2^32 / (top + 1), so that every
+  // bin is below NBIN.  A span below NBIN gives every key value its own bin.
+  const uint64_t span = (uint64_t)(mx - mn);
+  const uint32_t sh = span >> 32 ? 32 - __clz((uint32_t)(span >> 32)) : 0u;
+  const uint32_t top = (uint32_t)(span >> sh);
+  const bool direct = top < NBIN;
+  const uint32_t scale =
+      direct ? 0u : (uint32_t)((float)NBIN * 4294967296.0f * (1.0f - 0x1p-20f) / ((float)top + 1.0f));
+  uint32_t place[kTileItems];  // bin, and rank in it << 16
+  uint32_t worst = 0;
+#pragma unroll
+  for (int i = 0; i < kTileItems; ++i) {
+    if (i * NT < len) {
+      const uint32_t x = (uint32_t)((uint64_t)(k[i] - mn) >> sh);
+      const uint32_t bin = direct ? x : __umulhi(x, scale);
+      place[i] = bin;
+      if (i * NT + tid < len) {
+        const uint32_t byte = (bin & 3u) * 8;
+        const uint32_t r = (atomicAdd(&bins[bin >> 2], 1u << byte) >> byte) & 0xffu;
+        place[i] |= r << 16;
+        worst = r > worst ? r : worst;
+      }
+    }
+  }
+  if (__syncthreads_or(worst >= kCrowded)) {
+#pragma unroll
+    for (int i = 0; i < kTileItems; ++i) {
+      const uint32_t idx = i * NT + tid;
+      if (idx < len) {
+        out[off + idx] = k[i];
+        if constexpr (KV) vout[off + idx] = v[i];
+      }
+    }
+    if (tid == 0) {
+      const uint32_t to = atomicAdd(&L.ctr->rest, 1u);
+      if (to < L.max_rest) L.rest[to] = (uint64_t)off | (uint64_t)len << 32;
+    }
+    return;
+  }
+  // keys before every four bins, 16 bins a thread
+  {
+    const uint4 q = reinterpret_cast<const uint4 *>(bins)[tid];
+    const uint32_t c0 = __builtin_amdgcn_sad_u8(q.x, 0, 0), c1 = __builtin_amdgcn_sad_u8(q.y, 0, c0);
+    const uint32_t c2 = __builtin_amdgcn_sad_u8(q.z, 0, c1), c3 = __builtin_amdgcn_sad_u8(q.w, 0, c2);
+    uint32_t total;
+    const uint32_t run = block_scan<NT>(c3, wsum, total);
+    reinterpret_cast<uint2 *>(bin4)[tid] = uint2{run | (run + c0) << 16, (run + c1) | (run + c2) << 16};
+    if (tid < 32) sk[len + tid] = key_max<U>();
+    if constexpr (KV)
+      if (tid < 32) sidx[len + tid] = 0xffffu;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kTileItems; ++i) {
+    if (i * NT + tid < len) {
+      const uint32_t bin = place[i] & 0xffffu, w = bins[bin >> 2];
+      const uint32_t s = __builtin_amdgcn_sad_u8(w & ~(~0u << (bin & 3u) * 8), 0, bin4[bin >> 2]);
+      const uint32_t slot = s + (place[i] >> 16);
+      // first slot, rank and count of the bin
+      place[i] = s | (place[i] >> 16) << 14 | ((w >> (bin & 3u) * 8) & 0xffu) << 22;
+      sk[slot] = k[i];
+      if constexpr (KV) sidx[slot] = (uint16_t)(i * NT + tid);
+    }
+  }
+  __syncthreads();
+  // A key's final place: its bin's first slot, plus the keys of the bin below
+  // it (of equal keys: in an earlier slot; key-value: at an earlier position).
+  // Slots past the bin hold larger keys, so the loop needs no end check.
+  // place becomes: slot, and final place << 16
+  constexpr int GRP = 4;
+#pragma unroll
+  for (int g = 0; g < kTileItems; g += GRP) {
+    if (g * NT < len) {
+      uint32_t s[GRP], slot[GRP], fin[GRP];
+      uint32_t most = 0;
+#pragma unroll
+      for (int i = 0; i < GRP; ++i) {
+        const bool ok = (g + i) * NT + tid < len;
+        const uint32_t n = ok ? place[g + i] >> 22 : 0u;
+        s[i] = ok ? place[g + i] & 0x3fffu : 0u;
+        slot[i] = s[i] + ((place[g + i] >> 14) & 0xffu);
+        fin[i] = s[i];
+        most = n > most ? n : most;
+      }
+      if (__any(most > 1)) {
+        for (uint32_t t = 0; __any(t < most); ++t) {
+#pragma unroll
+          for (int i = 0; i < GRP; ++i) {
+            const U o = sk[s[i] + t];
+            const bool tie = KV ? sidx[s[i] + t] < (g + i) * NT + tid : s[i] + t < slot[i];
+            fin[i] += (tie ? o <= k[g + i] : o < k[g + i]) ? 1u : 0u;
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < GRP; ++i) place[g + i] = slot[i] | fin[i] << 16;
+    }
+  }
+  if constexpr (KV) {
+    // the leaf may lie in the output: every load has returned before any
+    // thread stores
+#pragma unroll
+    for (int i = 0; i < kTileItems; ++i) asm volatile("" : "+v"(v[i]));
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kTileItems; ++i)
+    if (i * NT + tid < len && (place[i] >> 16) != (place[i] & 0xffffu)) sk[place[i] >> 16] = k[i];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kTileItems; ++i) {
+    const uint32_t idx = i * NT + tid;
+    if (idx < len) __builtin_nontemporal_store(Key<KT>::unmap(sk[idx]), &out[off + idx]);
+  }
+  if constexpr (KV) {
+    uint32_t *sv = reinterpret_cast<uint32_t *>(sk);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kTileItems; ++i)
+      if (i * NT + tid < len) sv[place[i] >> 16] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kTileItems; ++i) {
+      const uint32_t idx = i * NT + tid;
+      if (idx < len) __builtin_nontemporal_store(sv[idx], &vout[off + idx]);
+    }
+  }
+}
+
+// ----------------------------------------------------------------- rest ---
+// What the leaf kernel left, as mapped keys at their place in the output:
+// leaves with a crowded bin, which go through the tile sort's network and merge
+// rounds, and buckets the last level left larger than CAP, which one workgroup
+// sorts tile by tile and merges pairwise between the output and the workspace.
+// The latter are rare (see kDistTarget), so their loop is short rather than
+// fast.
+template <int KT, bool KV, int NT>
+__global__ __launch_bounds__(NT) void dist_rest_kernel(typename Key<KT>::U *ws, uint32_t *vws,
+                                                       typename Key<KT>::U *out, uint32_t *vout,
+                                                       const uint64_t *__restrict__ rest,
+                                                       const DistCounters *__restrict__ ctr,
+                                                       uint32_t max_rest) {
+  using U = typename Key<KT>::U;
+  using T = TileLds<KV, NT>;
+  constexpr uint32_t CAP = NT * kTileItems;
+  __shared__ U sk[T::SLOTS];
+  __shared__ uint32_t sv[KV ? T::SLOTS : 1];
+  const uint32_t tid = threadIdx.x;
+  const uint32_t no = ctr->rest < max_rest ? ctr->rest : max_rest;
+  for (uint32_t oi = blockIdx.x; oi < no; oi += gridDim.x) {
+    const uint32_t off = (uint32_t)rest[oi], len = (uint32_t)(rest[oi] >> 32);
+    const bool one = len <= CAP;
+    U *a = out + off, *c = ws + off;
+    uint32_t *va = KV ? vout + off : nullptr, *vc = KV ? vws + off : nullptr;
+    for (uint32_t base = 0; base < len; base += CAP) {
+      const uint32_t m = len - base < CAP ? len - base : CAP;
+      U k[kTileItems];
+      uint32_t v[kTileItems];
+      __syncthreads();
+      if constexpr (KV) {
+        for (uint32_t i = tid; i < CAP; i += NT) {
+          sk[pad16(i)] = i < m ? a[base + i] : key_max<U>();
+          sv[pad16(i)] = i < m ? va[base + i] : 0u;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kTileItems; ++i) {
+          k[i] = sk[pad16(tid * kTileItems + i)];
+          v[i] = sv[pad16(tid * kTileItems + i)];
+        }
+        lds_sort_pairs<U, NT>(k, v, sk, sv);
+      } else {
+#pragma unroll
+        for (int i = 0; i < kTileItems; ++i) {
+          const uint32_t idx = i * NT + tid;
+          const U x = a[base + (idx < m ? idx : m - 1)];
+          k[i] = idx < m ? x : key_max<U>();
+        }
+        lds_sort_keys<U, NT>(k, sk);
+      }
+      for (uint32_t i = tid; i < m; i += NT) {
+        a[base + i] = one ? Key<KT>::unmap(sk[i]) : sk[i];
+        if constexpr (KV) va[base + i] = sv[i];
+      }
+    }
+    if (one) continue;
+    for (uint32_t w = CAP; w < len; w *= 2) {  // (len < 2^31)
+      __syncthreads();
+      for (uint32_t t = tid * kTileItems; t < len; t += CAP) {
+        // outputs t .. t+15 of this width's pairs (which start at multiples of 16)
+        const uint32_t a0 = t / (2 * w) * (2 * w);
+        const uint32_t a1 = len - a0 < w ? len : a0 + w;
+        const uint32_t b1 = len - a1 < w ? len : a1 + w;
+        const uint32_t d = t - a0, la = a1 - a0, lb = b1 - a1;
+        uint32_t lo = d > lb ? d - lb : 0, hi = d < la ? d : la;
+        while (lo < hi) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (a[a0 + mid] <= a[a1 + d - 1 - mid]) lo = mid + 1;
+          else hi = mid;
+        }
+        uint32_t pa = a0 + lo, pb = a1 + (d - lo);
+        for (uint32_t o = t; o < t + kTileItems && o < b1; ++o) {
+          const bool left = pa < a1 && (pb >= b1 || a[pa] <= a[pb]);
+          const uint32_t from = left ? pa++ : pb++;
+          c[o] = a[from];
+          if constexpr (KV) vc[o] = va[from];
+        }
+      }
+      U *x = a;
+      a = c;
+      c = x;
+      uint32_t *y = va;
+      va = vc;
+      vc = y;
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < len; i += NT) {
+      out[off + i] = Key<KT>::unmap(a[i]);
+      if constexpr (KV) vout[off + i] = va[i];
+    }
+  }
+}
+
+// ------------------------------------------------------------ launchers ---
+// Buffers of a level: the last level writes the workspace (the leaves go from
+// there to the output), the ones before it alternate.
+bool level_to_out(const DistPlan &d, int level) { return (d.levels - level) & 1; }
+
+const void *level_src(const DistPlan &d, const DistBufs &b, int level) {
+  return level == 1 ? b.in : level_to_out(d, level - 1) ? (const void *)b.out : (const void *)b.ws;
+}
+const uint32_t *level_vsrc(const DistPlan &d, const DistBufs &b, int level) {
+  return level == 1 ? b.vin : level_to_out(d, level - 1) ? b.vout : b.vws;
+}
+
+Level level_args(const DistPlan &d, int level, char *w) {
+  Level L{};
+  L.ctr = (DistCounters *)(w + d.off_ctr);
+  L.nodes = (DistNode *)(w + d.off_nodes[level]);
+  L.ranges = (DistRange *)(w + d.off_ranges[level]);
+  L.spl = w + d.off_spl;
+  L.start = (uint32_t *)(w + d.off_start);
+  L.table = w + d.off_table;
+  L.leaves = (DistLeaf *)(w + d.off_leaves);
+  L.rest = (uint64_t *)(w + d.off_rest);
+  L.level = (uint32_t)level;
+  L.levels = (uint32_t)d.levels;
+  L.cap = d.cap;
+  L.target = d.target;
+  L.rl = d.rl[level];
+  L.src = level == d.levels ? kSrcPieces : level_to_out(d, level) ? kSrcOut : kSrcWs;
+  L.max_cols = d.max_cols;
+  L.max_leaves = d.max_leaves;
+  L.max_rest = d.max_rest;
+  if (level < d.levels) {
+    L.next_nodes = (DistNode *)(w + d.off_nodes[level + 1]);
+    L.next_ranges = (DistRange *)(w + d.off_ranges[level + 1]);
+    L.next_rl = d.rl[level + 1];
+    L.max_next_nodes = d.max_nodes[level + 1];
+    L.max_next_ranges = d.max_ranges[level + 1];
+    L.max_next_table = d.max_table[level + 1];
+  }
+  return L;
+}
+
+// Level 1 reads raw keys of type kt; later levels read mapped keys, which are
+// unsigned integers.
+int level_type(int kt, int level) { return level == 1 ? kt : key_bytes(kt) == 8 ? 2 : 0; }
+
+template <typename F> hipError_t with_type(int kt, F &&f) {
+  switch (kt) {
+    case 0: return f(std::integral_constant<int, 0>{});
+    case 1: return f(std::integral_constant<int, 1>{});
+    case 2: return f(std::integral_constant<int, 2>{});
+    case 3: return f(std::integral_constant<int, 3>{});
+    case 4: return f(std::integral_constant<int, 4>{});
+    case 5: return f(std::integral_constant<int, 5>{});
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+
+hipError_t launch_dist_sample(int kt, const DistPlan &d, int level, const DistBufs &b, uint64_t n,
+                              char *w, hipStream_t s) {
+  Level L = level_args(d, level, w);
+  if (level == 1) {
+    L.root_len = (uint32_t)n;
+    L.root_p = d.root_p;
+  }
+  const dim3 grid(d.max_nodes[level]);
+  return with_type(level_type(kt, level), [&](auto c) {
+    constexpr int KT = decltype(c)::value;
+    using U = typename Key<KT>::U;
+    const U *src = (const U *)level_src(d, b, level);
+    // the tile holds 64 samples a bucket for one short array; 16384 samples
+    // for a root whose buckets are cut again (their evenness decides how many
+    // buckets the next level can give each)
+    if (level == 1 && d.root_p <= 32)
+      hipLaunchKernelGGL((dist_sample_kernel<KT, 128>), grid, dim3(128), 0, s, src, L);
+    else if (level == 1 && d.levels > 1)
+      hipLaunchKernelGGL((dist_sample_kernel<KT, 1024>), grid, dim3(1024), 0, s, src, L);
+    else
+      hipLaunchKernelGGL((dist_sample_kernel<KT, 512>), grid, dim3(512), 0, s, src, L);
+    return hipGetLastError();
+  });
+}
+
+hipError_t launch_dist_count(int kt, const DistPlan &d, int level, const DistBufs &b, char *w,
+                             hipStream_t s) {
+  const Level L = level_args(d, level, w);
+  return with_type(level_type(kt, level), [&](auto c) {
+    constexpr int KT = decltype(c)::value;
+    using U = typename Key<KT>::U;
+    hipLaunchKernelGGL((dist_count_kernel<KT>), dim3(d.max_ranges[level]), dim3(kDistThreads), 0, s,
+                       (const U *)level_src(d, b, level), L);
+    return hipGetLastError();
+  });
+}
+
+hipError_t launch_dist_scan(int kt, const DistPlan &d, int level, char *w, hipStream_t s) {
+  const Level L = level_args(d, level, w);
+  const int summed = level == 1 && d.levels > 1;
+  if (summed) {
+    hipLaunchKernelGGL(dist_columns_kernel, dim3((kDistSlots + 3) / 4), dim3(256), 0, s, L);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (key_bytes(kt) == 8)
+    hipLaunchKernelGGL((dist_scan_kernel<uint64_t>), dim3(d.max_nodes[level]), dim3(kDistSlots), 0, s,
+                       L, summed);
+  else
+    hipLaunchKernelGGL((dist_scan_kernel<uint32_t>), dim3(d.max_nodes[level]), dim3(kDistSlots), 0, s,
+                       L, summed);
+  return hipGetLastError();
+}
+
+hipError_t launch_dist_scatter(int kt, bool kv, const DistPlan &d, int level, const DistBufs &b,
+                               char *w, hipStream_t s) {
+  const Level L = level_args(d, level, w);
+  const uint32_t *vsrc = level_vsrc(d, b, level);
+  void *dst = level_to_out(d, level) ? b.out : b.ws;
+  uint32_t *vdst = level_to_out(d, level) ? b.vout : b.vws;
+  return with_type(level_type(kt, level), [&](auto c) {
+    constexpr int KT = decltype(c)::value;
+    using U = typename Key<KT>::U;
+    const U *src = (const U *)level_src(d, b, level);
+    if (kv)
+      hipLaunchKernelGGL((dist_scatter_kernel<KT, true>), dim3(d.max_ranges[level]),
+                         dim3(kDistThreads), 0, s, src, vsrc, (U *)dst, vdst, L);
+    else
+      hipLaunchKernelGGL((dist_scatter_kernel<KT, false>), dim3(d.max_ranges[level]),
+                         dim3(kDistThreads), 0, s, src, vsrc, (U *)dst, vdst, L);
+    return hipGetLastError();
+  });
+}
+
+hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
+                                 hipStream_t s) {
+  const int level = d.levels;
+  const Level L = level_args(d, level, w);
+  const uint32_t *vsrc = level_vsrc(d, b, level);
+  const dim3 grid(d.max_ranges[level]);
+  return with_type(level_type(kt, level), [&](auto c) {
+    constexpr int KT = decltype(c)::value;
+    using U = typename Key<KT>::U;
+    const U *src = (const U *)level_src(d, b, level);
+    if (kv)
+      hipLaunchKernelGGL((dist_partition_kernel<KT, true>), grid, dim3(kDistThreads), 0, s, src, vsrc,
+                         (U *)b.ws, b.vws, L);
+    else
+      hipLaunchKernelGGL((dist_partition_kernel<KT, false>), grid, dim3(kDistThreads), 0, s, src, vsrc,
+                         (U *)b.ws, b.vws, L);
+    return hipGetLastError();
+  });
+}
+
+hipError_t launch_dist_leaves(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
+                              hipStream_t s) {
+  const Level L = level_args(d, d.levels, w);
+  const dim3 grid(d.max_leaves);
+  return with_type(kt, [&](auto c) {
+    constexpr int KT = decltype(c)::value;
+    using U = typename Key<KT>::U;
+    if (kv)
+      hipLaunchKernelGGL((dist_leaf_kernel<KT, true, 256>), grid, dim3(256), 0, s, (const U *)b.ws,
+                         b.vws, (U *)b.out, b.vout, L);
+    else
+      hipLaunchKernelGGL((dist_leaf_kernel<KT, false, 512>), grid, dim3(512), 0, s, (const U *)b.ws,
+                         b.vws, (U *)b.out, b.vout, L);
+    return hipGetLastError();
+  });
+}
+
+hipError_t launch_dist_rest(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
+                            hipStream_t s) {
+  const DistCounters *ctr = (const DistCounters *)(w + d.off_ctr);
+  const uint64_t *rest = (const uint64_t *)(w + d.off_rest);
+  // workgroups loop over the list: usually nearly empty
+  const dim3 grid(std::min<uint32_t>(d.max_rest, 768));
+  return with_type(kt, [&](auto c) {
+    constexpr int KT = decltype(c)::value;
+    using U = typename Key<KT>::U;
+    if (kv)
+      hipLaunchKernelGGL((dist_rest_kernel<KT, true, 256>), grid, dim3(256), 0, s, (U *)b.ws, b.vws,
+                         (U *)b.out, b.vout, rest, ctr, d.max_rest);
+    else
+      hipLaunchKernelGGL((dist_rest_kernel<KT, false, 512>), grid, dim3(512), 0, s, (U *)b.ws, b.vws,
+                         (U *)b.out, b.vout, rest, ctr, d.max_rest);
+    return hipGetLastError();
+  });
+}
+
+}  // namespace pss

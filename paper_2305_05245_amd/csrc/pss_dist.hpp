@@ -1,0 +1,179 @@
+// Plan and launchers of the distribution sort: an array longer than one LDS
+// tile is cut into buckets by sampled splitters, level by level, until every
+// bucket fits one workgroup, which sorts it in LDS.
+#pragma once
+#include <algorithm>
+
+#include "pss_internal.hpp"
+
+namespace pss {
+
+// One tile of a level: kDistThreads * kDistItems keys.
+constexpr int kDistThreads = 512;
+constexpr int kDistItems = 12;
+constexpr uint32_t kDistTile = kDistThreads * kDistItems;
+// Buckets of one node: at most kDistMaxPicks sampled picks, of which each may
+// add a second splitter (the next larger key, so that a frequent key gets a
+// bucket of its own), capped at kDistSlots buckets.
+constexpr uint32_t kDistMaxPicks = 384;
+constexpr uint32_t kDistSlots = 512;
+constexpr int kDistMaxLevels = 3;
+// Keys one workgroup sorts in LDS (16 a thread), and the mean bucket the
+// splitters aim at: half of it, so that a bucket cut by 20 or more samples
+// overflows about once in 10^5.
+constexpr uint32_t kDistCap = 8192, kDistCapKV = 4096;
+constexpr uint32_t kDistTarget = 4096, kDistTargetKV = 2048;
+// Most tiles of one range, and most tiles of a node of the last level (a leaf
+// lists one piece a tile; the sampled buckets stay far below).
+constexpr uint32_t kDistRangeTiles = 11;
+constexpr uint32_t kDistNodeTiles = 2048;
+
+// A stretch of keys being cut into buckets by one level.
+struct DistNode {
+  uint32_t off, len;  // its keys
+  uint32_t p;         // buckets aimed at
+  uint32_t nr;        // ranges, one workgroup each
+  uint32_t cols;      // bucket slots reserved (at most 2 p)
+  uint32_t sbase;     // first entry in the splitter and start arrays
+  uint32_t tbase;     // first entry in the level's table
+  uint32_t stride;    // table entries per bucket
+  uint32_t nb;        // buckets (splitters + 1), set by the sampling kernel
+};
+// The table of a level: before the last, keys of every bucket in every range
+// ([bucket][range], uint32, made into prefix sums); last level, where every
+// bucket starts in every tile ([bucket][tile], uint16).
+struct DistRange { uint32_t node, r; };
+// A bucket (or at most cap keys of one) to be sorted or moved, with all that
+// its workgroup needs to know.
+struct DistLeaf {
+  uint32_t off;        // its place in the output
+  uint32_t len_flags;  // length, kLeaf* flags
+  // last level: the node's keys, the bucket's first key here, and the table
+  // rows of its starts and of the next bucket's (~0: the bucket is the last)
+  uint32_t node_off, node_len, first, row, next_row;
+  uint32_t pad;
+  uint64_t below, above;  // kLeafInner: below <= key < above
+};
+struct DistCounters {
+  uint32_t nodes[kDistMaxLevels + 1], ranges[kDistMaxLevels + 1];
+  uint32_t cols[kDistMaxLevels + 1], table[kDistMaxLevels + 1];
+  uint32_t leaves, rest;
+};
+
+// Host bounds and workspace layout (byte offsets) of one distribution sort.
+struct DistPlan {
+  bool on = false;
+  int levels = 0;
+  uint32_t cap = 0, target = 0;
+  uint32_t root_p = 0;
+  uint32_t rl[kDistMaxLevels + 1] = {};  // keys of a range (whole tiles)
+  uint32_t max_nodes[kDistMaxLevels + 1] = {}, max_ranges[kDistMaxLevels + 1] = {};
+  uint32_t max_cols = 0, max_table[kDistMaxLevels + 1] = {}, max_leaves = 0, max_rest = 0;
+  size_t off_ctr = 0, off_nodes[kDistMaxLevels + 1] = {}, off_ranges[kDistMaxLevels + 1] = {};
+  size_t off_spl = 0, off_start = 0, off_table = 0, off_leaves = 0, off_rest = 0;
+  size_t end = 0;  // first byte after the distribution's arrays
+};
+
+// Smallest p with p^levels >= units.
+inline uint32_t dist_root(uint64_t units, int levels) {
+  uint64_t p = 1;
+  auto pow = [&](uint64_t x) {
+    uint64_t y = 1;
+    for (int i = 0; i < levels; ++i) y *= x;
+    return y;
+  };
+  while (pow(p) < units) ++p;
+  return (uint32_t)p;
+}
+
+// Plan of one array of n > cap keys, its arrays laid out from byte offset
+// `off` on.  One level reaches kDistMaxPicks buckets of the target size; two
+// levels are kept up to the count where a first-level bucket half as large
+// again as the mean still gets its share of second-level buckets.
+inline DistPlan dist_plan(uint64_t n, int kb, bool kv, size_t off) {
+  DistPlan d;
+  d.cap = kv ? kDistCapKV : kDistCap;
+  d.target = kv ? kDistTargetKV : kDistTarget;
+  const uint64_t units = (n + d.target - 1) / d.target;
+  d.levels = units <= kDistMaxPicks ? 1 : units <= 144000 ? 2 : 3;
+  d.root_p = std::max<uint32_t>(2, std::min(kDistMaxPicks, dist_root(units, d.levels)));
+  auto tiles = [](uint64_t x) { return (x + kDistTile - 1) / kDistTile; };
+  uint64_t nodes = 1, cols = std::min(kDistSlots, 2 * d.root_p), leaves = 0;
+  uint64_t max_cols = 0, table_bytes = 0;
+  for (int l = 1; l <= d.levels; ++l) {
+    const bool last = l == d.levels;
+    // A first level that is not the last covers the array with two ranges a CU
+    // (one round of workgroups); otherwise nodes are of uneven length, and
+    // more, shorter ranges balance better.
+    const uint64_t rt = l == 1 && !last ? tiles((n + 511) / 512)
+                                        : std::min<uint64_t>(kDistRangeTiles, tiles((n + 2047) / 2048));
+    d.rl[l] = (uint32_t)(rt * kDistTile);
+    if (l > 1) {
+      nodes = std::min<uint64_t>(cols, n / d.cap + 1);
+      cols = std::min<uint64_t>(2 * (n / d.target) + 4 * nodes, (uint64_t)kDistSlots * nodes);
+    }
+    d.max_nodes[l] = (uint32_t)nodes;
+    d.max_ranges[l] = (uint32_t)(n / d.rl[l] + nodes);
+    max_cols = std::max(max_cols, cols);
+    // rows of the table are its buckets: one root's own, at most kDistSlots of
+    // any other node; last level: padded to 8 entries
+    const uint64_t widest = l == 1 ? cols : kDistSlots;
+    const uint64_t table =
+        last ? widest * (n / kDistTile) + 9 * cols : widest * (n / d.rl[l]) + cols;
+    d.max_table[l] = (uint32_t)std::min<uint64_t>(table, 0xffffffffu);
+    table_bytes = std::max(table_bytes, table * (last ? 2 : 4));
+    leaves += cols;
+  }
+  d.max_cols = (uint32_t)max_cols;
+  d.max_leaves = (uint32_t)(leaves + n / d.cap + 1);
+  d.max_rest = d.max_leaves;  // every leaf, or buckets above cap (fewer)
+  auto take = [&](size_t bytes) {
+    const size_t o = off;
+    off += (bytes + 255) / 256 * 256;
+    return o;
+  };
+  d.off_ctr = take(sizeof(DistCounters));
+  for (int l = 1; l <= d.levels; ++l) {
+    d.off_nodes[l] = take((size_t)d.max_nodes[l] * sizeof(DistNode));
+    d.off_ranges[l] = take((size_t)d.max_ranges[l] * sizeof(DistRange));
+  }
+  d.off_spl = take((size_t)d.max_cols * kb);
+  d.off_start = take((size_t)d.max_cols * 4);
+  d.off_table = take((size_t)table_bytes);
+  d.off_leaves = take((size_t)d.max_leaves * sizeof(DistLeaf));
+  d.off_rest = take((size_t)d.max_rest * 8);
+  d.end = off;
+  return d;
+}
+
+// Keys and values of one distribution sort.
+struct DistBufs {
+  const void *in;
+  const uint32_t *vin;
+  void *ws;
+  uint32_t *vws;
+  void *out;
+  uint32_t *vout;
+};
+
+// The steps of a level and the two kernels that end the sort.  Declared weak
+// so that a host-only program can link the plan without the device code.
+#define PSS_WEAK __attribute__((weak))
+PSS_WEAK hipError_t launch_dist_sample(int kt, const DistPlan &d, int level, const DistBufs &b,
+                                       uint64_t n, char *w, hipStream_t s);
+// before the last level
+PSS_WEAK hipError_t launch_dist_count(int kt, const DistPlan &d, int level, const DistBufs &b,
+                                      char *w, hipStream_t s);
+PSS_WEAK hipError_t launch_dist_scan(int kt, const DistPlan &d, int level, char *w, hipStream_t s);
+PSS_WEAK hipError_t launch_dist_scatter(int kt, bool kv, const DistPlan &d, int level,
+                                        const DistBufs &b, char *w, hipStream_t s);
+// last level (its launch_dist_scan follows)
+PSS_WEAK hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, const DistBufs &b,
+                                          char *w, hipStream_t s);
+PSS_WEAK hipError_t launch_dist_leaves(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
+                                       hipStream_t s);
+PSS_WEAK hipError_t launch_dist_rest(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
+                                     hipStream_t s);
+#undef PSS_WEAK
+
+}  // namespace pss

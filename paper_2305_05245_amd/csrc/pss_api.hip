@@ -219,7 +219,7 @@ pss_status make_plan(pss_key_t key, pss_val_t val, uint64_t n, uint32_t n_blocks
   }
   p->total = off;
   if (!p->paper && n >= kDistMinKeys && pss::launch_dist_sample) {
-    p->dist = pss::dist_plan(n, p->kb, p->kv, p->off_table);
+    p->dist = pss::dist_plan(n, n, 0, p->kb, p->kv, p->off_table);
     p->dist.on = p->dist.end <= p->total;
   }
   return PSS_OK;
@@ -426,21 +426,17 @@ pss_status paper_partition_search(pss_ctx *ctx, const Plan &p, int kt, const voi
   return PSS_OK;
 }
 
-// Distribution sort of p.n keys (and values) from keys_in into keys_out: the
+// Levels, leaves and rest of a distribution sort of n keys (and values): the
 // levels alternate between the workspace and the output, the leaves are sorted
 // from wherever their level left them into the output.
-pss_status run_dist_sort(pss_ctx *ctx, const Plan &p, int kt, const void *keys_in,
-                         const uint32_t *vals_in, void *keys_out, uint32_t *vals_out, char *w,
-                         hipStream_t s) {
-  const pss::DistPlan &d = p.dist;
-  const uint64_t kbytes = p.n * (uint64_t)p.kb;
-  const uint64_t sweep = 2 * p.n * ((uint64_t)p.kb + (p.kv ? 4 : 0));
-  const pss::DistBufs b{keys_in, vals_in, w + p.off_keys0, (uint32_t *)(w + p.off_vals0),
-                        keys_out, vals_out};
+pss_status run_dist_levels(pss_ctx *ctx, const pss::DistPlan &d, int kt, bool kv,
+                           const pss::DistBufs &b, uint64_t n, char *w, hipStream_t s) {
+  const uint64_t kbytes = n * (uint64_t)pss::key_bytes(kt);
+  const uint64_t sweep = 2 * (kbytes + (kv ? 4 * n : 0));
   for (int l = 1; l <= d.levels; ++l) {
     {
       LaunchTimer t(ctx, "dist_sample", 0, s);
-      PSS_LAUNCH(pss::launch_dist_sample(kt, d, l, b, p.n, w, s), "sample launch");
+      PSS_LAUNCH(pss::launch_dist_sample(kt, d, l, b, n, w, s), "sample launch");
     }
     if (l < d.levels) {
       {
@@ -452,11 +448,11 @@ pss_status run_dist_sort(pss_ctx *ctx, const Plan &p, int kt, const void *keys_i
         PSS_LAUNCH(pss::launch_dist_scan(kt, d, l, w, s), "scan launch");
       }
       LaunchTimer t(ctx, "dist_scatter", sweep, s);
-      PSS_LAUNCH(pss::launch_dist_scatter(kt, p.kv, d, l, b, w, s), "scatter launch");
+      PSS_LAUNCH(pss::launch_dist_scatter(kt, kv, d, l, b, w, s), "scatter launch");
     } else {
       {
         LaunchTimer t(ctx, "dist_partition", sweep, s);
-        PSS_LAUNCH(pss::launch_dist_partition(kt, p.kv, d, b, w, s), "partition launch");
+        PSS_LAUNCH(pss::launch_dist_partition(kt, kv, d, b, w, s), "partition launch");
       }
       LaunchTimer t(ctx, "dist_scan", 0, s);
       PSS_LAUNCH(pss::launch_dist_scan(kt, d, l, w, s), "scan launch");
@@ -464,12 +460,10 @@ pss_status run_dist_sort(pss_ctx *ctx, const Plan &p, int kt, const void *keys_i
   }
   {
     LaunchTimer t(ctx, "dist_leaves", sweep, s);
-    PSS_LAUNCH(pss::launch_dist_leaves(kt, p.kv, d, b, w, s), "leaf sort launch");
+    PSS_LAUNCH(pss::launch_dist_leaves(kt, kv, d, b, w, s), "leaf sort launch");
   }
-  {
-    LaunchTimer t(ctx, "dist_rest", 0, s);
-    PSS_LAUNCH(pss::launch_dist_rest(kt, p.kv, d, b, w, s), "rest sort launch");
-  }
+  LaunchTimer t(ctx, "dist_rest", 0, s);
+  PSS_LAUNCH(pss::launch_dist_rest(kt, kv, d, b, w, s), "rest sort launch");
   return PSS_OK;
 }
 
@@ -479,7 +473,11 @@ pss_status run_dist_sort(pss_ctx *ctx, const Plan &p, int kt, const void *keys_i
 pss_status run_auto_sort(pss_ctx *ctx, const Plan &p, int kt, const void *keys_in,
                          const uint32_t *vals_in, void *keys_out, uint32_t *vals_out, char *w,
                          hipStream_t s) {
-  if (p.dist.on) return run_dist_sort(ctx, p, kt, keys_in, vals_in, keys_out, vals_out, w, s);
+  if (p.dist.on) {
+    const pss::DistBufs b{keys_in, vals_in, w + p.off_keys0, (uint32_t *)(w + p.off_vals0),
+                          keys_out, vals_out};
+    return run_dist_levels(ctx, p.dist, kt, p.kv, b, p.n, w, s);
+  }
   const size_t P = p.passes.size();
   KeyBufs kb;
   ValBufs vb;
@@ -1003,6 +1001,10 @@ struct SegPlan {
   uint64_t ns = 0;                  // bound on samples
   size_t off_keys = 0, off_vals = 0, off_plan = 0, off_samples = 0, off_skeys = 0;
   size_t off_sruns = 0, off_table = 0, off_stable = 0, off_prefix = 0, total = 0;
+  // segments above one tile: the distribution sort, whose arrays take the
+  // place of the merge passes' tables (used when they fit there)
+  pss::DistPlan dist;
+  uint64_t longest = 0;  // longest segment the merge passes reach
 };
 
 uint32_t passes_for(uint64_t L, uint32_t fan_log2, uint32_t tile) {
@@ -1089,6 +1091,11 @@ pss_status make_seg_plan(const pss_ctx *ctx, pss_key_t key, pss_val_t val, uint6
     sp->off_prefix = take(max_sparts * (pss::kPart / pss::kChunk) * (1u << f) * sizeof(uint32_t));
   }
   sp->total = off;
+  sp->longest = std::min<uint64_t>((uint64_t)sp->tile << (f * sp->max_passes), n);
+  if (sp->max_passes && pss::launch_dist_segments) {
+    sp->dist = pss::dist_plan(n, max_len, n_segs, kb, kv, sp->off_plan);
+    sp->dist.on = sp->dist.end <= sp->total;
+  }
   return PSS_OK;
 }
 
@@ -1157,6 +1164,21 @@ pss_status pss_segmented_sort(pss_ctx *ctx, pss_key_t key, pss_val_t val, const 
   hipStream_t s = (hipStream_t)stream;
   const int kt = (int)key;
   char *w = (char *)ws;
+  if (sp.dist.on) {
+    const pss::DistPlan &d = sp.dist;
+    const pss::DistBufs b{keys_in, vals_in, w + sp.off_keys, (uint32_t *)(w + sp.off_vals), keys_out,
+                          vals_out};
+    {
+      LaunchTimer t(ctx, "segment_plan", (uint64_t)n_segs * 16, s);
+      PSS_LAUNCH(pss::launch_dist_segments(d, seg_offsets, n, sp.small0, sp.small1, sp.longest, w, s),
+              "segment plan launch");
+    }
+    {
+      LaunchTimer t(ctx, "tile_sort", 0, s);
+      PSS_LAUNCH(pss::launch_dist_small(kt, kv, d, b, seg_offsets, w, s), "tile sort launch");
+    }
+    return run_dist_levels(ctx, d, kt, kv, b, n, w, s);
+  }
   const pss::SegPlanPtrs pp = seg_plan_ptrs(w, sp, n_segs);
   void *kws = w + sp.off_keys;
   uint32_t *vws = kv ? (uint32_t *)(w + sp.off_vals) : nullptr;

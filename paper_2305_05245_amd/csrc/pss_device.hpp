@@ -1,6 +1,7 @@
 // Device code shared by the kernel files: the order-preserving key maps,
 // register sorting networks, chunk merges and the LDS sort of one tile.
 #pragma once
+#include "pss_dist.hpp"
 #include "pss_internal.hpp"
 
 namespace pss {
@@ -532,6 +533,26 @@ __device__ __forceinline__ void lds_sort_keys(U (&rk)[kTileItems], U *sk) {
     }
     __syncthreads();
   }
+}
+
+// ------------------------------------------- nodes of the distribution ---
+// p of a node: its share of the buckets the remaining levels have to reach.
+__device__ __forceinline__ uint32_t node_picks(uint32_t len, uint32_t target, int remaining) {
+  const uint32_t units = (len + target - 1) / target;
+  uint32_t p = units;
+  if (remaining == 2) p = (uint32_t)ceilf(sqrtf((float)units));
+  else if (remaining >= 3) p = (uint32_t)ceilf(cbrtf((float)units));
+  return p < 2 ? 2 : (p > kDistMaxPicks ? kDistMaxPicks : p);
+}
+
+__device__ __forceinline__ uint32_t node_cols(uint32_t p) {
+  return 2 * p < kDistSlots ? 2 * p : kDistSlots;
+}
+
+// Table entries per bucket: one a range, or (last level) one a tile, padded so
+// that every bucket's entries start on 16 bytes.
+__device__ __forceinline__ uint32_t node_stride(uint32_t len, uint32_t nr, bool last) {
+  return last ? ((len + kDistTile - 1) / kDistTile + 7) / 8 * 8 : nr;
 }
 
 }  // namespace

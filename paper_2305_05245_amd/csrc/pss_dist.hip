@@ -41,14 +41,6 @@ namespace {
 
 constexpr uint32_t kLutBins = 1024;
 
-// DistLeaf::len_flags
-constexpr uint32_t kLeafLenMask = 0xffffu;
-constexpr uint32_t kLeafEqual = 1u << 16;  // one key value: unmapped, not sorted
-constexpr uint32_t kLeafMove = 1u << 17;   // part of a rest entry: moved to the output
-constexpr uint32_t kLeafInner = 1u << 18;  // the splitters around it bound its keys
-constexpr int kLeafSrcShift = 19;          // where its keys are:
-constexpr uint32_t kSrcWs = 0, kSrcOut = 1, kSrcPieces = 2;
-
 // Arguments of one level's kernels.
 struct Level {
   DistCounters *ctr;
@@ -61,6 +53,7 @@ struct Level {
   uint64_t *rest;  // offset | length << 32, mapped keys in the output
   uint32_t level, levels, cap, target, rl, next_rl;
   uint32_t src;  // kSrc* of this level's leaves
+  uint32_t node_tiles;  // most tiles of a last-level node
   uint32_t max_next_nodes, max_next_ranges, max_cols, max_next_table, max_leaves, max_rest;
   uint32_t root_len, root_p;  // level 1 of a single array (0: nodes are given)
 };
@@ -98,32 +91,13 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *wsum, uint3
   return before + x - v;
 }
 
-// p of a node: its share of the buckets the remaining levels have to reach.
-__device__ __forceinline__ uint32_t node_picks(uint32_t len, uint32_t target, int remaining) {
-  const uint32_t units = (len + target - 1) / target;
-  uint32_t p = units;
-  if (remaining == 2) p = (uint32_t)ceilf(sqrtf((float)units));
-  else if (remaining >= 3) p = (uint32_t)ceilf(cbrtf((float)units));
-  return p < 2 ? 2 : (p > kDistMaxPicks ? kDistMaxPicks : p);
-}
-
-__device__ __forceinline__ uint32_t node_cols(uint32_t p) {
-  return 2 * p < kDistSlots ? 2 * p : kDistSlots;
-}
-
-// Table entries per bucket: one a range, or (last level) one a tile, padded so
-// that every bucket's entries start on 16 bytes.
-__device__ __forceinline__ uint32_t node_stride(uint32_t len, uint32_t nr, bool last) {
-  return last ? ((len + kDistTile - 1) / kDistTile + 7) / 8 * 8 : nr;
-}
-
 // ------------------------------------------------------------- sampling ---
 // One workgroup per node; latency-bound (a few random loads a thread, then
 // one LDS sort).  The picks come from S sorted samples, S a power of two of at
 // least 20 per bucket, at most one tile.
 template <int KT, int NT>
 __global__ __launch_bounds__(NT) void dist_sample_kernel(const typename Key<KT>::U *__restrict__ src,
-                                                         Level L) {
+                                                         Level L, uint32_t p_lo, uint32_t p_hi) {
   using U = typename Key<KT>::U;
   constexpr uint32_t TILE = NT * kTileItems;
   __shared__ U sk[TileLds<false, NT>::SLOTS];
@@ -150,6 +124,7 @@ __global__ __launch_bounds__(NT) void dist_sample_kernel(const typename Key<KT>:
   } else {
     if (blockIdx.x >= L.ctr->nodes[L.level]) return;
     nd = L.nodes[blockIdx.x];
+    if (nd.p < p_lo || nd.p > p_hi) return;  // another tile size samples it
   }
   uint32_t want = 64 * nd.p < TILE ? 64 * nd.p : TILE;
   want = nd.len / 2 < want ? nd.len / 2 : want;
@@ -404,7 +379,7 @@ __global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summ
     hi = b < ns ? spl[b] : U(0);
     equal = b < ns ? hi - lo == 1 : lo == key_max<U>();
     const bool fits = len <= L.cap;
-    node = !last && !equal && !fits && !(next_last && len > kDistNodeTiles * kDistTile);
+    node = !last && !equal && !fits && !(next_last && len > L.node_tiles * kDistTile);
     rest = !equal && !fits && !node;
     // (before the last level a rest entry already lies in the output)
     pieces = node || (rest && !last) ? 0u : (len + L.cap - 1) / L.cap;
@@ -721,6 +696,7 @@ constexpr uint32_t kCrowded = 24;
 
 template <int KT, bool KV, int NT>
 __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
+    const typename Key<KT>::U *__restrict__ in, const uint32_t *__restrict__ vin,
     const typename Key<KT>::U *__restrict__ ws, const uint32_t *__restrict__ vws,
     typename Key<KT>::U *out, uint32_t *vout, Level L) {
   using U = typename Key<KT>::U;
@@ -739,7 +715,7 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
   uint32_t *piece = reinterpret_cast<uint32_t *>(sk);  // address - position
   uint32_t *mask = bins;                               // CAP bits: a piece starts at the next position
   uint16_t *row_piece = reinterpret_cast<uint16_t *>(bins + CAP / 32);  // piece of position 64 r
-  static_assert(kDistNodeTiles * 4 <= sizeof(sk), "pieces fit the key area");
+  static_assert(dist_node_tiles(sizeof(U), KV) * 4 <= sizeof(sk), "pieces fit the key area");
   static_assert(CAP / 8 + CAP / 32 <= sizeof(bins), "mask and rows fit the bins");
   const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const uint32_t nl = L.ctr->leaves < L.max_leaves ? L.ctr->leaves : L.max_leaves;
@@ -760,8 +736,8 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
   const uint32_t off = leaf.off, len = leaf.len_flags & kLeafLenMask;
   const uint32_t from = (leaf.len_flags >> kLeafSrcShift) & 3u;
   const bool inner = from == kSrcPieces && (leaf.len_flags & kLeafInner);
-  const U *p = from == kSrcOut ? (const U *)out : ws;
-  const uint32_t *vp = from == kSrcOut ? (const uint32_t *)vout : vws;
+  const U *p = from == kSrcOut ? (const U *)out : from == kSrcIn ? in : ws;
+  const uint32_t *vp = from == kSrcOut ? (const uint32_t *)vout : from == kSrcIn ? vin : vws;
   U k[kTileItems];
   uint32_t v[KV ? kTileItems : 1];
   uint32_t addr[kTileItems];
@@ -827,6 +803,11 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
       k[i] = __builtin_nontemporal_load(&p[addr[i]]);
       if constexpr (KV) v[i] = __builtin_nontemporal_load(&vp[addr[i]]);
     }
+  }
+  if (from == kSrcIn) {
+#pragma unroll
+    for (int i = 0; i < kTileItems; ++i)
+      if (i * NT < len) k[i] = Key<KT>::map(k[i]);
   }
   if (leaf.len_flags & (kLeafEqual | kLeafMove)) {
     const bool equal = leaf.len_flags & kLeafEqual;
@@ -1112,7 +1093,7 @@ const uint32_t *level_vsrc(const DistPlan &d, const DistBufs &b, int level) {
   return level == 1 ? b.vin : level_to_out(d, level - 1) ? b.vout : b.vws;
 }
 
-Level level_args(const DistPlan &d, int level, char *w) {
+Level level_args(int kt, const DistPlan &d, int level, char *w) {
   Level L{};
   L.ctr = (DistCounters *)(w + d.off_ctr);
   L.nodes = (DistNode *)(w + d.off_nodes[level]);
@@ -1128,6 +1109,7 @@ Level level_args(const DistPlan &d, int level, char *w) {
   L.target = d.target;
   L.rl = d.rl[level];
   L.src = level == d.levels ? kSrcPieces : level_to_out(d, level) ? kSrcOut : kSrcWs;
+  L.node_tiles = dist_node_tiles(key_bytes(kt), d.cap == kDistCapKV);
   L.max_cols = d.max_cols;
   L.max_leaves = d.max_leaves;
   L.max_rest = d.max_rest;
@@ -1162,8 +1144,8 @@ template <typename F> hipError_t with_type(int kt, F &&f) {
 
 hipError_t launch_dist_sample(int kt, const DistPlan &d, int level, const DistBufs &b, uint64_t n,
                               char *w, hipStream_t s) {
-  Level L = level_args(d, level, w);
-  if (level == 1) {
+  Level L = level_args(kt, d, level, w);
+  if (level == 1 && !d.n_segs) {
     L.root_len = (uint32_t)n;
     L.root_p = d.root_p;
   }
@@ -1172,22 +1154,30 @@ hipError_t launch_dist_sample(int kt, const DistPlan &d, int level, const DistBu
     constexpr int KT = decltype(c)::value;
     using U = typename Key<KT>::U;
     const U *src = (const U *)level_src(d, b, level);
-    // the tile holds 64 samples a bucket for one short array; 16384 samples
-    // for a root whose buckets are cut again (their evenness decides how many
-    // buckets the next level can give each)
-    if (level == 1 && d.root_p <= 32)
-      hipLaunchKernelGGL((dist_sample_kernel<KT, 128>), grid, dim3(128), 0, s, src, L);
-    else if (level == 1 && d.levels > 1)
-      hipLaunchKernelGGL((dist_sample_kernel<KT, 1024>), grid, dim3(1024), 0, s, src, L);
-    else
-      hipLaunchKernelGGL((dist_sample_kernel<KT, 512>), grid, dim3(512), 0, s, src, L);
-    return hipGetLastError();
+    // 64 samples a bucket fit a tile of 2048 up to 32 buckets, which short
+    // segments take: many of its workgroups fit a CU at once; 16384 samples for a root whose buckets are cut again
+    // (their evenness decides how many buckets the next level can give each)
+    const uint32_t few = 32, all = kDistMaxPicks;
+    auto go = [&](auto nt, uint32_t lo, uint32_t hi) -> hipError_t {
+      constexpr int NT = decltype(nt)::value;
+      hipLaunchKernelGGL((dist_sample_kernel<KT, NT>), grid, dim3(NT), 0, s, src, L, lo, hi);
+      return hipGetLastError();
+    };
+    using N128 = std::integral_constant<int, 128>;
+    using N512 = std::integral_constant<int, 512>;
+    using N1024 = std::integral_constant<int, 1024>;
+    if (L.root_len)
+      return d.root_p <= few ? go(N128{}, 0, all) : d.levels > 1 ? go(N1024{}, 0, all) : go(N512{}, 0, all);
+    if (level > 1) return go(N512{}, 0, all);  // (few nodes: a second launch costs more)
+    const hipError_t e = go(N128{}, 0, few);
+    if (e != hipSuccess) return e;
+    return go(N512{}, few + 1, all);
   });
 }
 
 hipError_t launch_dist_count(int kt, const DistPlan &d, int level, const DistBufs &b, char *w,
                              hipStream_t s) {
-  const Level L = level_args(d, level, w);
+  const Level L = level_args(kt, d, level, w);
   return with_type(level_type(kt, level), [&](auto c) {
     constexpr int KT = decltype(c)::value;
     using U = typename Key<KT>::U;
@@ -1198,8 +1188,8 @@ hipError_t launch_dist_count(int kt, const DistPlan &d, int level, const DistBuf
 }
 
 hipError_t launch_dist_scan(int kt, const DistPlan &d, int level, char *w, hipStream_t s) {
-  const Level L = level_args(d, level, w);
-  const int summed = level == 1 && d.levels > 1;
+  const Level L = level_args(kt, d, level, w);
+  const int summed = level == 1 && d.levels > 1 && !d.n_segs;
   if (summed) {
     hipLaunchKernelGGL(dist_columns_kernel, dim3((kDistSlots + 3) / 4), dim3(256), 0, s, L);
     const hipError_t e = hipGetLastError();
@@ -1216,7 +1206,7 @@ hipError_t launch_dist_scan(int kt, const DistPlan &d, int level, char *w, hipSt
 
 hipError_t launch_dist_scatter(int kt, bool kv, const DistPlan &d, int level, const DistBufs &b,
                                char *w, hipStream_t s) {
-  const Level L = level_args(d, level, w);
+  const Level L = level_args(kt, d, level, w);
   const uint32_t *vsrc = level_vsrc(d, b, level);
   void *dst = level_to_out(d, level) ? b.out : b.ws;
   uint32_t *vdst = level_to_out(d, level) ? b.vout : b.vws;
@@ -1237,7 +1227,7 @@ hipError_t launch_dist_scatter(int kt, bool kv, const DistPlan &d, int level, co
 hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
                                  hipStream_t s) {
   const int level = d.levels;
-  const Level L = level_args(d, level, w);
+  const Level L = level_args(kt, d, level, w);
   const uint32_t *vsrc = level_vsrc(d, b, level);
   const dim3 grid(d.max_ranges[level]);
   return with_type(level_type(kt, level), [&](auto c) {
@@ -1256,17 +1246,17 @@ hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, const DistB
 
 hipError_t launch_dist_leaves(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
                               hipStream_t s) {
-  const Level L = level_args(d, d.levels, w);
+  const Level L = level_args(kt, d, d.levels, w);
   const dim3 grid(d.max_leaves);
   return with_type(kt, [&](auto c) {
     constexpr int KT = decltype(c)::value;
     using U = typename Key<KT>::U;
     if (kv)
-      hipLaunchKernelGGL((dist_leaf_kernel<KT, true, 256>), grid, dim3(256), 0, s, (const U *)b.ws,
-                         b.vws, (U *)b.out, b.vout, L);
+      hipLaunchKernelGGL((dist_leaf_kernel<KT, true, 256>), grid, dim3(256), 0, s, (const U *)b.in,
+                         b.vin, (const U *)b.ws, b.vws, (U *)b.out, b.vout, L);
     else
-      hipLaunchKernelGGL((dist_leaf_kernel<KT, false, 512>), grid, dim3(512), 0, s, (const U *)b.ws,
-                         b.vws, (U *)b.out, b.vout, L);
+      hipLaunchKernelGGL((dist_leaf_kernel<KT, false, 512>), grid, dim3(512), 0, s, (const U *)b.in,
+                         b.vin, (const U *)b.ws, b.vws, (U *)b.out, b.vout, L);
     return hipGetLastError();
   });
 }

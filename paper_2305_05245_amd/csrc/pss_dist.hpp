@@ -23,10 +23,13 @@ constexpr int kDistMaxLevels = 3;
 // overflows about once in 10^5.
 constexpr uint32_t kDistCap = 8192, kDistCapKV = 4096;
 constexpr uint32_t kDistTarget = 4096, kDistTargetKV = 2048;
-// Most tiles of one range, and most tiles of a node of the last level (a leaf
-// lists one piece a tile; the sampled buckets stay far below).
+// Most tiles of one range.
 constexpr uint32_t kDistRangeTiles = 11;
-constexpr uint32_t kDistNodeTiles = 2048;
+// Most tiles of a node of the last level: a leaf lists one piece a tile in the
+// LDS its keys take later (16 a thread).  Sampled nodes stay far below.
+inline constexpr uint32_t dist_node_tiles(int kb, bool kv) {
+  return (kv ? kDistCapKV : kDistCap) * (uint32_t)kb / 4;
+}
 
 // A stretch of keys being cut into buckets by one level.
 struct DistNode {
@@ -58,19 +61,29 @@ struct DistCounters {
   uint32_t nodes[kDistMaxLevels + 1], ranges[kDistMaxLevels + 1];
   uint32_t cols[kDistMaxLevels + 1], table[kDistMaxLevels + 1];
   uint32_t leaves, rest;
+  uint32_t small[2];  // segments of the two smallest classes
 };
+
+// DistLeaf::len_flags
+constexpr uint32_t kLeafLenMask = 0xffffu;
+constexpr uint32_t kLeafEqual = 1u << 16;  // one key value: unmapped, not sorted
+constexpr uint32_t kLeafMove = 1u << 17;   // part of a rest entry: moved to the output
+constexpr uint32_t kLeafInner = 1u << 18;  // the splitters around it bound its keys
+constexpr int kLeafSrcShift = 19;          // where its keys are:
+constexpr uint32_t kSrcWs = 0, kSrcOut = 1, kSrcPieces = 2, kSrcIn = 3;  // (kSrcIn: not mapped)
 
 // Host bounds and workspace layout (byte offsets) of one distribution sort.
 struct DistPlan {
   bool on = false;
   int levels = 0;
   uint32_t cap = 0, target = 0;
-  uint32_t root_p = 0;
+  uint32_t root_p = 0;    // most buckets aimed at in a first-level node
+  uint32_t n_segs = 0;    // segmented: segments (0: one array)
   uint32_t rl[kDistMaxLevels + 1] = {};  // keys of a range (whole tiles)
   uint32_t max_nodes[kDistMaxLevels + 1] = {}, max_ranges[kDistMaxLevels + 1] = {};
   uint32_t max_cols = 0, max_table[kDistMaxLevels + 1] = {}, max_leaves = 0, max_rest = 0;
   size_t off_ctr = 0, off_nodes[kDistMaxLevels + 1] = {}, off_ranges[kDistMaxLevels + 1] = {};
-  size_t off_spl = 0, off_start = 0, off_table = 0, off_leaves = 0, off_rest = 0;
+  size_t off_spl = 0, off_start = 0, off_table = 0, off_leaves = 0, off_rest = 0, off_small = 0;
   size_t end = 0;  // first byte after the distribution's arrays
 };
 
@@ -86,20 +99,24 @@ inline uint32_t dist_root(uint64_t units, int levels) {
   return (uint32_t)p;
 }
 
-// Plan of one array of n > cap keys, its arrays laid out from byte offset
-// `off` on.  One level reaches kDistMaxPicks buckets of the target size; two
-// levels are kept up to the count where a first-level bucket half as large
-// again as the mean still gets its share of second-level buckets.
-inline DistPlan dist_plan(uint64_t n, int kb, bool kv, size_t off) {
+// Plan of n keys in arrays of at most max_len > cap keys (one array: max_len =
+// n and n_segs = 0), laid out from byte offset `off` on.  One level reaches
+// kDistMaxPicks buckets of the target size; two levels are kept up to the
+// count where a first-level bucket half as large again as the mean still gets
+// its share of second-level buckets.
+inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb, bool kv, size_t off) {
   DistPlan d;
   d.cap = kv ? kDistCapKV : kDistCap;
   d.target = kv ? kDistTargetKV : kDistTarget;
-  const uint64_t units = (n + d.target - 1) / d.target;
+  d.n_segs = n_segs;
+  const uint64_t units = (max_len + d.target - 1) / d.target;
   d.levels = units <= kDistMaxPicks ? 1 : units <= 144000 ? 2 : 3;
   d.root_p = std::max<uint32_t>(2, std::min(kDistMaxPicks, dist_root(units, d.levels)));
   auto tiles = [](uint64_t x) { return (x + kDistTile - 1) / kDistTile; };
-  uint64_t nodes = 1, cols = std::min(kDistSlots, 2 * d.root_p), leaves = 0;
-  uint64_t max_cols = 0, table_bytes = 0;
+  // (segments up to cap keys are no nodes)
+  uint64_t nodes = n_segs ? std::min<uint64_t>(n_segs, n / d.cap + 1) : 1;
+  uint64_t cols = n_segs ? 2 * (n / d.target) + 4 * nodes : std::min(kDistSlots, 2 * d.root_p);
+  uint64_t leaves = n_segs, max_cols = 0, table_bytes = 0;
   for (int l = 1; l <= d.levels; ++l) {
     const bool last = l == d.levels;
     // A first level that is not the last covers the array with two ranges a CU
@@ -115,9 +132,9 @@ inline DistPlan dist_plan(uint64_t n, int kb, bool kv, size_t off) {
     d.max_nodes[l] = (uint32_t)nodes;
     d.max_ranges[l] = (uint32_t)(n / d.rl[l] + nodes);
     max_cols = std::max(max_cols, cols);
-    // rows of the table are its buckets: one root's own, at most kDistSlots of
-    // any other node; last level: padded to 8 entries
-    const uint64_t widest = l == 1 ? cols : kDistSlots;
+    // rows of the table are its buckets: at most 2 root_p in the first level,
+    // kDistSlots later; last level: padded to 8 entries
+    const uint64_t widest = l == 1 ? std::min(kDistSlots, 2 * d.root_p) : kDistSlots;
     const uint64_t table =
         last ? widest * (n / kDistTile) + 9 * cols : widest * (n / d.rl[l]) + cols;
     d.max_table[l] = (uint32_t)std::min<uint64_t>(table, 0xffffffffu);
@@ -142,6 +159,7 @@ inline DistPlan dist_plan(uint64_t n, int kb, bool kv, size_t off) {
   d.off_table = take((size_t)table_bytes);
   d.off_leaves = take((size_t)d.max_leaves * sizeof(DistLeaf));
   d.off_rest = take((size_t)d.max_rest * 8);
+  d.off_small = take((size_t)n_segs * 8);
   d.end = off;
   return d;
 }
@@ -156,9 +174,17 @@ struct DistBufs {
   uint32_t *vout;
 };
 
-// The steps of a level and the two kernels that end the sort.  Declared weak
+// Segmented: reads the segment offsets, and writes the first level's nodes and
+// ranges, the leaves of segments of at most cap keys above small1, and the
+// lists of those up to small0 and small1 (sorted by launch_dist_small).  The
+// steps of a level and the two kernels that end the sort follow.  Declared weak
 // so that a host-only program can link the plan without the device code.
 #define PSS_WEAK __attribute__((weak))
+PSS_WEAK hipError_t launch_dist_segments(const DistPlan &d, const uint64_t *seg_off, uint64_t n,
+                                         uint32_t small0, uint32_t small1, uint64_t longest, char *w,
+                                         hipStream_t s);
+PSS_WEAK hipError_t launch_dist_small(int kt, bool kv, const DistPlan &d, const DistBufs &b,
+                                      const uint64_t *seg_off, char *w, hipStream_t s);
 PSS_WEAK hipError_t launch_dist_sample(int kt, const DistPlan &d, int level, const DistBufs &b,
                                        uint64_t n, char *w, hipStream_t s);
 // before the last level

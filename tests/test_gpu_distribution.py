@@ -127,3 +127,67 @@ def test_buckets_the_samples_miss(n, samples, kv):
         keys[_sample_positions(n, s)] = np.uint64(1 << 63)
     announce("distribution, samples miss", n, "kv" if kv else "keys")
     check(keys, kv)
+
+
+def _segmented(keys, sizes, vals=None, max_seg_len=None):
+    """(sorted keys, sorted values, device error word) of one segmented sort
+    on a poisoned workspace."""
+    import torch
+
+    import paper_2305_05245_amd as pss
+    from gpu_util import KEY_OF_DTYPE, from_device, poisoned_workspace, to_device
+    from paper_2305_05245_amd import _lib
+
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    kt = _lib.KEY_NAMES[KEY_OF_DTYPE[keys.dtype]]
+    vt = _lib.VAL_NONE if vals is None else _lib.VAL_U32
+    tu = _lib.Tuning(2048, 4096, int(max_seg_len or max(sizes)), 0, 0)
+    ws = poisoned_workspace(_lib.segmented_workspace_bytes(kt, vt, keys.size, len(sizes), tu))
+    out, vout = pss.segmented_sort(to_device(keys), torch.from_numpy(offs).cuda(),
+                                   None if vals is None else to_device(vals), key_type=kt, tuning=tu,
+                                   workspace=ws)
+    torch.cuda.synchronize()
+    return (from_device(out, keys.dtype), None if vals is None else from_device(vout, np.uint32),
+            pss.device_check(0), offs)
+
+
+EDGES = [4096, 4097, 8192, 8193, 0, 3 * TILE, 3 * TILE + 1, 2048, 2049, 50_000, 1, 33 * 4096, 65 * TILE - 1]
+
+
+@pytest.mark.parametrize("longest", [EDGES[-1], MAX_PICKS * TARGET, MAX_PICKS * TARGET + 1],
+                         ids=["short", "one level", "two levels"])
+@pytest.mark.parametrize("dtype", [np.uint32, np.int64], ids=lambda d: np.dtype(d).name)
+def test_segments(dtype, longest):
+    """Segments on both sides of every class: the two short ones, one leaf, a
+    node of one tile and of several, nodes of few and of many buckets, and
+    with a longer one in the batch the last single level and two levels."""
+    sizes = EDGES + ([longest] if longest > max(EDGES) else [])
+    rng = np.random.default_rng(longest)
+    keys = random_keys(rng, dtype, sum(sizes))
+    vals = rng.permutation(keys.size).astype(np.uint32)
+    for v in (None, vals):
+        announce("distribution segments", np.dtype(dtype).name, longest, "keys" if v is None else "kv")
+        got, vgot, err, offs = _segmented(keys, sizes, v)
+        assert err == 0
+        for lo, hi in zip(offs[:-1], offs[1:]):
+            perm = np.argsort(order_bits(keys[lo:hi]), kind="stable")
+            assert got[lo:hi].tobytes() == keys[lo:hi][perm].tobytes()
+            if v is not None:
+                assert np.array_equal(vgot[lo:hi], vals[lo:hi][perm])
+
+
+def test_segment_length_bound_too_small():
+    """A bound on the segment length below the longest segment: up to the
+    length that takes as many merge passes as the bound, the segment is sorted
+    all the same; a longer one is left out and reported, the others are
+    sorted."""
+    rng = np.random.default_rng(3)
+    for longest, reported in ((200_000, False), (32 * 8192 + 1, True)):
+        sizes = [9000, longest, 100, 8200]
+        keys = random_keys(rng, np.int64, sum(sizes))
+        announce("distribution segments, bound 9000, longest", longest)
+        got, _, err, offs = _segmented(keys, sizes, max_seg_len=9000)
+        assert (err != 0) == reported and (err & 16 != 0) == reported
+        for i, (lo, hi) in enumerate(zip(offs[:-1], offs[1:])):
+            if not (reported and i == 1):
+                assert np.array_equal(got[lo:hi], np.sort(keys[lo:hi]))

@@ -27,7 +27,7 @@
 // too large is sorted by merging through memory.
 //
 // At 2^28 int64 uniform keys (ms): samples 0.22, count 0.43, scatter 1.48,
-// partition 0.90, leaves 1.77; the sort 4.80, against 7.31 for the merge plan's
+// partition 0.90, leaves 1.52; the sort 4.54, against 7.31 for the merge plan's
 // tile sort (1.71) and three merge passes (1.88 each with their searches).
 //
 // Key-value sorts place equal keys in input order at every step (the ranges
@@ -685,14 +685,78 @@ __device__ __forceinline__ DistLeaf uniform(const DistLeaf &f) {
 // One workgroup sorts one leaf of at most CAP = 16 NT keys.  The keys are
 // binned by interpolation between the bounds of the leaf (CAP bins, one key in
 // two bins when the leaf has its target size), placed in bin order in LDS, and
-// each key's final place is counted within its bin.  A leaf with a crowded bin
-// (a key of rank kCrowded or more: many equal keys, or keys spread over many
-// magnitudes) is left to the rest list.
+// the bins of two keys or more (one in eleven at the target size) are listed
+// and sorted, one thread each (counting every key's place within its bin
+// instead looked at each bin as often as it has keys, in lockstep with the
+// fullest of 256: 1.77 against 1.52 ms at 2^28 int64).  VALU instructions (116
+// a key) and the latency of the gather bound it: 76 KB of LDS leave two
+// workgroups a CU.  A leaf with a crowded bin (a key of rank
+// kCrowded or more: many equal keys, or keys spread over many magnitudes) is
+// left to the rest list.
 //
 // Keys of the last level are gathered: the leaf's piece of every tile of the
 // node is found in the table, and a bit mask over the leaf's positions, set
 // where a piece starts, tells every position its piece.
 constexpr uint32_t kCrowded = 24;
+
+// Sorts the n >= 2 keys of a bin in LDS, key-value by key and position: four
+// in registers, any further ones (1 bin in 500 at the target size) by
+// insertion.
+template <typename U, bool KV>
+__device__ __forceinline__ void sort_bin(U *sk, uint16_t *sidx, uint32_t n) {
+  U k[4];
+  uint32_t x[KV ? 4 : 1];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t a = j < (int)n ? j : 0;
+    k[j] = sk[a];
+    k[j] = j < (int)n ? k[j] : key_max<U>();
+    if constexpr (KV) x[j] = j < (int)n ? (uint32_t)sidx[a] : 0xffffu;
+  }
+  auto order = [&](int a, int b) {
+    bool sw = k[b] < k[a];
+    if constexpr (KV) sw = sw || (k[b] == k[a] && x[b] < x[a]);
+    const U ka = opaque(k[a]), kb = opaque(k[b]);
+    k[a] = sw ? kb : ka;
+    k[b] = sw ? ka : kb;
+    if constexpr (KV) {
+      const uint32_t xa = x[a], xb = x[b];
+      x[a] = sw ? xb : xa;
+      x[b] = sw ? xa : xb;
+    }
+  };
+  order(0, 1);
+  order(2, 3);
+  order(0, 2);
+  order(1, 3);
+  order(1, 2);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (j < (int)n) {
+      sk[j] = k[j];
+      if constexpr (KV) sidx[j] = (uint16_t)x[j];
+    }
+  }
+  for (uint32_t t = 4; t < n; ++t) {
+    const U y = sk[t];
+    const uint32_t z = KV ? sidx[t] : 0;
+    uint32_t j = t;
+    for (; j > 0; --j) {
+      const U o = sk[j - 1];
+      if (o < y) break;
+      if constexpr (KV) {
+        const uint32_t oz = sidx[j - 1];
+        if (o == y && oz < z) break;
+        sidx[j] = (uint16_t)oz;
+      } else {
+        if (o == y) break;
+      }
+      sk[j] = o;
+    }
+    sk[j] = y;
+    if constexpr (KV) sidx[j] = (uint16_t)z;
+  }
+}
 
 template <int KT, bool KV, int NT>
 __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
@@ -702,13 +766,14 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
   using U = typename Key<KT>::U;
   constexpr uint32_t CAP = NT * kTileItems, NBIN = CAP, NW = NT / 64;
   static_assert(NBIN / 4 / NT == 4, "one 16-byte word of bin counts a thread");
-  // (the counting loop reads up to kCrowded keys past a bin's start)
-  __shared__ U sk[CAP + 32];
-  __shared__ uint16_t sidx[KV ? CAP + 32 : 1];
+  __shared__ U sk[CAP];
+  __shared__ uint16_t sidx[KV ? CAP : 1];  // position of the key of a slot
   // bin counts, a byte each (a count past 255 runs into its neighbours, but
-  // the leaf is crowded by then), and the keys before every four bins
-  __shared__ __attribute__((aligned(16))) uint32_t bins[NBIN / 4];
-  __shared__ __attribute__((aligned(8))) uint16_t bin4[NBIN / 4];
+  // the leaf is crowded by then), and the keys before every four bins; later
+  // the list of bins to sort
+  constexpr uint32_t kList = NBIN / 4 + NBIN / 8;
+  __shared__ __attribute__((aligned(16))) uint32_t bins[kList];
+  uint16_t *bin4 = reinterpret_cast<uint16_t *>(bins + NBIN / 4);
   __shared__ U smin[NW], smax[NW];
   __shared__ uint32_t wsum[NW];
   // the gather's tables, dead before the keys are placed
@@ -897,63 +962,39 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
     }
     return;
   }
-  // keys before every four bins, 16 bins a thread
+  // keys before every four bins, 16 bins a thread; and the bins of two keys or
+  // more, each listed by its second key
+  uint32_t at, listed;
   {
+    uint32_t seconds = 0;
+#pragma unroll
+    for (int i = 0; i < kTileItems; ++i)
+      if (i * NT < len) seconds += place[i] >> 16 == 1 ? 1u : 0u;
     const uint4 q = reinterpret_cast<const uint4 *>(bins)[tid];
     const uint32_t c0 = __builtin_amdgcn_sad_u8(q.x, 0, 0), c1 = __builtin_amdgcn_sad_u8(q.y, 0, c0);
     const uint32_t c2 = __builtin_amdgcn_sad_u8(q.z, 0, c1), c3 = __builtin_amdgcn_sad_u8(q.w, 0, c2);
     uint32_t total;
-    const uint32_t run = block_scan<NT>(c3, wsum, total);
+    const uint32_t x = block_scan<NT>(c3 | seconds << 16, wsum, total);
+    const uint32_t run = x & 0xffffu;
     reinterpret_cast<uint2 *>(bin4)[tid] = uint2{run | (run + c0) << 16, (run + c1) | (run + c2) << 16};
-    if (tid < 32) sk[len + tid] = key_max<U>();
-    if constexpr (KV)
-      if (tid < 32) sidx[len + tid] = 0xffffu;
+    at = x >> 16;
+    // (bins of one key value hold equal keys, which need no order keys-only)
+    listed = !KV && direct ? 0u : total >> 16;
   }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < kTileItems; ++i) {
-    if (i * NT + tid < len) {
-      const uint32_t bin = place[i] & 0xffffu, w = bins[bin >> 2];
-      const uint32_t s = __builtin_amdgcn_sad_u8(w & ~(~0u << (bin & 3u) * 8), 0, bin4[bin >> 2]);
-      const uint32_t slot = s + (place[i] >> 16);
-      // first slot, rank and count of the bin
-      place[i] = s | (place[i] >> 16) << 14 | ((w >> (bin & 3u) * 8) & 0xffu) << 22;
-      sk[slot] = k[i];
-      if constexpr (KV) sidx[slot] = (uint16_t)(i * NT + tid);
-    }
-  }
-  __syncthreads();
-  // A key's final place: its bin's first slot, plus the keys of the bin below
-  // it (of equal keys: in an earlier slot; key-value: at an earlier position).
-  // Slots past the bin hold larger keys, so the loop needs no end check.
-  // place becomes: slot, and final place << 16
-  constexpr int GRP = 4;
-#pragma unroll
-  for (int g = 0; g < kTileItems; g += GRP) {
-    if (g * NT < len) {
-      uint32_t s[GRP], slot[GRP], fin[GRP];
-      uint32_t most = 0;
-#pragma unroll
-      for (int i = 0; i < GRP; ++i) {
-        const bool ok = (g + i) * NT + tid < len;
-        const uint32_t n = ok ? place[g + i] >> 22 : 0u;
-        s[i] = ok ? place[g + i] & 0x3fffu : 0u;
-        slot[i] = s[i] + ((place[g + i] >> 14) & 0xffu);
-        fin[i] = s[i];
-        most = n > most ? n : most;
+    if (i * NT < len) {
+      const uint32_t bin = place[i] & 0xffffu, rank = place[i] >> 16;
+      place[i] = 0;
+      if (i * NT + tid < len) {
+        const uint32_t w = bins[bin >> 2];
+        const uint32_t s = __builtin_amdgcn_sad_u8(w & ~(~0u << (bin & 3u) * 8), 0, bin4[bin >> 2]);
+        sk[s + rank] = k[i];
+        if constexpr (KV) sidx[s + rank] = (uint16_t)(i * NT + tid);
+        // a listed bin: first slot, and keys << 16
+        if (rank == 1) place[i] = s | ((w >> (bin & 3u) * 8) & 0xffu) << 16;
       }
-      if (__any(most > 1)) {
-        for (uint32_t t = 0; __any(t < most); ++t) {
-#pragma unroll
-          for (int i = 0; i < GRP; ++i) {
-            const U o = sk[s[i] + t];
-            const bool tie = KV ? sidx[s[i] + t] < (g + i) * NT + tid : s[i] + t < slot[i];
-            fin[i] += (tie ? o <= k[g + i] : o < k[g + i]) ? 1u : 0u;
-          }
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < GRP; ++i) place[g + i] = slot[i] | fin[i] << 16;
     }
   }
   if constexpr (KV) {
@@ -963,10 +1004,24 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
     for (int i = 0; i < kTileItems; ++i) asm volatile("" : "+v"(v[i]));
   }
   __syncthreads();
+  // The keys of every listed bin are sorted in place by one thread.  The list
+  // takes the place of the counts; a leaf of many pairs needs it twice.
+  uint32_t *list = bins;
+  for (uint32_t base = 0; base < listed; base += kList) {
+    uint32_t to = at - base;
 #pragma unroll
-  for (int i = 0; i < kTileItems; ++i)
-    if (i * NT + tid < len && (place[i] >> 16) != (place[i] & 0xffffu)) sk[place[i] >> 16] = k[i];
-  __syncthreads();
+    for (int i = 0; i < kTileItems; ++i) {
+      if (i * NT < len && place[i]) {
+        if (to < kList) list[to] = place[i];
+        ++to;
+      }
+    }
+    __syncthreads();
+    const uint32_t m = listed - base < kList ? listed - base : kList;
+    for (uint32_t e = tid; e < m; e += NT)
+      sort_bin<U, KV>(sk + (list[e] & 0xffffu), sidx + (KV ? list[e] & 0xffffu : 0u), list[e] >> 16);
+    __syncthreads();
+  }
 #pragma unroll
   for (int i = 0; i < kTileItems; ++i) {
     const uint32_t idx = i * NT + tid;
@@ -977,12 +1032,12 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kTileItems; ++i)
-      if (i * NT + tid < len) sv[place[i] >> 16] = v[i];
+      if (i * NT + tid < len) sv[i * NT + tid] = v[i];
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kTileItems; ++i) {
       const uint32_t idx = i * NT + tid;
-      if (idx < len) __builtin_nontemporal_store(sv[idx], &vout[off + idx]);
+      if (idx < len) __builtin_nontemporal_store(sv[sidx[idx]], &vout[off + idx]);
     }
   }
 }

@@ -191,3 +191,23 @@ def test_segment_length_bound_too_small():
         for i, (lo, hi) in enumerate(zip(offs[:-1], offs[1:])):
             if not (reported and i == 1):
                 assert np.array_equal(got[lo:hi], np.sort(keys[lo:hi]))
+
+
+@pytest.mark.parametrize("copies", [2, 3, 6, 20])
+@pytest.mark.parametrize("dtype", [np.uint32, np.int64], ids=lambda d: np.dtype(d).name)
+def test_leaf_bins(dtype, copies):
+    """One leaf of keys with several copies each: more bins to sort than the
+    leaf's list holds at once (pairs), bins sorted in registers (3), by
+    insertion (6), and up to the crowded limit (20)."""
+    rng = np.random.default_rng(copies)
+    for kv, n in ((False, 8192), (False, 8191), (True, 4096), (True, 4093)):
+        keys = np.repeat(random_keys(rng, dtype, n // copies + 1), copies)[:n]
+        keys = rng.permutation(keys)
+        vals = rng.permutation(n).astype(np.uint32) if kv else None
+        announce("distribution leaf", np.dtype(dtype).name, copies, n, "kv" if kv else "keys")
+        got, vgot, err, _ = _segmented(keys, [n], vals, max_seg_len=3 * TILE)
+        assert err == 0
+        perm = np.argsort(order_bits(keys), kind="stable")
+        assert got.tobytes() == keys[perm].tobytes()
+        if kv:
+            assert np.array_equal(vgot, vals[perm])

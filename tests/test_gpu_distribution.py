@@ -211,3 +211,14 @@ def test_leaf_bins(dtype, copies):
         assert got.tobytes() == keys[perm].tobytes()
         if kv:
             assert np.array_equal(vgot, vals[perm])
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 8192])
+def test_one_short_tile(n):
+    """One array on both sides of each step of the workgroup that sorts it."""
+    for dtype in (np.uint32, np.int64):
+        for kv in (False, True):
+            announce("one tile", np.dtype(dtype).name, n, "kv" if kv else "keys")
+            keys = random_keys(np.random.default_rng(n), dtype, n)
+            keys[: n // 3] = keys[-1]
+            check(keys, kv)

@@ -682,7 +682,7 @@ __device__ __forceinline__ DistLeaf uniform(const DistLeaf &f) {
   return u;
 }
 
-// One workgroup sorts one leaf of at most CAP = 16 NT keys.  The keys are
+// One workgroup sorts one leaf of at most CAP = NT * NI keys.  The keys are
 // binned by interpolation between the bounds of the leaf (CAP bins, one key in
 // two bins when the leaf has its target size), placed in bin order in LDS, and
 // the bins of two keys or more (one in eleven at the target size) are listed
@@ -758,14 +758,16 @@ __device__ __forceinline__ void sort_bin(U *sk, uint16_t *sidx, uint32_t n) {
   }
 }
 
-template <int KT, bool KV, int NT>
-__global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
+template <int KT, bool KV, int NT, int NI>
+__device__ __forceinline__ void sort_leaf(
     const typename Key<KT>::U *__restrict__ in, const uint32_t *__restrict__ vin,
     const typename Key<KT>::U *__restrict__ ws, const uint32_t *__restrict__ vws,
-    typename Key<KT>::U *out, uint32_t *vout, Level L) {
+    typename Key<KT>::U *out, uint32_t *vout, const Level &L, uint32_t li) {
   using U = typename Key<KT>::U;
-  constexpr uint32_t CAP = NT * kTileItems, NBIN = CAP, NW = NT / 64;
-  static_assert(NBIN / 4 / NT == 4, "one 16-byte word of bin counts a thread");
+  constexpr uint32_t CAP = NT * NI, NBIN = CAP, NW = NT / 64;
+  constexpr int BW = NBIN / 4 / NT;  // words of bin counts a thread scans
+  static_assert(BW == 4 || BW == 2, "one vector of bin counts a thread");
+  using Counts = std::conditional_t<BW == 4, uint4, uint2>;
   __shared__ U sk[CAP];
   __shared__ uint16_t sidx[KV ? CAP : 1];  // position of the key of a slot
   // bin counts, a byte each (a count past 255 runs into its neighbours, but
@@ -783,11 +785,8 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
   static_assert(dist_node_tiles(sizeof(U), KV) * 4 <= sizeof(sk), "pieces fit the key area");
   static_assert(CAP / 8 + CAP / 32 <= sizeof(bins), "mask and rows fit the bins");
   const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const uint32_t nl = L.ctr->leaves < L.max_leaves ? L.ctr->leaves : L.max_leaves;
   const uint16_t *table = (const uint16_t *)L.table;
-
-  if (blockIdx.x >= nl) return;
-  const DistLeaf leaf = uniform(L.leaves[blockIdx.x]);
+  const DistLeaf leaf = uniform(L.leaves[li]);
   // The leaf's piece of tile t: its first position in the tile and its end.
   auto piece_of = [&](uint32_t t, uint32_t &s, uint32_t &e) {
     s = e = 0;
@@ -803,9 +802,9 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
   const bool inner = from == kSrcPieces && (leaf.len_flags & kLeafInner);
   const U *p = from == kSrcOut ? (const U *)out : from == kSrcIn ? in : ws;
   const uint32_t *vp = from == kSrcOut ? (const uint32_t *)vout : from == kSrcIn ? vin : vws;
-  U k[kTileItems];
-  uint32_t v[KV ? kTileItems : 1];
-  uint32_t addr[kTileItems];
+  U k[NI];
+  uint32_t v[KV ? NI : 1];
+  uint32_t addr[NI];
   if (from == kSrcPieces) {
     if (!KV && (leaf.len_flags & kLeafEqual)) {
       // one key value, known from the splitters: nothing to read
@@ -846,7 +845,7 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
       __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < kTileItems; ++i) {
+    for (int i = 0; i < NI; ++i) {
       if (i * NT < len) {  // (positions past the end: the last key)
         const uint32_t j = i * NT + tid < len ? i * NT + tid : len - 1;
         const uint32_t r = j >> 6;
@@ -858,12 +857,12 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
     __syncthreads();
   } else {
 #pragma unroll
-    for (int i = 0; i < kTileItems; ++i) addr[i] = off + (i * NT + tid < len ? i * NT + tid : len - 1);
+    for (int i = 0; i < NI; ++i) addr[i] = off + (i * NT + tid < len ? i * NT + tid : len - 1);
   }
   // the loads are all issued before any is used: clamped, not conditional;
   // steps of NT keys past the end are skipped throughout
 #pragma unroll
-  for (int i = 0; i < kTileItems; ++i) {
+  for (int i = 0; i < NI; ++i) {
     if (i * NT < len) {
       k[i] = __builtin_nontemporal_load(&p[addr[i]]);
       if constexpr (KV) v[i] = __builtin_nontemporal_load(&vp[addr[i]]);
@@ -871,13 +870,13 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
   }
   if (from == kSrcIn) {
 #pragma unroll
-    for (int i = 0; i < kTileItems; ++i)
+    for (int i = 0; i < NI; ++i)
       if (i * NT < len) k[i] = Key<KT>::map(k[i]);
   }
   if (leaf.len_flags & (kLeafEqual | kLeafMove)) {
     const bool equal = leaf.len_flags & kLeafEqual;
 #pragma unroll
-    for (int i = 0; i < kTileItems; ++i) {
+    for (int i = 0; i < NI; ++i) {
       const uint32_t idx = i * NT + tid;
       if (idx < len) {
         out[off + idx] = equal ? Key<KT>::unmap(k[i]) : k[i];
@@ -886,7 +885,7 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
     }
     return;
   }
-  reinterpret_cast<uint4 *>(bins)[tid] = uint4{0, 0, 0, 0};
+  reinterpret_cast<Counts *>(bins)[tid] = Counts{};
   // Bounds of the keys: the splitters around the bucket, or (a node's first
   // and last bucket, and leaves of earlier levels) the smallest and largest
   // key.
@@ -898,7 +897,7 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
   } else {
     mn = mx = k[0];  // (clamped loads repeat the last key)
 #pragma unroll
-    for (int i = 1; i < kTileItems; ++i) {
+    for (int i = 1; i < NI; ++i) {
       if (i * NT < len) {
         mn = k[i] < mn ? k[i] : mn;
         mx = k[i] > mx ? k[i] : mx;
@@ -931,10 +930,10 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
   const bool direct = top < NBIN;
   const uint32_t scale =
       direct ? 0u : (uint32_t)((float)NBIN * 4294967296.0f * (1.0f - 0x1p-20f) / ((float)top + 1.0f));
-  uint32_t place[kTileItems];  // bin, and rank in it << 16
+  uint32_t place[NI];  // bin, and rank in it << 16
   uint32_t worst = 0;
 #pragma unroll
-  for (int i = 0; i < kTileItems; ++i) {
+  for (int i = 0; i < NI; ++i) {
     if (i * NT < len) {
       const uint32_t x = (uint32_t)((uint64_t)(k[i] - mn) >> sh);
       const uint32_t bin = direct ? x : __umulhi(x, scale);
@@ -949,7 +948,7 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
   }
   if (__syncthreads_or(worst >= kCrowded)) {
 #pragma unroll
-    for (int i = 0; i < kTileItems; ++i) {
+    for (int i = 0; i < NI; ++i) {
       const uint32_t idx = i * NT + tid;
       if (idx < len) {
         out[off + idx] = k[i];
@@ -968,22 +967,29 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
   {
     uint32_t seconds = 0;
 #pragma unroll
-    for (int i = 0; i < kTileItems; ++i)
+    for (int i = 0; i < NI; ++i)
       if (i * NT < len) seconds += place[i] >> 16 == 1 ? 1u : 0u;
-    const uint4 q = reinterpret_cast<const uint4 *>(bins)[tid];
-    const uint32_t c0 = __builtin_amdgcn_sad_u8(q.x, 0, 0), c1 = __builtin_amdgcn_sad_u8(q.y, 0, c0);
-    const uint32_t c2 = __builtin_amdgcn_sad_u8(q.z, 0, c1), c3 = __builtin_amdgcn_sad_u8(q.w, 0, c2);
+    const Counts q = reinterpret_cast<const Counts *>(bins)[tid];
+    uint32_t c[BW + 1] = {};  // keys in the words before
+    c[1] = __builtin_amdgcn_sad_u8(q.x, 0, 0);
+    c[2] = __builtin_amdgcn_sad_u8(q.y, 0, c[1]);
+    if constexpr (BW == 4) {
+      c[3] = __builtin_amdgcn_sad_u8(q.z, 0, c[2]);
+      c[4] = __builtin_amdgcn_sad_u8(q.w, 0, c[3]);
+    }
     uint32_t total;
-    const uint32_t x = block_scan<NT>(c3 | seconds << 16, wsum, total);
+    const uint32_t x = block_scan<NT>(c[BW] | seconds << 16, wsum, total);
     const uint32_t run = x & 0xffffu;
-    reinterpret_cast<uint2 *>(bin4)[tid] = uint2{run | (run + c0) << 16, (run + c1) | (run + c2) << 16};
+#pragma unroll
+    for (int j = 0; j < BW; j += 2)
+      reinterpret_cast<uint32_t *>(bin4)[(tid * BW + j) / 2] = (run + c[j]) | (run + c[j + 1]) << 16;
     at = x >> 16;
     // (bins of one key value hold equal keys, which need no order keys-only)
     listed = !KV && direct ? 0u : total >> 16;
   }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < kTileItems; ++i) {
+  for (int i = 0; i < NI; ++i) {
     if (i * NT < len) {
       const uint32_t bin = place[i] & 0xffffu, rank = place[i] >> 16;
       place[i] = 0;
@@ -1001,7 +1007,7 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
     // the leaf may lie in the output: every load has returned before any
     // thread stores
 #pragma unroll
-    for (int i = 0; i < kTileItems; ++i) asm volatile("" : "+v"(v[i]));
+    for (int i = 0; i < NI; ++i) asm volatile("" : "+v"(v[i]));
   }
   __syncthreads();
   // The keys of every listed bin are sorted in place by one thread.  The list
@@ -1010,7 +1016,7 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
   for (uint32_t base = 0; base < listed; base += kList) {
     uint32_t to = at - base;
 #pragma unroll
-    for (int i = 0; i < kTileItems; ++i) {
+    for (int i = 0; i < NI; ++i) {
       if (i * NT < len && place[i]) {
         if (to < kList) list[to] = place[i];
         ++to;
@@ -1023,7 +1029,7 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
     __syncthreads();
   }
 #pragma unroll
-  for (int i = 0; i < kTileItems; ++i) {
+  for (int i = 0; i < NI; ++i) {
     const uint32_t idx = i * NT + tid;
     if (idx < len) __builtin_nontemporal_store(Key<KT>::unmap(sk[idx]), &out[off + idx]);
   }
@@ -1031,14 +1037,29 @@ __global__ __launch_bounds__(NT, 4) void dist_leaf_kernel(
     uint32_t *sv = reinterpret_cast<uint32_t *>(sk);
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kTileItems; ++i)
+    for (int i = 0; i < NI; ++i)
       if (i * NT + tid < len) sv[i * NT + tid] = v[i];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kTileItems; ++i) {
+    for (int i = 0; i < NI; ++i) {
       const uint32_t idx = i * NT + tid;
       if (idx < len) __builtin_nontemporal_store(sv[sidx[idx]], &vout[off + idx]);
     }
+  }
+}
+
+// The grid is the count of leaves to expect: the bound on them is more than
+// twice that, and empty workgroups cost (4096 int64 arrays: 2546 us with, 2445
+// without).  Frequent keys and short segments may leave more.
+template <int KT, bool KV, int NT, int NI, int WAVES>
+__global__ __launch_bounds__(NT, WAVES) void dist_leaf_kernel(
+    const typename Key<KT>::U *__restrict__ in, const uint32_t *__restrict__ vin,
+    const typename Key<KT>::U *__restrict__ ws, const uint32_t *__restrict__ vws,
+    typename Key<KT>::U *out, uint32_t *vout, Level L) {
+  const uint32_t nl = L.ctr->leaves < L.max_leaves ? L.ctr->leaves : L.max_leaves;
+  for (uint32_t li = blockIdx.x; li < nl; li += gridDim.x) {
+    if (li != blockIdx.x) __syncthreads();  // the last leaf's LDS is read no more
+    sort_leaf<KT, KV, NT, NI>(in, vin, ws, vws, out, vout, L, li);
   }
 }
 
@@ -1302,15 +1323,19 @@ hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, const DistB
 hipError_t launch_dist_leaves(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
                               hipStream_t s) {
   const Level L = level_args(kt, d, d.levels, w);
-  const dim3 grid(d.max_leaves);
+  const dim3 grid(d.leaf_grid);
   return with_type(kt, [&](auto c) {
     constexpr int KT = decltype(c)::value;
     using U = typename Key<KT>::U;
     if (kv)
-      hipLaunchKernelGGL((dist_leaf_kernel<KT, true, 256>), grid, dim3(256), 0, s, (const U *)b.in,
+      // (8 keys a thread: LDS holds three workgroups a CU, which with 256
+      // threads of 16 keys left it 12 waves; 1069 against 1001 us at 2^27 u64.
+      // Keys-only leaves fill two workgroups' LDS, and 1024 threads of 8 keys
+      // measured slower there, 1632 against 1487 us at 2^28 int64.)
+      hipLaunchKernelGGL((dist_leaf_kernel<KT, true, 512, 8, 6>), grid, dim3(512), 0, s, (const U *)b.in,
                          b.vin, (const U *)b.ws, b.vws, (U *)b.out, b.vout, L);
     else
-      hipLaunchKernelGGL((dist_leaf_kernel<KT, false, 512>), grid, dim3(512), 0, s, (const U *)b.in,
+      hipLaunchKernelGGL((dist_leaf_kernel<KT, false, 512, 16, 4>), grid, dim3(512), 0, s, (const U *)b.in,
                          b.vin, (const U *)b.ws, b.vws, (U *)b.out, b.vout, L);
     return hipGetLastError();
   });

@@ -18,7 +18,7 @@ constexpr uint32_t kDistTile = kDistThreads * kDistItems;
 constexpr uint32_t kDistMaxPicks = 384;
 constexpr uint32_t kDistSlots = 512;
 constexpr int kDistMaxLevels = 3;
-// Keys one workgroup sorts in LDS (16 a thread), and the mean bucket the
+// Keys one workgroup sorts in LDS, and the mean bucket the
 // splitters aim at: half of it, so that a bucket cut by 20 or more samples
 // overflows about once in 10^5.
 constexpr uint32_t kDistCap = 8192, kDistCapKV = 4096;
@@ -26,7 +26,7 @@ constexpr uint32_t kDistTarget = 4096, kDistTargetKV = 2048;
 // Most tiles of one range.
 constexpr uint32_t kDistRangeTiles = 11;
 // Most tiles of a node of the last level: a leaf lists one piece a tile in the
-// LDS its keys take later (16 a thread).  Sampled nodes stay far below.
+// LDS its keys take later.  Sampled nodes stay far below.
 inline constexpr uint32_t dist_node_tiles(int kb, bool kv) {
   return (kv ? kDistCapKV : kDistCap) * (uint32_t)kb / 4;
 }
@@ -82,6 +82,7 @@ struct DistPlan {
   uint32_t rl[kDistMaxLevels + 1] = {};  // keys of a range (whole tiles)
   uint32_t max_nodes[kDistMaxLevels + 1] = {}, max_ranges[kDistMaxLevels + 1] = {};
   uint32_t max_cols = 0, max_table[kDistMaxLevels + 1] = {}, max_leaves = 0, max_rest = 0;
+  uint32_t leaf_grid = 0;  // workgroups of the leaf kernel: the leaves to expect
   size_t off_ctr = 0, off_nodes[kDistMaxLevels + 1] = {}, off_ranges[kDistMaxLevels + 1] = {};
   size_t off_spl = 0, off_start = 0, off_table = 0, off_leaves = 0, off_rest = 0, off_small = 0;
   size_t end = 0;  // first byte after the distribution's arrays
@@ -143,6 +144,8 @@ inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb,
   }
   d.max_cols = (uint32_t)max_cols;
   d.max_leaves = (uint32_t)(leaves + n / d.cap + 1);
+  const uint64_t expect = n / d.target + n / d.target / 8 + d.max_nodes[d.levels] + n_segs + 64;
+  d.leaf_grid = (uint32_t)std::min<uint64_t>(d.max_leaves, expect);
   d.max_rest = d.max_leaves;  // every leaf, or buckets above cap (fewer)
   auto take = [&](size_t bytes) {
     const size_t o = off;

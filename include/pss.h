@@ -116,7 +116,9 @@ pss_status pss_workspace_bytes(const pss_ctx *ctx, pss_key_t key, pss_val_t val,
  * the number of full read+write sweeps over the keys.  Keys-only sorts use
  * tiles and merge partitions of 8192 keys and passes of at most 32 runs;
  * key-value sorts tiles and partitions of 4096 keys and passes of at most 64
- * runs (they hold 12 bytes a key in LDS).  Host-only. */
+ * runs (they hold 12 bytes a key in LDS).  Inputs cut into buckets by sampled
+ * splitters (see pss_sort) are described by the merge plan whose workspace they
+ * use.  Host-only. */
 pss_status pss_plan_describe(pss_key_t key, pss_val_t val, uint64_t n, uint32_t n_blocks,
                              uint32_t n_parts, char *buf, size_t buf_len);
 
@@ -430,7 +432,9 @@ pss_status pss_set_merge_method(pss_ctx *ctx, pss_merge_method method);
  * partition_sample_merge when its search starts from the blocks' samples),
  * psrs_samples, psrs_sample_sort,
  * psrs_partition and psrs_chunks (regular-sampling pivots), record_keys and
- * record_gather (record sorts).
+ * record_gather (record sorts), dist_sample, dist_count, dist_scan,
+ * dist_scatter, dist_partition, dist_pieces, dist_leaves and dist_rest (the
+ * automatic plan's sampled buckets).
  */
 pss_status pss_profile_enable(pss_ctx *ctx, int on);
 pss_status pss_profile_read(pss_ctx *ctx, char *buf, size_t buf_len);

@@ -123,6 +123,16 @@ struct Plan {
   pss::DistPlan dist;
 };
 
+// The distribution plan whose arrays fit between `off` and `total`, gathered
+// if they do.
+pss::DistPlan plan_dist(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb, bool kv, size_t off,
+                        size_t total) {
+  pss::DistPlan d = pss::dist_plan(n, max_len, n_segs, kb, kv, off, true);
+  if (d.end > total) d = pss::dist_plan(n, max_len, n_segs, kb, kv, off, false);
+  d.on = d.end <= total;
+  return d;
+}
+
 pss_status make_plan(pss_key_t key, pss_val_t val, uint64_t n, uint32_t n_blocks,
                      uint32_t n_parts, Plan *p, std::string *err) {
   p->kv = val == PSS_VAL_U32;
@@ -219,8 +229,7 @@ pss_status make_plan(pss_key_t key, pss_val_t val, uint64_t n, uint32_t n_blocks
   }
   p->total = off;
   if (!p->paper && n >= kDistMinKeys && pss::launch_dist_sample) {
-    p->dist = pss::dist_plan(n, n, 0, p->kb, p->kv, p->off_table);
-    p->dist.on = p->dist.end <= p->total;
+    p->dist = plan_dist(n, n, 0, p->kb, p->kv, p->off_table, p->total);
   }
   return PSS_OK;
 }
@@ -438,7 +447,7 @@ pss_status run_dist_levels(pss_ctx *ctx, const pss::DistPlan &d, int kt, bool kv
       LaunchTimer t(ctx, "dist_sample", 0, s);
       PSS_LAUNCH(pss::launch_dist_sample(kt, d, l, b, n, w, s), "sample launch");
     }
-    if (l < d.levels) {
+    if (!d.tiled(l)) {
       {
         LaunchTimer t(ctx, "dist_count", kbytes, s);
         PSS_LAUNCH(pss::launch_dist_count(kt, d, l, b, w, s), "count launch");
@@ -452,7 +461,11 @@ pss_status run_dist_levels(pss_ctx *ctx, const pss::DistPlan &d, int kt, bool kv
     } else {
       {
         LaunchTimer t(ctx, "dist_partition", sweep, s);
-        PSS_LAUNCH(pss::launch_dist_partition(kt, kv, d, b, w, s), "partition launch");
+        PSS_LAUNCH(pss::launch_dist_partition(kt, kv, d, l, b, w, s), "partition launch");
+      }
+      if (l < d.levels) {
+        LaunchTimer t(ctx, "dist_pieces", 0, s);
+        PSS_LAUNCH(pss::launch_dist_pieces(kt, d, l, w, s), "piece count launch");
       }
       LaunchTimer t(ctx, "dist_scan", 0, s);
       PSS_LAUNCH(pss::launch_dist_scan(kt, d, l, w, s), "scan launch");
@@ -1093,8 +1106,7 @@ pss_status make_seg_plan(const pss_ctx *ctx, pss_key_t key, pss_val_t val, uint6
   sp->total = off;
   sp->longest = std::min<uint64_t>((uint64_t)sp->tile << (f * sp->max_passes), n);
   if (sp->max_passes && pss::launch_dist_segments) {
-    sp->dist = pss::dist_plan(n, max_len, n_segs, kb, kv, sp->off_plan);
-    sp->dist.on = sp->dist.end <= sp->total;
+    sp->dist = plan_dist(n, max_len, n_segs, kb, kv, sp->off_plan, sp->total);
   }
   return PSS_OK;
 }

@@ -549,10 +549,10 @@ __device__ __forceinline__ uint32_t node_cols(uint32_t p) {
   return 2 * p < kDistSlots ? 2 * p : kDistSlots;
 }
 
-// Table entries per bucket: one a range, or (last level) one a tile, padded so
+// Table entries per bucket: one a range, or (tiles in place) one a tile, padded so
 // that every bucket's entries start on 16 bytes.
-__device__ __forceinline__ uint32_t node_stride(uint32_t len, uint32_t nr, bool last) {
-  return last ? ((len + kDistTile - 1) / kDistTile + 7) / 8 * 8 : nr;
+__device__ __forceinline__ uint32_t node_stride(uint32_t len, uint32_t nr, bool tiled) {
+  return tiled ? ((len + kDistTile - 1) / kDistTile + 7) / 8 * 8 : nr;
 }
 
 }  // namespace

@@ -8,27 +8,36 @@
 //              LDS; every (S/p)-th is a splitter.  A key seen twice at a
 //              splitter also gives the next larger key, so that a frequent key
 //              has a bucket of its own, which needs no further work.
-//   count      (before the last level) keys per bucket of every range
+//   partition  every tile is ordered by bucket in LDS and written back as one
+//              piece, with a table of where each bucket starts in it: nothing
+//              has to be counted first, and no partial cache lines are written.
+//              A further level gathers its keys from the pieces the one before
+//              left, for which "pieces" counts the keys before every 8 tiles
 //   scan       where the buckets start; they become leaves (fit one workgroup,
 //              or hold one key value only), nodes of the next level, or - if the
 //              last level left one too large - entries of the rest list
-//   scatter    (before the last level) the same ranges, tile by tile: a tile is
-//              ordered by bucket in LDS and leaves in runs of consecutive
-//              addresses, each bucket's at its own place
-//   partition  (last level, in place of count and scatter) every tile is ordered
-//              by bucket in LDS and written back as one piece, with a table of
-//              where each bucket starts in it; no counts are needed first, and
-//              no partial cache lines are written
 //
 // and a leaf is sorted by one workgroup, which gathers it from its piece of
-// every tile of the node.  Samples are taken at hashed positions, so the order
-// of the input does not matter, and any distribution of keys gives buckets of
-// about the same size.  Nothing depends on the sizes being met: a bucket left
-// too large is sorted by merging through memory.
+// every tile of the node.  The last two levels leave their tiles in place;
+// before them, and for arrays too short to gather (kDistGatherMin), a level is
 //
-// At 2^28 int64 uniform keys (ms): samples 0.22, count 0.43, scatter 1.48,
-// partition 0.90, leaves 1.52; the sort 4.54, against 7.31 for the merge plan's
-// tile sort (1.71) and three merge passes (1.88 each with their searches).
+//   count      keys per bucket of every range
+//   scatter    the same ranges, tile by tile: a tile is ordered by bucket in LDS
+//              and leaves in runs of consecutive addresses, each bucket's at its
+//              own place
+//
+// Samples are taken at hashed positions, so the order of the input does not
+// matter, and any distribution of keys gives buckets of about the same size.
+// Nothing depends on the sizes being met: a bucket left too large is sorted by
+// merging through memory.
+//
+// At 2^28 int64 uniform keys (ms): samples 0.21, first partition 0.86, gathered
+// partition 1.24, leaves 1.50; the sort 3.85.  With a count (0.44) and a
+// scatter (1.48) in place of the first partition, and 0.89 for a partition that
+// need not gather, it took 4.50, and the merge plan's tile sort (1.71) and three
+// merge passes (1.88 each with their searches) 7.31.  A piece is 24 keys of 8
+// bytes there, at any multiple of 8, so that a gather reads 1.7 times its bytes
+// in cache lines; a scatter writes as many partial lines, to 256 places at once.
 //
 // Key-value sorts place equal keys in input order at every step (the ranges
 // are in order, and a tile's ranks follow it), keys-only sorts need not:
@@ -40,6 +49,8 @@ namespace pss {
 namespace {
 
 constexpr uint32_t kLutBins = 1024;
+constexpr uint32_t kXcds = 8;
+constexpr uint32_t kGang = 4;  // neighbouring nodes gathered on one XCD
 
 // Arguments of one level's kernels.
 struct Level {
@@ -56,6 +67,11 @@ struct Level {
   uint32_t node_tiles;  // most tiles of a last-level node
   uint32_t max_next_nodes, max_next_ranges, max_cols, max_next_table, max_leaves, max_rest;
   uint32_t root_len, root_p;  // level 1 of a single array (0: nodes are given)
+  uint32_t tiled, next_tiled;  // its tiles are left in place
+  uint32_t gather;  // its keys are gathered from the tiles of the level before
+  uint32_t kv, max_copies, max_ranges, max_nodes;
+  const uint16_t *ptable;  // gathered: the table of the level before,
+  uint32_t *pre;           // and per bucket the keys before every 8 tiles
 };
 
 // Inclusive sum over the wave's lanes, in DPP moves: shifts by 1, 2, 4 and 8
@@ -91,6 +107,126 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *wsum, uint3
   return before + x - v;
 }
 
+// ------------------------------------------------------------ gathering ---
+// A gathered node's keys lie in its parent's tiles: eight tiles' pieces of
+// them, as starts (s) and ends (e) in the tiles.
+__device__ __forceinline__ uint32_t parent_tiles(const DistNode &nd) {
+  return (nd.plen + kDistTile - 1) / kDistTile;
+}
+
+// The bucket's piece of tile t (row, next: the table's rows of the bucket and
+// the next one) of a node of len keys.
+__device__ __forceinline__ void piece_of(const uint16_t *table, uint32_t row, uint32_t next,
+                                         uint32_t len, uint32_t t, uint32_t &s, uint32_t &e) {
+  s = e = 0;
+  if (t * kDistTile < len) {
+    const uint32_t rem = len - t * kDistTile, whole = rem < kDistTile ? rem : kDistTile;
+    s = table[row + t];
+    e = next != ~0u ? table[next + t] : whole;
+  }
+}
+
+// The pieces of tiles t .. t+7 (t a multiple of 8); empty past the last tile.
+__device__ __forceinline__ void pieces_of_8(const uint16_t *table, uint32_t row, uint32_t next,
+                                            uint32_t len, uint32_t t, uint32_t (&s)[8],
+                                            uint32_t (&e)[8]) {
+  const uint4 a = *reinterpret_cast<const uint4 *>(table + row + t);
+  const uint4 z = *reinterpret_cast<const uint4 *>(table + (next != ~0u ? next : row) + t);
+  const uint32_t x[4] = {a.x, a.y, a.z, a.w}, y[4] = {z.x, z.y, z.z, z.w};
+#pragma unroll
+  for (uint32_t q = 0; q < 8; ++q) {
+    const uint32_t at = (t + q) * kDistTile, rem = len > at ? len - at : 0u;
+    const uint32_t whole = rem < kDistTile ? rem : kDistTile;
+    s[q] = (x[q >> 1] >> (16 * (q & 1))) & 0xffffu;
+    e[q] = next != ~0u ? (y[q >> 1] >> (16 * (q & 1))) & 0xffffu : whole;
+    s[q] = rem ? s[q] : 0u;
+    e[q] = rem ? e[q] : 0u;
+  }
+}
+
+// Turns positions of a gathered node into addresses in the level's source; pre:
+// the keys before each group of 8 tiles.
+template <int N>
+__device__ __forceinline__ void gathered_from(const Level &L, const DistNode &nd, uint32_t (&at)[N],
+                                              const uint32_t *pre, uint32_t groups) {
+  uint32_t g[N];  // the last group of 8 tiles whose keys start at or before the position
+#pragma unroll
+  for (int i = 0; i < N; ++i) g[i] = 0;
+  for (uint32_t step = 1u << (31 - __clz(groups)); step; step >>= 1) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const uint32_t to = g[i] + step < groups ? g[i] + step : g[i];
+      g[i] = pre[to] <= at[i] ? to : g[i];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    uint32_t s[8], e[8], rem = at[i] - pre[g[i]], where = 0;
+    pieces_of_8(L.ptable, nd.prow, nd.pnext, nd.plen, g[i] * 8, s, e);
+    bool found = false;
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q) {
+      const uint32_t c = e[q] - s[q];
+      const bool here = !found && rem < c;
+      where = here ? nd.poff + (g[i] * 8 + q) * kDistTile + s[q] + rem : where;
+      found |= here;
+      rem -= found ? 0u : c;
+    }
+    at[i] = where;
+  }
+}
+
+// The same.  A thread's positions rise with the thread, so that a wave's lookups
+// share cache lines; `lds` (`room` entries) takes the groups' starts if they
+// fit, as every step of the search waits for the one before it.
+template <int N>
+__device__ __forceinline__ void gathered_at(const Level &L, const DistNode &nd, uint32_t (&at)[N],
+                                            uint32_t *lds, uint32_t room) {
+  const uint32_t groups = (parent_tiles(nd) + 7) / 8;
+  const uint32_t *pre = L.pre + nd.prow / 8;
+  if (groups <= room) {
+    for (uint32_t i = threadIdx.x; i < groups; i += blockDim.x) lds[i] = pre[i];
+    __syncthreads();
+    gathered_from(L, nd, at, lds, groups);
+    __syncthreads();
+  } else {
+    gathered_from(L, nd, at, pre, groups);
+  }
+}
+
+// After a partition that is not the last level's: a bucket's keys before every
+// eight tiles, and in all.  One workgroup a bucket (few nodes), or several
+// buckets each.
+constexpr int kPiecesThreads = 512;
+
+__global__ __launch_bounds__(kPiecesThreads) void dist_pieces_kernel(Level L) {
+  __shared__ uint32_t wsum[kPiecesThreads / 64];
+  const uint32_t tid = threadIdx.x;
+  if (blockIdx.x >= L.ctr->nodes[L.level]) return;
+  const DistNode nd = L.nodes[blockIdx.x];
+  const uint32_t tiles = (nd.len + kDistTile - 1) / kDistTile;
+  for (uint32_t b = blockIdx.y; b < nd.nb; b += gridDim.y) {
+    const uint32_t row = nd.tbase + b * nd.stride;
+    uint32_t run = 0;
+    for (uint32_t t0 = 0; t0 < tiles; t0 += kPiecesThreads * 8) {
+      const uint32_t t = t0 + tid * 8;
+      uint32_t c = 0;
+      if (t < tiles) {
+        uint32_t s[8], e[8];
+        pieces_of_8(L.ptable, row, b + 1 < nd.nb ? row + nd.stride : ~0u, nd.len, t, s, e);
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q) c += e[q] - s[q];
+      }
+      uint32_t total;
+      const uint32_t x = block_scan<kPiecesThreads>(c, wsum, total);
+      if (t < tiles) L.pre[(row + t) / 8] = run + x;
+      run += total;
+      __syncthreads();
+    }
+    if (tid == 0) L.start[nd.sbase + b] = run;
+  }
+}
+
 // ------------------------------------------------------------- sampling ---
 // One workgroup per node; latency-bound (a few random loads a thread, then
 // one LDS sort).  The picks come from S sorted samples, S a power of two of at
@@ -112,7 +248,8 @@ __global__ __launch_bounds__(NT) void dist_sample_kernel(const typename Key<KT>:
     nd.cols = node_cols(nd.p);
     nd.sbase = 0;
     nd.tbase = 0;
-    nd.stride = node_stride(nd.len, nd.nr, L.levels == 1);
+    nd.stride = node_stride(nd.len, nd.nr, L.tiled != 0);
+    nd.poff = nd.plen = nd.prow = nd.pnext = 0;
     uint32_t *c = (uint32_t *)L.ctr;
     for (uint32_t i = tid; i < sizeof(DistCounters) / 4; i += NT) c[i] = 0;
     for (uint32_t r = tid; r < nd.nr; r += NT) L.ranges[r] = DistRange{0u, r};
@@ -130,6 +267,7 @@ __global__ __launch_bounds__(NT) void dist_sample_kernel(const typename Key<KT>:
   want = nd.len / 2 < want ? nd.len / 2 : want;
   const uint32_t lg = 31 - __clz(want), S = 1u << lg;
   U rk[kTileItems];
+  uint32_t at[kTileItems];
 #pragma unroll
   for (int i = 0; i < kTileItems; ++i) {
     const uint32_t j = i * NT + tid;
@@ -141,7 +279,13 @@ __global__ __launch_bounds__(NT) void dist_sample_kernel(const typename Key<KT>:
     h ^= h >> 15;
     // a hashed position of the j-th of S equal strata
     const uint64_t pos = ((uint64_t)j * nd.len + (((uint64_t)h * nd.len) >> 32)) >> lg;
-    rk[i] = j < S ? Key<KT>::map(src[nd.off + pos]) : key_max<U>();
+    at[i] = j < S ? (uint32_t)pos : 0u;
+  }
+  if (L.gather) gathered_at(L, nd, at, reinterpret_cast<uint32_t *>(sk), (uint32_t)(sizeof(sk) / 4));
+#pragma unroll
+  for (int i = 0; i < kTileItems; ++i) {
+    const U x = src[L.gather ? at[i] : nd.off + at[i]];
+    rk[i] = i * NT + tid < S ? Key<KT>::map(x) : key_max<U>();
   }
   lds_sort_keys<U, NT>(rk, sk);
   // splitters of p picks; when frequent keys double them beyond the slots,
@@ -166,10 +310,10 @@ __global__ __launch_bounds__(NT) void dist_sample_kernel(const typename Key<KT>:
       e = (first ? 1u : 0u) + (next ? 1u : 0u);
     }
     uint32_t total;
-    const uint32_t at = block_scan<NT>(e, wsum, total);
+    const uint32_t to = block_scan<NT>(e, wsum, total);
     if (total < nd.cols || p <= 2) {
-      if (first) spl[at] = v;
-      if (next) spl[at + (first ? 1u : 0u)] = v + 1;
+      if (first) spl[to] = v;
+      if (next) spl[to + (first ? 1u : 0u)] = v + 1;
       ns = total;
       break;
     }
@@ -370,7 +514,7 @@ __global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summ
   const uint32_t ns = nd.nb - 1;
   const bool next_last = L.level + 1 == L.levels;
   bool equal = false;  // the bucket can hold one key value only
-  bool node = false, rest = false;
+  bool node = false, rest = false, copy = false, known = false;
   uint32_t pieces = 0;
   U lo = 0, hi = 0;
   if (b < nd.nb && len) {
@@ -381,8 +525,12 @@ __global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summ
     const bool fits = len <= L.cap;
     node = !last && !equal && !fits && !(next_last && len > L.node_tiles * kDistTile);
     rest = !equal && !fits && !node;
-    // (before the last level a rest entry already lies in the output)
-    pieces = node || (rest && !last) ? 0u : (len + L.cap - 1) / L.cap;
+    // (after a scatter a rest entry already lies in the output)
+    pieces = node || (rest && !L.tiled) ? 0u : (len + L.cap - 1) / L.cap;
+    // in place before the last level: the last level's workgroups bring it to
+    // its place in the workspace (keys of one value need not be read)
+    known = equal && !L.kv;
+    copy = L.tiled && !last && !node && !known;
   }
   uint32_t npieces;
   const uint32_t at = block_scan<kDistSlots>(pieces, wsum2, npieces);
@@ -394,7 +542,7 @@ __global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summ
     if (to < L.max_leaves) {
       const uint32_t row = nd.tbase + b * nd.stride;
       L.leaves[to] = DistLeaf{off + o,
-                              l | L.src << kLeafSrcShift | (equal ? kLeafEqual : 0u) |
+                              l | (copy ? kSrcWs : L.tiled ? kSrcPieces : L.src) << kLeafSrcShift | (equal ? kLeafEqual : 0u) |
                                   (rest ? kLeafMove : 0u) | (b > 0 && b < ns ? kLeafInner : 0u),
                               nd.off, nd.len, o, row, b < ns ? row + nd.stride : ~0u, 0u, (uint64_t)lo,
                               (uint64_t)hi};
@@ -411,18 +559,43 @@ __global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summ
     c.p = node_picks(len, L.target, (int)(L.levels - L.level));
     c.nr = (len + L.next_rl - 1) / L.next_rl;
     c.cols = node_cols(c.p);
-    c.stride = node_stride(len, c.nr, next_last);
+    c.stride = node_stride(len, c.nr, L.next_tiled != 0);
     c.nb = 0;
+    c.poff = nd.off;
+    c.plen = nd.len;
+    c.prow = nd.tbase + b * nd.stride;
+    c.pnext = b < ns ? c.prow + nd.stride : ~0u;
     const uint32_t lv = L.level + 1;
     const uint32_t at_node = atomicAdd(&L.ctr->nodes[lv], 1u);
-    const uint32_t at_range = atomicAdd(&L.ctr->ranges[lv], c.nr);
+    // (a gathered level takes its nodes' ranges in turn, without a list)
+    const bool list = !L.tiled;
+    const uint32_t at_range = list ? atomicAdd(&L.ctr->ranges[lv], c.nr) : 0u;
+    if (!list) atomicMax(&L.ctr->most_ranges, c.nr);
     c.sbase = atomicAdd(&L.ctr->cols[lv], c.cols);
     c.tbase = atomicAdd(&L.ctr->table[lv], c.cols * c.stride);
     // (the plan's bounds hold for any lengths; this keeps writes inside them)
-    if (at_node < L.max_next_nodes && at_range + c.nr <= L.max_next_ranges &&
+    if (at_node < L.max_next_nodes && (!list || at_range + c.nr <= L.max_next_ranges) &&
         c.sbase + c.cols <= L.max_cols && c.tbase + c.cols * c.stride <= L.max_next_table) {
       L.next_nodes[at_node] = c;
-      for (uint32_t r = 0; r < c.nr; ++r) L.next_ranges[at_range + r] = DistRange{at_node, r};
+      for (uint32_t r = 0; list && r < c.nr; ++r) L.next_ranges[at_range + r] = DistRange{at_node, r};
+    }
+  }
+  if (copy) {  // a node without splitters, listed after the others
+    DistNode c{};
+    c.off = off;
+    c.len = len;
+    c.nr = (len + L.next_rl - 1) / L.next_rl;
+    c.nb = 1;
+    c.poff = nd.off;
+    c.plen = nd.len;
+    c.prow = nd.tbase + b * nd.stride;
+    c.pnext = b < ns ? c.prow + nd.stride : ~0u;
+    const uint32_t at_copy = atomicAdd(&L.ctr->copies, 1u);
+    const uint32_t at_range = atomicAdd(&L.ctr->ranges[L.level + 1], c.nr);
+    if (at_copy < L.max_copies && at_range + c.nr <= L.max_next_ranges) {
+      L.next_nodes[L.max_next_nodes + at_copy] = c;
+      for (uint32_t r = 0; r < c.nr; ++r)
+        L.next_ranges[at_range + r] = DistRange{L.max_next_nodes + at_copy, r};
     }
   }
 }
@@ -587,47 +760,161 @@ __global__ __launch_bounds__(kDistThreads, 4) void dist_scatter_kernel(
 }
 
 // ------------------------------------------------------------ partition ---
-// Last level: one workgroup per range; every tile is ordered by bucket in LDS
-// and written to its own place in the output array, so stores are whole lines
+// One workgroup per range; every tile is ordered by bucket in LDS and written
+// to its own place in the level's output, so stores are whole lines
 // and nothing has to be counted first.  The starts of the buckets in the
 // range's tiles are collected in LDS and leave as one short run per bucket.
-template <int KT, bool KV>
+//
+// GATHER: the level's keys are gathered from the tiles of the level before,
+// which takes the place of counting and scattering them there.  As in
+// the leaves, the pieces of a tile are listed and a bit mask tells every
+// position its piece.  A node without splitters is only brought to its place.
+template <int KT, bool KV, bool GATHER>
 __global__ __launch_bounds__(kDistThreads, 4) void dist_partition_kernel(
     const typename Key<KT>::U *__restrict__ src, const uint32_t *__restrict__ vsrc,
     typename Key<KT>::U *__restrict__ dst, uint32_t *__restrict__ vdst, Level L) {
   using U = typename Key<KT>::U;
   constexpr int NT = kDistThreads, NI = kDistItems, NW = NT / 64;
   __shared__ Classifier<U> cl;
-  __shared__ U sk[kDistTile];
+  // (gathered: a tile may list the pieces of up to 8 tiles before its first)
+  __shared__ U sk[kDistTile + (GATHER ? 16 : 0)];
   __shared__ uint32_t hist[kDistSlots], lofs[kDistSlots], wsum[NW];
   __shared__ uint16_t rows[kDistRangeTiles][kDistSlots];
   // key-value: per-wave bucket counts, dead before the keys are placed
   uint16_t *wh = reinterpret_cast<uint16_t *>(sk);
-  const uint32_t tid = threadIdx.x, wid = tid >> 6;
-  if (blockIdx.x >= L.ctr->ranges[L.level]) return;
-  const DistRange rg = L.ranges[blockIdx.x];
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const uint32_t nranges = L.ctr->ranges[L.level] < L.max_ranges ? L.ctr->ranges[L.level] : L.max_ranges;
+  // gathered: the next tile's first key is key cur_key of its node or later,
+  // the first of the piece of the parent's tile cur_t
+  __shared__ uint32_t mask[GATHER ? kDistTile / 32 : 1], next_t, next_key;
+  __shared__ uint16_t row_piece[GATHER ? kDistTile / 64 : 1];
+  uint32_t *piece = reinterpret_cast<uint32_t *>(sk);  // address - position
+  // Gathered: every XCD takes a stretch of neighbouring nodes, all ranges of
+  // kGang of them, then of the next kGang, so that workgroups that run together
+  // read the cache lines where their nodes' pieces adjoin once.  (One range of
+  // all nodes after the other: 1314 against 1238 us at 2^28 int64; the ranges
+  // dealt out to the XCDs: 1267 against 1136 at 2^27 uint64 with values.)  The
+  // copies' ranges follow.
+  uint32_t nodes = 0, each = 0, most = 0, listed = 0;
+  if constexpr (GATHER) {
+    nodes = L.ctr->nodes[L.level] < L.max_nodes ? L.ctr->nodes[L.level] : L.max_nodes;
+    each = (nodes + kXcds - 1) / kXcds;
+    most = L.ctr->most_ranges;
+    listed = (each + kGang - 1) / kGang * kGang * most * kXcds;
+  }
+  for (uint32_t ri = blockIdx.x; ri < listed + nranges; ri += gridDim.x) {
+  DistRange rg;
+  if (ri < listed) {
+    const uint32_t x = ri / kXcds, y = x / kGang;
+    const uint32_t local = y / most * kGang + x % kGang;
+    rg = DistRange{ri % kXcds * each + local, y % most};
+    if (local >= each || rg.node >= nodes || rg.r >= L.nodes[rg.node].nr) continue;
+  } else {
+    rg = L.ranges[ri - listed];
+  }
+  __syncthreads();  // the last range's LDS is read no more
   const DistNode nd = L.nodes[rg.node];
-  const ClassifierRegs<U> cr = classifier_load(cl, (const U *)L.spl + nd.sbase, nd.nb - 1);
+  const bool cut = !GATHER || nd.nb > 1;
+  ClassifierRegs<U> cr{};
+  if (cut) cr = classifier_load(cl, (const U *)L.spl + nd.sbase, nd.nb - 1);
   const uint32_t begin = rg.r * L.rl, end = begin + L.rl < nd.len ? begin + L.rl : nd.len;
-  const U *p = src + nd.off;
-  const uint32_t *vp = KV ? vsrc + nd.off : nullptr;
+  const U *p = GATHER ? src : src + nd.off;
+  const uint32_t *vp = KV ? (GATHER ? vsrc : vsrc + nd.off) : nullptr;
   U *q = dst + nd.off;
   uint32_t *vq = KV ? vdst + nd.off : nullptr;
   const uint32_t nbits = 32 - __clz(nd.nb - 1);
-  uint32_t tile = 0;
+  uint32_t tile = 0, cur_t = 0, cur_key = 0;
+  const uint32_t ptiles = GATHER ? parent_tiles(nd) : 0u;
+  if constexpr (GATHER) {
+    // the last group of 8 tiles whose keys start at or before the range's
+    const uint32_t *pre = L.pre + nd.prow / 8;
+    uint32_t lo = 0, m = (ptiles + 7) / 8;
+    while (m > 1) {
+      const uint32_t step = (m + 63) / 64, x = lane * step;
+      const uint64_t le = __ballot(x < m && pre[lo + (x < m ? x : 0u)] <= begin);
+      const uint32_t c = (uint32_t)__popcll(le) - 1;  // (the first one is)
+      lo += c * step;
+      m = m - c * step < step ? m - c * step : step;
+    }
+    cur_t = lo * 8;
+    cur_key = pre[lo];
+  }
   for (uint32_t base = begin; base < end; base += kDistTile, ++tile) {
     const uint32_t count = end - base < kDistTile ? end - base : kDistTile;
     auto at = [](int i) { return tile_at<KV>(i); };
     U k[NI];
     uint32_t v[KV ? NI : 1], b[NI], pos[NI];
+    if constexpr (GATHER) {
+      for (uint32_t i = tid; i < kDistTile / 32; i += NT) mask[i] = 0;
+      __syncthreads();
+      const uint32_t limit = base + count;
+      uint32_t np = 0;
+      do {
+        const uint32_t t = cur_t + tid;
+        uint32_t s, c;
+        piece_of(L.ptable, nd.prow, nd.pnext, nd.plen, t, s, c);
+        c -= s;
+        // keys (at most 512 tiles of 6144: 22 bits) and non-empty pieces before
+        uint32_t total;
+        const uint32_t x = block_scan<NT>(c | (c ? 1u << 22 : 0u), wsum, total);
+        const uint32_t first = cur_key + (x & 0x3fffffu), to = np + (x >> 22);
+        if (c && first < limit && first + c > base) {
+          const uint32_t from = first > base ? first - base : 0u;
+          const uint32_t stop = first + c < limit ? first + c - base : count;
+          piece[to] = nd.poff + t * kDistTile + s + base - first;  // modulo 2^32
+          if (from & 63u) {
+            const uint32_t bit = (from & 63u) - 1;
+            atomicOr(&mask[(from >> 6) * 2 + (bit >> 5)], 1u << (bit & 31u));
+          }
+          for (uint32_t r = (from + 63) / 64; r * 64 < stop; ++r) row_piece[r] = (uint16_t)to;
+        }
+        if (c && first <= limit && limit - first < c) {
+          next_t = t;
+          next_key = first;
+        }
+        np += total >> 22;
+        cur_t += NT;
+        cur_key += total & 0x3fffffu;
+        __syncthreads();
+      } while (cur_key < limit && cur_t < ptiles);
+      if (cur_key > limit) {  // a piece listed now continues in the next tile
+        cur_t = next_t;
+        cur_key = next_key;
+      }
+      uint32_t addr[NI];
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const uint32_t j = at(i) < count ? at(i) : count - 1;
-      k[i] = __builtin_nontemporal_load(&p[base + j]);
-      if constexpr (KV) v[i] = __builtin_nontemporal_load(&vp[base + j]);
+      for (int i = 0; i < NI; ++i) {
+        const uint32_t j = at(i) < count ? at(i) : count - 1, r = j >> 6;
+        const uint64_t m = (uint64_t)mask[r * 2] | (uint64_t)mask[r * 2 + 1] << 32;
+        const uint32_t started = __popcll(m & (((uint64_t)1 << (j & 63u)) - 1));
+        addr[i] = piece[row_piece[r] + started] + j;
+      }
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        k[i] = __builtin_nontemporal_load(&p[addr[i]]);
+        if constexpr (KV) v[i] = __builtin_nontemporal_load(&vp[addr[i]]);
+      }
+      __syncthreads();  // the list is read before keys or counts overwrite it
+      if (!cut) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          if (at(i) < count) {
+            q[base + at(i)] = k[i];
+            if constexpr (KV) vq[base + at(i)] = v[i];
+          }
+        }
+        continue;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const uint32_t j = at(i) < count ? at(i) : count - 1;
+        k[i] = __builtin_nontemporal_load(&p[base + j]);
+        if constexpr (KV) v[i] = __builtin_nontemporal_load(&vp[base + j]);
+      }
+#pragma unroll
+      for (int i = 0; i < NI; ++i) k[i] = Key<KT>::map(k[i]);
     }
-#pragma unroll
-    for (int i = 0; i < NI; ++i) k[i] = Key<KT>::map(k[i]);
     classify(cl, cr, k, b);
     const uint32_t mine = tile_ranks<KV>(b, pos, count, nbits, wh, hist);
     uint32_t total;
@@ -665,9 +952,10 @@ __global__ __launch_bounds__(kDistThreads, 4) void dist_partition_kernel(
     }
     __syncthreads();
   }
-  if (tid < nd.nb) {
+  if (cut && tid < nd.nb) {
     uint16_t *to = (uint16_t *)L.table + nd.tbase + tid * nd.stride + begin / kDistTile;
     for (uint32_t t = 0; t < tile; ++t) to[t] = rows[t][tid];
+  }
   }
 }
 
@@ -787,16 +1075,6 @@ __device__ __forceinline__ void sort_leaf(
   const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const uint16_t *table = (const uint16_t *)L.table;
   const DistLeaf leaf = uniform(L.leaves[li]);
-  // The leaf's piece of tile t: its first position in the tile and its end.
-  auto piece_of = [&](uint32_t t, uint32_t &s, uint32_t &e) {
-    s = e = 0;
-    if (t * kDistTile < leaf.node_len) {
-      const uint32_t rem = leaf.node_len - t * kDistTile, whole = rem < kDistTile ? rem : kDistTile;
-      s = table[leaf.row + t];
-      e = leaf.next_row != ~0u ? table[leaf.next_row + t] : whole;
-    }
-  };
-
   const uint32_t off = leaf.off, len = leaf.len_flags & kLeafLenMask;
   const uint32_t from = (leaf.len_flags >> kLeafSrcShift) & 3u;
   const bool inner = from == kSrcPieces && (leaf.len_flags & kLeafInner);
@@ -819,7 +1097,7 @@ __device__ __forceinline__ void sort_leaf(
     for (uint32_t t0 = 0; t0 < tiles && run < leaf.first + len; t0 += NT) {
       const uint32_t t = t0 + tid;
       uint32_t s, c;
-      piece_of(t, s, c);
+      piece_of(table, leaf.row, leaf.next_row, leaf.node_len, t, s, c);
       c -= s;
       // keys (at most 512 tiles of 6144: 22 bits) and non-empty pieces before
       uint32_t total;
@@ -1050,15 +1328,20 @@ __device__ __forceinline__ void sort_leaf(
 
 // The grid is the count of leaves to expect: the bound on them is more than
 // twice that, and empty workgroups cost (4096 int64 arrays: 2546 us with, 2445
-// without).  Frequent keys and short segments may leave more.
+// without).  Frequent keys and short segments may leave more.  Neighbouring
+// leaves run on one XCD (workgroups go to the eight in turn): their pieces of
+// a tile adjoin and share cache lines, which that XCD's L2 then reads once.
 template <int KT, bool KV, int NT, int NI, int WAVES>
 __global__ __launch_bounds__(NT, WAVES) void dist_leaf_kernel(
     const typename Key<KT>::U *__restrict__ in, const uint32_t *__restrict__ vin,
     const typename Key<KT>::U *__restrict__ ws, const uint32_t *__restrict__ vws,
     typename Key<KT>::U *out, uint32_t *vout, Level L) {
   const uint32_t nl = L.ctr->leaves < L.max_leaves ? L.ctr->leaves : L.max_leaves;
-  for (uint32_t li = blockIdx.x; li < nl; li += gridDim.x) {
-    if (li != blockIdx.x) __syncthreads();  // the last leaf's LDS is read no more
+  const uint32_t each = (nl + kXcds - 1) / kXcds;
+  for (uint32_t x = blockIdx.x; x < each * kXcds; x += gridDim.x) {
+    const uint32_t li = x % kXcds * each + x / kXcds;
+    if (li >= nl) continue;
+    __syncthreads();  // the last leaf's LDS is read no more
     sort_leaf<KT, KV, NT, NI>(in, vin, ws, vws, out, vout, L, li);
   }
 }
@@ -1176,7 +1459,16 @@ Level level_args(int kt, const DistPlan &d, int level, char *w) {
   L.ranges = (DistRange *)(w + d.off_ranges[level]);
   L.spl = w + d.off_spl;
   L.start = (uint32_t *)(w + d.off_start);
-  L.table = w + d.off_table;
+  L.table = w + (d.tiled(level) && level < d.levels ? d.off_ptable : d.off_table);
+  L.ptable = (const uint16_t *)(w + d.off_ptable);
+  L.pre = (uint32_t *)(w + d.off_pre);
+  L.tiled = d.tiled(level);
+  L.next_tiled = d.tiled(level + 1);
+  L.gather = d.gather && level == d.levels;
+  L.kv = d.cap == kDistCapKV;
+  L.max_copies = d.max_copies;
+  L.max_ranges = d.max_ranges[level];
+  L.max_nodes = d.max_nodes[level];
   L.leaves = (DistLeaf *)(w + d.off_leaves);
   L.rest = (uint64_t *)(w + d.off_rest);
   L.level = (uint32_t)level;
@@ -1244,7 +1536,9 @@ hipError_t launch_dist_sample(int kt, const DistPlan &d, int level, const DistBu
     using N1024 = std::integral_constant<int, 1024>;
     if (L.root_len)
       return d.root_p <= few ? go(N128{}, 0, all) : d.levels > 1 ? go(N1024{}, 0, all) : go(N512{}, 0, all);
-    if (level > 1) return go(N512{}, 0, all);  // (few nodes: a second launch costs more)
+    // (nodes of later levels are much alike, so one launch does when they need
+    // the large tile)
+    if (level > 1 && d.root_p > few) return go(N512{}, 0, all);
     const hipError_t e = go(N128{}, 0, few);
     if (e != hipSuccess) return e;
     return go(N512{}, few + 1, all);
@@ -1265,8 +1559,9 @@ hipError_t launch_dist_count(int kt, const DistPlan &d, int level, const DistBuf
 
 hipError_t launch_dist_scan(int kt, const DistPlan &d, int level, char *w, hipStream_t s) {
   const Level L = level_args(kt, d, level, w);
-  const int summed = level == 1 && d.levels > 1 && !d.n_segs;
-  if (summed) {
+  const int columns = level == 1 && d.levels > 1 && !d.n_segs && !d.tiled(level);
+  const int summed = columns || (d.tiled(level) && level < d.levels);
+  if (columns) {
     hipLaunchKernelGGL(dist_columns_kernel, dim3((kDistSlots + 3) / 4), dim3(256), 0, s, L);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1300,24 +1595,37 @@ hipError_t launch_dist_scatter(int kt, bool kv, const DistPlan &d, int level, co
   });
 }
 
-hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
-                                 hipStream_t s) {
-  const int level = d.levels;
+hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, int level, const DistBufs &b,
+                                 char *w, hipStream_t s) {
   const Level L = level_args(kt, d, level, w);
   const uint32_t *vsrc = level_vsrc(d, b, level);
-  const dim3 grid(d.max_ranges[level]);
+  void *dst = level_to_out(d, level) ? b.out : b.ws;
+  uint32_t *vdst = level_to_out(d, level) ? b.vout : b.vws;
+  // (buckets that are only brought to their place are rare)
+  const uint32_t ranges = d.max_ranges[level] - (level == d.levels ? d.max_copies : 0);
+  const dim3 grid((ranges + std::min<uint32_t>(d.max_copies, 64) + kXcds - 1) / kXcds * kXcds);
   return with_type(level_type(kt, level), [&](auto c) {
     constexpr int KT = decltype(c)::value;
     using U = typename Key<KT>::U;
     const U *src = (const U *)level_src(d, b, level);
-    if (kv)
-      hipLaunchKernelGGL((dist_partition_kernel<KT, true>), grid, dim3(kDistThreads), 0, s, src, vsrc,
-                         (U *)b.ws, b.vws, L);
-    else
-      hipLaunchKernelGGL((dist_partition_kernel<KT, false>), grid, dim3(kDistThreads), 0, s, src, vsrc,
-                         (U *)b.ws, b.vws, L);
-    return hipGetLastError();
+    auto go = [&](auto with_values, auto gather) -> hipError_t {
+      hipLaunchKernelGGL((dist_partition_kernel<KT, decltype(with_values)::value, decltype(gather)::value>),
+                         grid, dim3(kDistThreads), 0, s, src, vsrc, (U *)dst, vdst, L);
+      return hipGetLastError();
+    };
+    if constexpr (KT == 0 || KT == 2) {  // (mapped keys)
+      if (L.gather) return kv ? go(std::true_type{}, std::true_type{}) : go(std::false_type{}, std::true_type{});
+    }
+    return kv ? go(std::true_type{}, std::false_type{}) : go(std::false_type{}, std::false_type{});
   });
+}
+
+hipError_t launch_dist_pieces(int kt, const DistPlan &d, int level, char *w, hipStream_t s) {
+  const Level L = level_args(kt, d, level, w);
+  // a workgroup a bucket for one array; segments are shorter
+  hipLaunchKernelGGL(dist_pieces_kernel, dim3(d.max_nodes[level], d.max_nodes[level] > 1 ? 16 : kDistSlots),
+                     dim3(kPiecesThreads), 0, s, L);
+  return hipGetLastError();
 }
 
 hipError_t launch_dist_leaves(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,

@@ -25,6 +25,12 @@ constexpr uint32_t kDistCap = 8192, kDistCapKV = 4096;
 constexpr uint32_t kDistTarget = 4096, kDistTargetKV = 2048;
 // Most tiles of one range.
 constexpr uint32_t kDistRangeTiles = 11;
+// Shortest array whose last level gathers its keys.  Sampling gathered nodes
+// and looking up their pieces costs more than the count and the scatter of
+// short arrays (96 requests of up to 2^20 u64 with values: 664 us gathered, 644
+// scattered; the kernels of 10^7 u64 with values: 397 and 340), less than those
+// of long ones (5*10^7 int64 mod 1000: 654 and 762; 2^28 int64: 3856 and 4504).
+constexpr uint64_t kDistGatherMin = (uint64_t)1 << 25;
 // Most tiles of a node of the last level: a leaf lists one piece a tile in the
 // LDS its keys take later.  Sampled nodes stay far below.
 inline constexpr uint32_t dist_node_tiles(int kb, bool kv) {
@@ -41,11 +47,15 @@ struct DistNode {
   uint32_t tbase;     // first entry in the level's table
   uint32_t stride;    // table entries per bucket
   uint32_t nb;        // buckets (splitters + 1), set by the sampling kernel
+  // gathered nodes: the node it was a bucket of, and the rows of that node's
+  // table for this bucket and the next one (~0: the last bucket)
+  uint32_t poff, plen, prow, pnext;
 };
-// The table of a level: before the last, keys of every bucket in every range
-// ([bucket][range], uint32, made into prefix sums); last level, where every
-// bucket starts in every tile ([bucket][tile], uint16).
-struct DistRange { uint32_t node, r; };
+// The table of a level: keys of every bucket in every range ([bucket][range],
+// uint32, made into prefix sums), or, for a level that leaves its tiles in
+// place (DistPlan::tiled), where every bucket starts in every tile
+// ([bucket][tile], uint16).
+struct DistRange { uint32_t node, r; };  // (gathered level: those of copies only)
 // A bucket (or at most cap keys of one) to be sorted or moved, with all that
 // its workgroup needs to know.
 struct DistLeaf {
@@ -61,6 +71,9 @@ struct DistCounters {
   uint32_t nodes[kDistMaxLevels + 1], ranges[kDistMaxLevels + 1];
   uint32_t cols[kDistMaxLevels + 1], table[kDistMaxLevels + 1];
   uint32_t leaves, rest;
+  // gathered: buckets of the level before that are not cut again, and the most
+  // ranges of one that is
+  uint32_t copies, most_ranges;
   uint32_t small[2];  // segments of the two smallest classes
 };
 
@@ -79,11 +92,18 @@ struct DistPlan {
   uint32_t cap = 0, target = 0;
   uint32_t root_p = 0;    // most buckets aimed at in a first-level node
   uint32_t n_segs = 0;    // segmented: segments (0: one array)
+  // Two or more levels: the level before the last leaves its tiles in place
+  // as well, and the last level gathers its keys from them, which takes the
+  // place of a count and a scatter (if the tables fit the workspace).
+  bool gather = false;
+  bool tiled(int level) const { return level == levels || (gather && level == levels - 1); }
   uint32_t rl[kDistMaxLevels + 1] = {};  // keys of a range (whole tiles)
   uint32_t max_nodes[kDistMaxLevels + 1] = {}, max_ranges[kDistMaxLevels + 1] = {};
   uint32_t max_cols = 0, max_table[kDistMaxLevels + 1] = {}, max_leaves = 0, max_rest = 0;
+  uint32_t max_copies = 0;
   uint32_t leaf_grid = 0;  // workgroups of the leaf kernel: the leaves to expect
   size_t off_ctr = 0, off_nodes[kDistMaxLevels + 1] = {}, off_ranges[kDistMaxLevels + 1] = {};
+  size_t off_ptable = 0, off_pre = 0;  // gathered: the level before's table, keys before every 8 tiles
   size_t off_spl = 0, off_start = 0, off_table = 0, off_leaves = 0, off_rest = 0, off_small = 0;
   size_t end = 0;  // first byte after the distribution's arrays
 };
@@ -105,47 +125,51 @@ inline uint32_t dist_root(uint64_t units, int levels) {
 // kDistMaxPicks buckets of the target size; two levels are kept up to the
 // count where a first-level bucket half as large again as the mean still gets
 // its share of second-level buckets.
-inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb, bool kv, size_t off) {
+inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb, bool kv, size_t off,
+                          bool gather) {
   DistPlan d;
   d.cap = kv ? kDistCapKV : kDistCap;
   d.target = kv ? kDistTargetKV : kDistTarget;
   d.n_segs = n_segs;
   const uint64_t units = (max_len + d.target - 1) / d.target;
   d.levels = units <= kDistMaxPicks ? 1 : units <= 144000 ? 2 : 3;
+  d.gather = gather && d.levels > 1 && max_len >= kDistGatherMin;
   d.root_p = std::max<uint32_t>(2, std::min(kDistMaxPicks, dist_root(units, d.levels)));
   auto tiles = [](uint64_t x) { return (x + kDistTile - 1) / kDistTile; };
   // (segments up to cap keys are no nodes)
   uint64_t nodes = n_segs ? std::min<uint64_t>(n_segs, n / d.cap + 1) : 1;
   uint64_t cols = n_segs ? 2 * (n / d.target) + 4 * nodes : std::min(kDistSlots, 2 * d.root_p);
-  uint64_t leaves = n_segs, max_cols = 0, table_bytes = 0;
+  uint64_t leaves = n_segs, max_cols = 0, table_bytes = 0, ptable_bytes = 0;
   for (int l = 1; l <= d.levels; ++l) {
-    const bool last = l == d.levels;
-    // A first level that is not the last covers the array with two ranges a CU
+    const bool tiled = d.tiled(l);
+    // A first level that scatters covers the array with two ranges a CU
     // (one round of workgroups); otherwise nodes are of uneven length, and
     // more, shorter ranges balance better.
-    const uint64_t rt = l == 1 && !last ? tiles((n + 511) / 512)
+    const uint64_t rt = l == 1 && !tiled ? tiles((n + 511) / 512)
                                         : std::min<uint64_t>(kDistRangeTiles, tiles((n + 2047) / 2048));
     d.rl[l] = (uint32_t)(rt * kDistTile);
     if (l > 1) {
+      if (d.gather && l == d.levels) d.max_copies = (uint32_t)cols;
       nodes = std::min<uint64_t>(cols, n / d.cap + 1);
       cols = std::min<uint64_t>(2 * (n / d.target) + 4 * nodes, (uint64_t)kDistSlots * nodes);
     }
     d.max_nodes[l] = (uint32_t)nodes;
-    d.max_ranges[l] = (uint32_t)(n / d.rl[l] + nodes);
+    d.max_ranges[l] = (uint32_t)(n / d.rl[l] + nodes + (l == d.levels ? d.max_copies : 0));
     max_cols = std::max(max_cols, cols);
     // rows of the table are its buckets: at most 2 root_p in the first level,
-    // kDistSlots later; last level: padded to 8 entries
+    // kDistSlots later; tiles are padded to 8 entries
     const uint64_t widest = l == 1 ? std::min(kDistSlots, 2 * d.root_p) : kDistSlots;
     const uint64_t table =
-        last ? widest * (n / kDistTile) + 9 * cols : widest * (n / d.rl[l]) + cols;
+        tiled ? widest * (n / kDistTile) + 9 * cols : widest * (n / d.rl[l]) + cols;
     d.max_table[l] = (uint32_t)std::min<uint64_t>(table, 0xffffffffu);
-    table_bytes = std::max(table_bytes, table * (last ? 2 : 4));
+    if (tiled && l < d.levels) ptable_bytes = table * 2;
+    else table_bytes = std::max(table_bytes, table * (tiled ? 2 : 4));
     leaves += cols;
   }
   d.max_cols = (uint32_t)max_cols;
   d.max_leaves = (uint32_t)(leaves + n / d.cap + 1);
   const uint64_t expect = n / d.target + n / d.target / 8 + d.max_nodes[d.levels] + n_segs + 64;
-  d.leaf_grid = (uint32_t)std::min<uint64_t>(d.max_leaves, expect);
+  d.leaf_grid = (uint32_t)((std::min<uint64_t>(d.max_leaves, expect) + 7) / 8 * 8);
   d.max_rest = d.max_leaves;  // every leaf, or buckets above cap (fewer)
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -154,12 +178,14 @@ inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb,
   };
   d.off_ctr = take(sizeof(DistCounters));
   for (int l = 1; l <= d.levels; ++l) {
-    d.off_nodes[l] = take((size_t)d.max_nodes[l] * sizeof(DistNode));
+    d.off_nodes[l] = take((size_t)(d.max_nodes[l] + (l == d.levels ? d.max_copies : 0)) * sizeof(DistNode));
     d.off_ranges[l] = take((size_t)d.max_ranges[l] * sizeof(DistRange));
   }
   d.off_spl = take((size_t)d.max_cols * kb);
   d.off_start = take((size_t)d.max_cols * 4);
   d.off_table = take((size_t)table_bytes);
+  d.off_ptable = take((size_t)ptable_bytes);
+  d.off_pre = take((size_t)ptable_bytes / 4);  // a uint32 for every 8 entries
   d.off_leaves = take((size_t)d.max_leaves * sizeof(DistLeaf));
   d.off_rest = take((size_t)d.max_rest * 8);
   d.off_small = take((size_t)n_segs * 8);
@@ -196,9 +222,12 @@ PSS_WEAK hipError_t launch_dist_count(int kt, const DistPlan &d, int level, cons
 PSS_WEAK hipError_t launch_dist_scan(int kt, const DistPlan &d, int level, char *w, hipStream_t s);
 PSS_WEAK hipError_t launch_dist_scatter(int kt, bool kv, const DistPlan &d, int level,
                                         const DistBufs &b, char *w, hipStream_t s);
-// last level (its launch_dist_scan follows)
-PSS_WEAK hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, const DistBufs &b,
-                                          char *w, hipStream_t s);
+// levels that leave their tiles in place (launch_dist_scan follows)
+PSS_WEAK hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, int level,
+                                          const DistBufs &b, char *w, hipStream_t s);
+// after a partition that is not the last level's
+PSS_WEAK hipError_t launch_dist_pieces(int kt, const DistPlan &d, int level, char *w,
+                                       hipStream_t s);
 PSS_WEAK hipError_t launch_dist_leaves(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
                                        hipStream_t s);
 PSS_WEAK hipError_t launch_dist_rest(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,

@@ -1971,7 +1971,7 @@ struct SegDistArgs {
   const uint64_t *off;
   uint32_t n_segs;
   uint64_t n, longest;
-  uint32_t small0, small1, cap, target, rl, root_p, levels;
+  uint32_t small0, small1, cap, target, rl, root_p, levels, tiled;
   DistCounters *ctr;
   DistNode *nodes;
   DistRange *ranges;
@@ -2018,8 +2018,9 @@ __global__ __launch_bounds__(1024) void seg_dist_plan_kernel(SegDistArgs a) {
       d.p = d.p < a.root_p ? d.p : a.root_p;
       d.nr = (len + a.rl - 1) / a.rl;
       d.cols = node_cols(d.p);
-      d.stride = node_stride(len, d.nr, a.levels == 1);
+      d.stride = node_stride(len, d.nr, a.tiled != 0);
       d.nb = 0;
+      d.poff = d.plen = d.prow = d.pnext = 0;
       const uint32_t at = atomicAdd(&n_nodes, 1u), r0 = atomicAdd(&n_ranges, d.nr);
       d.sbase = atomicAdd(&n_cols, d.cols);
       d.tbase = atomicAdd(&n_table, d.cols * d.stride);
@@ -2176,6 +2177,7 @@ hipError_t launch_dist_segments(const DistPlan &d, const uint64_t *seg_off, uint
   a.rl = d.rl[1];
   a.root_p = d.root_p;
   a.levels = (uint32_t)d.levels;
+  a.tiled = d.tiled(1) ? 1u : 0u;
   a.ctr = (DistCounters *)(w + d.off_ctr);
   a.nodes = (DistNode *)(w + d.off_nodes[1]);
   a.ranges = (DistRange *)(w + d.off_ranges[1]);

@@ -222,3 +222,44 @@ def test_one_short_tile(n):
             keys = random_keys(np.random.default_rng(n), dtype, n)
             keys[: n // 3] = keys[-1]
             check(keys, kv)
+
+
+GATHER_MIN = 1 << 25  # from here on the last of two levels gathers its keys
+
+
+@pytest.mark.parametrize("kind", ["random", "sorted", "half", "copies", "powers", "runs"])
+@pytest.mark.parametrize("dtype", ["int32", "int64"])
+def test_gathered_level(dtype, kind):
+    """The gathered last level against torch's stable sort: pieces of a few
+    keys and of whole tiles, empty ones, and buckets that are not cut again
+    (one value, or few keys)."""
+    import torch
+
+    import paper_2305_05245_amd as pss
+
+    dt = getattr(torch, dtype)
+    info = torch.iinfo(dt)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    n = GATHER_MIN + 7 * TILE + 1
+    keys = torch.randint(info.min, info.max, (n,), dtype=dt, device="cuda", generator=g)
+    if kind == "sorted":
+        keys = torch.sort(keys).values
+    elif kind == "half":
+        keys[torch.rand(n, device="cuda", generator=g) < 0.5] = 12345
+    elif kind == "copies":
+        keys = torch.randint(0, n // 40, (n,), dtype=dt, device="cuda", generator=g)
+    elif kind == "powers":
+        keys >>= torch.randint(0, info.bits, (n,), dtype=dt, device="cuda", generator=g)
+    elif kind == "runs":    # sorted stretches, and a few low keys far apart
+        m = n // 100_000
+        keys[:m * 100_000] = torch.sort(keys[:m * 100_000].view(m, -1), dim=1).values.view(-1)
+        keys[::50_021] = info.min
+    want, at = torch.sort(keys, stable=True)
+    vals = torch.randint(0, 1 << 31, (n,), dtype=torch.int64, device="cuda", generator=g).to(torch.int32)
+    for v in (None, vals):
+        announce("distribution, gathered", dtype, kind, n, "keys" if v is None else "kv")
+        out, vout = pss.sort(keys, v, key_type="i32" if dtype == "int32" else "i64")
+        assert torch.equal(out, want)
+        if v is not None:
+            assert torch.equal(vout, v[at])

@@ -831,15 +831,20 @@ __global__ __launch_bounds__(kCorankThreads) void corank_kernel(
 
 // Same search for groups of at most 64 runs, one lane per run: the prefix
 // bounds live in registers, each level's candidates are loaded one per slot
-// by all lanes at once and sorted in registers by a bitonic network across the
-// wave (slot s = lane + 64 e), and the two prefix counts are read off with LDS
-// atomics.  E = largest number of slots per lane (3 * 64 candidates < 64 * 4).
+// by all lanes at once (slot s = lane + 64 e) and ordered, and the two prefix
+// counts are read off with LDS atomics.  E = largest number of slots per lane
+// (3 * 64 candidates < 64 * 4).  A single wave a row: its time is the length of
+// its instruction stream.  Up to 32 runs every candidate is ranked by comparing
+// it with all of them through LDS broadcasts (8 runs of 4096 f32: 18.4 us with
+// the network, 14.5 ranked); beyond, a bitonic network across the wave (64
+// blocks of 16384 int32: 137 us, 150 ranked).
 template <typename U, int E, bool SAMPLED>
 __global__ __launch_bounds__(kCorankThreads) void corank_wave_kernel(
     const U *__restrict__ src_primary, const U *__restrict__ src_alt, RunGeom g,
     uint32_t *__restrict__ table, U *__restrict__ pivots, uint64_t *__restrict__ counts, int kt,
     SampleIndex si) {
   __shared__ uint32_t slot_run[64 * E];
+  __shared__ U slot_key[E <= 2 ? 64 * E : 1];
   __shared__ uint32_t cnt[2 * 64];
 
   const uint32_t lane = threadIdx.x;
@@ -936,10 +941,8 @@ __global__ __launch_bounds__(kCorankThreads) void corank_wave_kernel(
       cnt[lane + 64] = 0;
       __syncthreads();
 
-      uint32_t Cp = 64;
-      while (Cp < C) Cp <<= 1;
       U key[E];
-      uint32_t tie[E];
+      uint32_t tie[E], rank[E];
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const uint32_t s = lane + 64 * e;
@@ -949,33 +952,60 @@ __global__ __launch_bounds__(kCorankThreads) void corank_wave_kernel(
         const uint32_t rb_a = __shfl(A, (int)rb, 64);
         key[e] = key_max<U>();
         tie[e] = 0xffffffffu;
+        rank[e] = s;
         if (s < C) {
           const uint32_t x = s - rb_off;
           key[e] = src[ri.grp.start + (uint64_t)rb * R + (uint64_t)(2 * rb_a + 1 + x) * h - 1];
           tie[e] = (rb << 20) | x;
         }
       }
-
-      // bitonic sort of Cp slots, ascending by (key, tie): distances of 64
-      // and more exchange slots inside a lane, smaller ones exchange lanes
-      for (uint32_t k = 2; k <= Cp; k <<= 1) {
-        for (uint32_t d = k >> 1; d >= 64; d >>= 1) {
-          const uint32_t de = d >> 6;
+      if constexpr (E <= 2) {
+        // The slots lie in the order of the candidates' ties: each candidate's
+        // rank is the number of those before it in (key, slot).
 #pragma unroll
-          for (int e = 0; e < E; ++e) {
-            if (E > 1 && ((uint32_t)e & de) == 0 && (e | (int)de) < E && 64u * (e | de) < Cp) {
-              const bool up = ((lane + 64u * e) & k) == 0;
-              if (de == 1) cas<U, E>(key[e], tie[e], key[e | 1], tie[e | 1], up);
-              else if (de == 2) cas<U, E>(key[e], tie[e], key[(e | 2) & (E - 1)], tie[(e | 2) & (E - 1)], up);
+        for (int e = 0; e < E; ++e) {
+          slot_key[lane + 64 * e] = key[e];
+          rank[e] = 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < E; ++b) {
+          const uint32_t end = C < 64u * b ? 0u : (C - 64u * b < 64u ? C - 64u * b : 64u);
+#pragma unroll 4
+          for (uint32_t t = 0; t < end; ++t) {
+            const U o = slot_key[64 * b + t];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+              const bool before = e > b ? o <= key[e] : e < b ? o < key[e]
+                                        : o < key[e] || (o == key[e] && t < lane);
+              rank[e] += before ? 1u : 0u;
             }
           }
         }
-        if (k > 32) bitonic_lane_stage<32>(key, tie, lane, k, Cp);
-        if (k > 16) bitonic_lane_stage<16>(key, tie, lane, k, Cp);
-        if (k > 8) bitonic_lane_stage<8>(key, tie, lane, k, Cp);
-        if (k > 4) bitonic_lane_stage<4>(key, tie, lane, k, Cp);
-        if (k > 2) bitonic_lane_stage<2>(key, tie, lane, k, Cp);
-        bitonic_lane_stage<1>(key, tie, lane, k, Cp);
+      } else {
+        uint32_t Cp = 64;
+        while (Cp < C) Cp <<= 1;
+        // bitonic sort of Cp slots, ascending by (key, tie): distances of 64
+        // and more exchange slots inside a lane, smaller ones exchange lanes
+        for (uint32_t k = 2; k <= Cp; k <<= 1) {
+          for (uint32_t d = k >> 1; d >= 64; d >>= 1) {
+            const uint32_t de = d >> 6;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+              if (E > 1 && ((uint32_t)e & de) == 0 && (e | (int)de) < E && 64u * (e | de) < Cp) {
+                const bool up = ((lane + 64u * e) & k) == 0;
+                if (de == 1) cas<U, E>(key[e], tie[e], key[e | 1], tie[e | 1], up);
+                else if (de == 2) cas<U, E>(key[e], tie[e], key[(e | 2) & (E - 1)], tie[(e | 2) & (E - 1)], up);
+              }
+            }
+          }
+          if (k > 32) bitonic_lane_stage<32>(key, tie, lane, k, Cp);
+          if (k > 16) bitonic_lane_stage<16>(key, tie, lane, k, Cp);
+          if (k > 8) bitonic_lane_stage<8>(key, tie, lane, k, Cp);
+          if (k > 4) bitonic_lane_stage<4>(key, tie, lane, k, Cp);
+          if (k > 2) bitonic_lane_stage<2>(key, tie, lane, k, Cp);
+          bitonic_lane_stage<1>(key, tie, lane, k, Cp);
+        }
       }
 
       uint64_t rho_lo = q_lo - base, rho_hi = q_hi - base;
@@ -988,10 +1018,10 @@ __global__ __launch_bounds__(kCorankThreads) void corank_wave_kernel(
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const uint32_t s = lane + 64 * e;
-        if (s < rho_hi) {
+        if (s < C && rank[e] < rho_hi) {  // (sorted: the key of rank s is in slot s)
           const uint32_t rb = tie[e] >> 20;
           atomicAdd(&cnt[64 + rb], 1u);
-          if (s < rho_lo) atomicAdd(&cnt[rb], 1u);
+          if (rank[e] < rho_lo) atomicAdd(&cnt[rb], 1u);
         }
       }
       __syncthreads();

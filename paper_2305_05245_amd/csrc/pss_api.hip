@@ -52,10 +52,16 @@ uint64_t ceil_div(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 constexpr uint64_t kMaxTableEntries = (uint64_t)1 << 28;
 
 // Shortest array the automatic plan distributes into buckets.  Below it the few
-// launches of one or two merge passes cost less than sampling (30011 f32 pairs:
-// 68 us merged, 81 us distributed); above it distributing wins (10^6 int64: 82
-// against 178 us).
-constexpr uint64_t kDistMinKeys = 65537;
+// launches of one or two merge passes cost less than sampling.  Integers from
+// one tile on (9001 int32 merged and distributed: 43 and 37 us, with values 55
+// and 37, few values with values 55 and 44; 60001: 60 and 38, 74 and 42, 74 and
+// 70).  Floats of both signs have a bucket around zero that spans all small
+// magnitudes, and its crowded leaf takes the slow path, which shorter arrays
+// don't make up for (30011 normal f32: 51 and 54 us, with values 64 and 66;
+// 60001: 60 and 56, 74 and 69).
+constexpr uint64_t dist_min_keys(pss_key_t key) {
+  return key == PSS_F32 || key == PSS_F64 ? 40000 : 8193;
+}
 
 // Merge passes that sort every segment of seg_len keys, starting from sorted
 // tiles of `tile` keys: the number of doublings needed is split as evenly as
@@ -228,7 +234,7 @@ pss_status make_plan(pss_key_t key, pss_val_t val, uint64_t n, uint32_t n_blocks
     p->off_offsets = take(((size_t)n_parts + 1) * sizeof(uint64_t));
   }
   p->total = off;
-  if (!p->paper && n >= kDistMinKeys && pss::launch_dist_sample) {
+  if (!p->paper && n >= dist_min_keys(key) && pss::launch_dist_sample) {
     p->dist = plan_dist(n, n, 0, p->kb, p->kv, p->off_table, p->total);
   }
   return PSS_OK;

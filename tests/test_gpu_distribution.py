@@ -193,24 +193,28 @@ def test_segment_length_bound_too_small():
                 assert np.array_equal(got[lo:hi], np.sort(keys[lo:hi]))
 
 
-@pytest.mark.parametrize("copies", [2, 3, 6, 20])
+@pytest.mark.parametrize("copies", [2, 3, 6, 20, 96, 97, 255, 256])
 @pytest.mark.parametrize("dtype", [np.uint32, np.int64], ids=lambda d: np.dtype(d).name)
 def test_leaf_bins(dtype, copies):
     """One leaf of keys with several copies each: more bins to sort than the
     leaf's list holds at once (pairs), bins sorted in registers (3), by
-    insertion (6), and up to the crowded limit (20)."""
+    insertion (6), and up to the crowded limits.  Keys of all bits, and small
+    ones whose bins hold one value each."""
     rng = np.random.default_rng(copies)
     for kv, n in ((False, 8192), (False, 8191), (True, 4096), (True, 4093)):
-        keys = np.repeat(random_keys(rng, dtype, n // copies + 1), copies)[:n]
-        keys = rng.permutation(keys)
-        vals = rng.permutation(n).astype(np.uint32) if kv else None
-        announce("distribution leaf", np.dtype(dtype).name, copies, n, "kv" if kv else "keys")
-        got, vgot, err, _ = _segmented(keys, [n], vals, max_seg_len=3 * TILE)
-        assert err == 0
-        perm = np.argsort(order_bits(keys), kind="stable")
-        assert got.tobytes() == keys[perm].tobytes()
-        if kv:
-            assert np.array_equal(vgot, vals[perm])
+        for small in (False, True):
+            each = random_keys(rng, dtype, n // copies + 1)
+            if small:
+                each = np.arange(each.size).astype(dtype)
+            keys = rng.permutation(np.repeat(each, copies)[:n])
+            vals = rng.permutation(n).astype(np.uint32) if kv else None
+            announce("distribution leaf", np.dtype(dtype).name, copies, n, "kv" if kv else "keys")
+            got, vgot, err, _ = _segmented(keys, [n], vals, max_seg_len=3 * TILE)
+            assert err == 0
+            perm = np.argsort(order_bits(keys), kind="stable")
+            assert got.tobytes() == keys[perm].tobytes()
+            if kv:
+                assert np.array_equal(vgot, vals[perm])
 
 
 @pytest.mark.parametrize("n", [1, 2, 63, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 8192])
@@ -263,3 +267,18 @@ def test_gathered_level(dtype, kind):
         assert torch.equal(out, want)
         if v is not None:
             assert torch.equal(vout, v[at])
+
+
+@pytest.mark.parametrize("n", [8191, 8192, 8193, 8194, 39_999, 40_000])
+@pytest.mark.parametrize("dtype", [np.int32, np.uint64, np.float32, np.float64],
+                         ids=lambda d: np.dtype(d).name)
+def test_shortest_distributed(dtype, n):
+    """Both sides of the shortest arrays distributed, of random bits (floats:
+    every special value), of 200 values (bins of one value) and normal ones."""
+    rng = np.random.default_rng(n)
+    few = rng.integers(0, 200, size=n)
+    for keys in (random_keys(rng, dtype, n), few.astype(dtype),
+                 (rng.standard_normal(n) * 1e6).astype(dtype)):
+        for kv in (False, True):
+            announce("shortest distributed", np.dtype(dtype).name, n, "kv" if kv else "keys")
+            check(keys, kv)

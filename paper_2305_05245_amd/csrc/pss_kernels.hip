@@ -1917,9 +1917,13 @@ __global__ __launch_bounds__(1024) void seg_plan_kernel(const uint64_t *__restri
                                                         uint32_t fan_log2, uint32_t tile,
                                                         uint32_t part) {
   __shared__ uint64_t wsum[17];
-  __shared__ uint32_t bad;
+  // two words: `bad` is read while another wave may already set `over`
+  __shared__ uint32_t bad, over;
   const uint32_t tid = threadIdx.x;
-  if (tid == 0) bad = (off[0] != 0 || off[n_segs] > n) ? 1u : 0u;
+  if (tid == 0) {
+    bad = (off[0] != 0 || off[n_segs] > n) ? 1u : 0u;
+    over = 0;
+  }
   __syncthreads();
   for (uint32_t s = tid; s < n_segs; s += blockDim.x)
     if (off[s + 1] < off[s]) atomicOr(&bad, 1u);
@@ -1949,7 +1953,7 @@ __global__ __launch_bounds__(1024) void seg_plan_kernel(const uint64_t *__restri
       np = (bits + fan_log2 - 1) / fan_log2;
     }
     if (np > max_passes) {  // the host bound on passes was too small
-      atomicOr(&bad, 2u);
+      atomicOr(&over, 1u);
       np = 0;
       cls = -1;
     }
@@ -1980,7 +1984,7 @@ __global__ __launch_bounds__(1024) void seg_plan_kernel(const uint64_t *__restri
     }
   }
   __syncthreads();
-  if (tid == 0 && (bad & 2u)) report(kErrSegments);
+  if (tid == 0 && over) report(kErrSegments);
   for (int c = 0; c < 3; ++c) block_inclusive_scan_u64(pa.tiles[c] + 1, n_segs, wsum);
   block_inclusive_scan_u64(pa.soff + 1, n_segs, wsum);
   for (uint32_t q = 0; q < max_passes; ++q) {
@@ -2011,13 +2015,15 @@ struct SegDistArgs {
 };
 
 __global__ __launch_bounds__(1024) void seg_dist_plan_kernel(SegDistArgs a) {
-  __shared__ uint32_t bad;
+  // two words: `bad` is read while another wave may already set `over`
+  __shared__ uint32_t bad, over;
   __shared__ uint32_t n_small[2], n_leaves, n_nodes, n_ranges, n_cols, n_table;
   const uint32_t tid = threadIdx.x;
   uint32_t *c = (uint32_t *)a.ctr;
   for (uint32_t i = tid; i < sizeof(DistCounters) / 4; i += 1024) c[i] = 0;
   if (tid == 0) {
     bad = (a.off[0] != 0 || a.off[a.n_segs] > a.n) ? 1u : 0u;
+    over = 0;
     n_small[0] = n_small[1] = n_leaves = n_nodes = n_ranges = n_cols = n_table = 0;
   }
   __syncthreads();
@@ -2061,10 +2067,10 @@ __global__ __launch_bounds__(1024) void seg_dist_plan_kernel(SegDistArgs a) {
       }
     }
   }
-  if (left_out) atomicOr(&bad, 2u);
+  if (left_out) atomicOr(&over, 1u);
   __syncthreads();
   if (tid == 0) {
-    if (bad & 2u) report(kErrSegments);
+    if (over) report(kErrSegments);
     a.ctr->nodes[1] = n_nodes;
     a.ctr->ranges[1] = n_ranges;
     a.ctr->cols[1] = n_cols;

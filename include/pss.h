@@ -453,7 +453,9 @@ pss_status pss_profile_only(pss_ctx *ctx, const char *family);
  * segments do not add up to their partition.  A kernel that sets a bit stops
  * before writing outside its own partition, and its output is then invalid.
  * Bit 16: segment offsets of pss_segmented_sort invalid (or a segment needing
- * more merge passes than tuning->max_seg_len allowed for).
+ * more merge passes than tuning->max_seg_len allowed for).  Bit 32: more
+ * buckets, ranges or table entries than the plan of a sort by sampled buckets
+ * has room for; the rest of that sort is not run and its output is invalid.
  * Meant for tests and debugging; it synchronises the whole device.
  */
 pss_status pss_device_check(pss_ctx *ctx, uint32_t *code);

@@ -69,10 +69,19 @@ struct Level {
   uint32_t root_len, root_p;  // level 1 of a single array (0: nodes are given)
   uint32_t tiled, next_tiled;  // its tiles are left in place
   uint32_t gather;  // its keys are gathered from the tiles of the level before
-  uint32_t kv, max_copies, max_ranges, max_nodes;
+  uint32_t kv, max_copies;
   const uint16_t *ptable;  // gathered: the table of the level before,
   uint32_t *pre;           // and per bucket the keys before every 8 tiles
+  uint32_t *err;           // device error word
 };
+
+// A bound of the plan does not hold: what would lie past it is not written, the
+// error word is set, and every later kernel of the sort returns at once (it
+// would meet nodes, ranges or leaves that were never written).
+__device__ __forceinline__ void plan_failed(DistCounters *ctr, uint32_t *err) {
+  atomicOr(&ctr->failed, 1u);
+  atomicOr(err, kErrPlan);
+}
 
 // Inclusive sum over the wave's lanes, in DPP moves: shifts by 1, 2, 4 and 8
 // lanes within rows of 16, then the last lane of row 0 to row 1 and of row 2
@@ -202,7 +211,7 @@ constexpr int kPiecesThreads = 512;
 __global__ __launch_bounds__(kPiecesThreads) void dist_pieces_kernel(Level L) {
   __shared__ uint32_t wsum[kPiecesThreads / 64];
   const uint32_t tid = threadIdx.x;
-  if (blockIdx.x >= L.ctr->nodes[L.level]) return;
+  if (blockIdx.x >= L.ctr->nodes[L.level] || L.ctr->failed) return;
   const DistNode nd = L.nodes[blockIdx.x];
   const uint32_t tiles = (nd.len + kDistTile - 1) / kDistTile;
   for (uint32_t b = blockIdx.y; b < nd.nb; b += gridDim.y) {
@@ -224,6 +233,97 @@ __global__ __launch_bounds__(kPiecesThreads) void dist_pieces_kernel(Level L) {
       __syncthreads();
     }
     if (tid == 0) L.start[nd.sbase + b] = run;
+  }
+}
+
+// ------------------------------------------------------------- segments ---
+// Segmented distribution sort: one workgroup reads the segment offsets, checks
+// them, and lists every segment by its length: the two classes of short
+// segments, leaves (at most cap keys), first-level nodes.  Invalid offsets (not
+// starting at 0, decreasing, or ending beyond n) give empty lists and an error
+// bit; segments above `longest` (what the caller's bound on the segment length
+// allows) are left out and give it too.
+struct SegDistArgs {
+  const uint64_t *off;
+  uint32_t n_segs;
+  uint64_t n, longest;
+  uint32_t small0, small1, cap, target, rl, root_p, levels, tiled;
+  DistCounters *ctr;
+  DistNode *nodes;
+  DistRange *ranges;
+  DistLeaf *leaves;
+  uint32_t *small;  // [2][n_segs]
+  uint32_t max_nodes, max_ranges, max_cols, max_table, max_leaves;
+  uint32_t *err;  // device error word
+};
+
+__global__ __launch_bounds__(1024) void seg_dist_plan_kernel(SegDistArgs a) {
+  // two words: `bad` is read while another wave may already set `over`
+  __shared__ uint32_t bad, over;
+  __shared__ uint32_t n_small[2], n_leaves, n_nodes, n_ranges, n_cols, n_table;
+  const uint32_t tid = threadIdx.x;
+  uint32_t *c = (uint32_t *)a.ctr;
+  for (uint32_t i = tid; i < sizeof(DistCounters) / 4; i += 1024) c[i] = 0;
+  if (tid == 0) {
+    bad = (a.off[0] != 0 || a.off[a.n_segs] > a.n) ? 1u : 0u;
+    over = 0;
+    n_small[0] = n_small[1] = n_leaves = n_nodes = n_ranges = n_cols = n_table = 0;
+  }
+  __syncthreads();
+  for (uint32_t s = tid; s < a.n_segs; s += 1024)
+    if (a.off[s + 1] < a.off[s]) atomicOr(&bad, 1u);
+  __syncthreads();
+  const bool ok = bad == 0;
+  if (tid == 0 && !ok) atomicOr(a.err, kErrSegments);
+  if (!ok) return;
+  bool left_out = false;
+  for (uint32_t s = tid; s < a.n_segs; s += 1024) {
+    const uint64_t len64 = a.off[s + 1] - a.off[s];
+    const uint32_t off = (uint32_t)a.off[s], len = (uint32_t)len64;
+    if (len64 == 0) continue;
+    if (len64 > a.longest) {
+      left_out = true;
+    } else if (len <= a.small1) {
+      const int cls = len <= a.small0 ? 0 : 1;
+      a.small[(uint64_t)cls * a.n_segs + atomicAdd(&n_small[cls], 1u)] = s;
+    } else if (len <= a.cap) {
+      const uint32_t to = atomicAdd(&n_leaves, 1u);
+      if (to < a.max_leaves) a.leaves[to] = DistLeaf{off, len | kSrcIn << kLeafSrcShift, 0, 0, 0, 0, 0, 0, 0, 0};
+      else plan_failed(a.ctr, a.err);
+    } else {
+      DistNode d;
+      d.off = off;
+      d.len = len;
+      d.p = node_picks(len, a.target, (int)a.levels);
+      d.p = d.p < a.root_p ? d.p : a.root_p;
+      d.nr = (len + a.rl - 1) / a.rl;
+      d.cols = node_cols(d.p);
+      d.stride = node_stride(len, d.nr, a.tiled != 0);
+      d.nb = 0;
+      d.poff = d.plen = d.prow = d.pnext = 0;
+      const uint32_t at = atomicAdd(&n_nodes, 1u), r0 = atomicAdd(&n_ranges, d.nr);
+      d.sbase = atomicAdd(&n_cols, d.cols);
+      d.tbase = atomicAdd(&n_table, d.cols * d.stride);
+      if (at < a.max_nodes && r0 + d.nr <= a.max_ranges && d.sbase + d.cols <= a.max_cols &&
+          d.tbase + d.cols * d.stride <= a.max_table) {
+        a.nodes[at] = d;
+        for (uint32_t r = 0; r < d.nr; ++r) a.ranges[r0 + r] = DistRange{at, r};
+      } else {
+        plan_failed(a.ctr, a.err);
+      }
+    }
+  }
+  if (left_out) atomicOr(&over, 1u);
+  __syncthreads();
+  if (tid == 0) {
+    if (over) atomicOr(a.err, kErrSegments);
+    a.ctr->nodes[1] = n_nodes;
+    a.ctr->ranges[1] = n_ranges;
+    a.ctr->cols[1] = n_cols;
+    a.ctr->table[1] = n_table;
+    a.ctr->leaves = n_leaves;
+    a.ctr->small[0] = n_small[0];
+    a.ctr->small[1] = n_small[1];
   }
 }
 
@@ -259,7 +359,7 @@ __global__ __launch_bounds__(NT) void dist_sample_kernel(const typename Key<KT>:
       L.ctr->ranges[1] = nd.nr;
     }
   } else {
-    if (blockIdx.x >= L.ctr->nodes[L.level]) return;
+    if (blockIdx.x >= L.ctr->nodes[L.level] || L.ctr->failed) return;
     nd = L.nodes[blockIdx.x];
     if (nd.p < p_lo || nd.p > p_hi) return;  // another tile size samples it
   }
@@ -405,7 +505,7 @@ __global__ __launch_bounds__(kDistThreads) void dist_count_kernel(
   __shared__ Classifier<U> cl;
   __shared__ uint32_t hist[kDistSlots];
   const uint32_t tid = threadIdx.x;
-  if (blockIdx.x >= L.ctr->ranges[L.level]) return;
+  if (blockIdx.x >= L.ctr->ranges[L.level] || L.ctr->failed) return;
   const DistRange rg = L.ranges[blockIdx.x];
   const DistNode nd = L.nodes[rg.node];
   for (uint32_t i = tid; i < kDistSlots; i += kDistThreads) hist[i] = 0;
@@ -445,6 +545,7 @@ __global__ __launch_bounds__(kDistThreads) void dist_count_kernel(
 // One wave per bucket of the root node, whose hundreds of ranges are too many
 // for one thread: exclusive sums over the ranges in place, the total to start.
 __global__ __launch_bounds__(256) void dist_columns_kernel(Level L) {
+  if (L.ctr->failed) return;
   const DistNode nd = L.nodes[0];
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t b = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -470,6 +571,8 @@ __global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summ
   __shared__ uint32_t leaf0;
   const uint32_t b = threadIdx.x;
   if (blockIdx.x >= L.ctr->nodes[L.level]) return;
+  // (other workgroups of this launch may set the flag: one answer for all waves)
+  if (__syncthreads_or(L.ctr->failed != 0)) return;
   const DistNode nd = L.nodes[blockIdx.x];
   const bool last = L.level == L.levels;
   uint32_t len = 0, off = nd.off;
@@ -552,11 +655,14 @@ __global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summ
                                   (rest ? kLeafMove : 0u) | (b > 0 && b < ns ? kLeafInner : 0u),
                               nd.off, nd.len, o, row, b < ns ? row + nd.stride : ~0u, 0u, (uint64_t)lo,
                               (uint64_t)hi};
+    } else {
+      plan_failed(L.ctr, L.err);
     }
   }
   if (rest) {
     const uint32_t to = atomicAdd(&L.ctr->rest, 1u);
     if (to < L.max_rest) L.rest[to] = (uint64_t)off | (uint64_t)len << 32;
+    else plan_failed(L.ctr, L.err);
   }
   if (node) {
     DistNode c;
@@ -579,11 +685,13 @@ __global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summ
     if (!list) atomicMax(&L.ctr->most_ranges, c.nr);
     c.sbase = atomicAdd(&L.ctr->cols[lv], c.cols);
     c.tbase = atomicAdd(&L.ctr->table[lv], c.cols * c.stride);
-    // (the plan's bounds hold for any lengths; this keeps writes inside them)
+    // (the plan's bounds hold for any lengths)
     if (at_node < L.max_next_nodes && (!list || at_range + c.nr <= L.max_next_ranges) &&
         c.sbase + c.cols <= L.max_cols && c.tbase + c.cols * c.stride <= L.max_next_table) {
       L.next_nodes[at_node] = c;
       for (uint32_t r = 0; list && r < c.nr; ++r) L.next_ranges[at_range + r] = DistRange{at_node, r};
+    } else {
+      plan_failed(L.ctr, L.err);
     }
   }
   if (copy) {  // a node without splitters, listed after the others
@@ -602,6 +710,8 @@ __global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summ
       L.next_nodes[L.max_next_nodes + at_copy] = c;
       for (uint32_t r = 0; r < c.nr; ++r)
         L.next_ranges[at_range + r] = DistRange{L.max_next_nodes + at_copy, r};
+    } else {
+      plan_failed(L.ctr, L.err);
     }
   }
 }
@@ -693,7 +803,7 @@ __global__ __launch_bounds__(kDistThreads, 4) void dist_scatter_kernel(
   static_assert(NW * kDistSlots * 2 <= sizeof(sk), "wave counts fit the key area");
   static_assert(NT == (int)kDistSlots, "one thread per bucket");
   const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  if (blockIdx.x >= L.ctr->ranges[L.level]) return;
+  if (blockIdx.x >= L.ctr->ranges[L.level] || L.ctr->failed) return;
   const DistRange rg = L.ranges[blockIdx.x];
   const DistNode nd = L.nodes[rg.node];
   const ClassifierRegs<U> cr = classifier_load(cl, (const U *)L.spl + nd.sbase, nd.nb - 1);
@@ -789,7 +899,8 @@ __global__ __launch_bounds__(kDistThreads, 4) void dist_partition_kernel(
   // key-value: per-wave bucket counts, dead before the keys are placed
   uint16_t *wh = reinterpret_cast<uint16_t *>(sk);
   const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const uint32_t nranges = L.ctr->ranges[L.level] < L.max_ranges ? L.ctr->ranges[L.level] : L.max_ranges;
+  const uint32_t nranges = L.ctr->ranges[L.level];
+  if (L.ctr->failed) return;
   // gathered: the next tile's first key is key cur_key of its node or later,
   // the first of the piece of the parent's tile cur_t
   __shared__ uint32_t mask[GATHER ? kDistTile / 32 : 1], next_t, next_key;
@@ -803,7 +914,7 @@ __global__ __launch_bounds__(kDistThreads, 4) void dist_partition_kernel(
   // copies' ranges follow.
   uint32_t nodes = 0, each = 0, most = 0, listed = 0;
   if constexpr (GATHER) {
-    nodes = L.ctr->nodes[L.level] < L.max_nodes ? L.ctr->nodes[L.level] : L.max_nodes;
+    nodes = L.ctr->nodes[L.level];
     each = (nodes + kXcds - 1) / kXcds;
     most = L.ctr->most_ranges;
     listed = (each + kGang - 1) / kGang * kGang * most * kXcds;
@@ -1245,6 +1356,7 @@ __device__ __forceinline__ void sort_leaf(
     if (tid == 0) {
       const uint32_t to = atomicAdd(&L.ctr->rest, 1u);
       if (to < L.max_rest) L.rest[to] = (uint64_t)off | (uint64_t)len << 32;
+      else plan_failed(L.ctr, L.err);
     }
     return;
   }
@@ -1370,7 +1482,10 @@ __global__ __launch_bounds__(NT, WAVES) void dist_leaf_kernel(
     const typename Key<KT>::U *__restrict__ in, const uint32_t *__restrict__ vin,
     const typename Key<KT>::U *__restrict__ ws, const uint32_t *__restrict__ vws,
     typename Key<KT>::U *out, uint32_t *vout, Level L) {
-  const uint32_t nl = L.ctr->leaves < L.max_leaves ? L.ctr->leaves : L.max_leaves;
+  const uint32_t nl = L.ctr->leaves;
+  // a bound did not hold (the flag is not looked at, as this launch may set it:
+  // the leaves that were written can be sorted)
+  if (nl > L.max_leaves) return;
   const uint32_t each = (nl + kXcds - 1) / kXcds;
   for (uint32_t x = blockIdx.x; x < each * kXcds; x += gridDim.x) {
     const uint32_t li = x % kXcds * each + x / kXcds;
@@ -1391,15 +1506,15 @@ template <int KT, bool KV, int NT>
 __global__ __launch_bounds__(NT) void dist_rest_kernel(typename Key<KT>::U *ws, uint32_t *vws,
                                                        typename Key<KT>::U *out, uint32_t *vout,
                                                        const uint64_t *__restrict__ rest,
-                                                       const DistCounters *__restrict__ ctr,
-                                                       uint32_t max_rest) {
+                                                       const DistCounters *__restrict__ ctr) {
   using U = typename Key<KT>::U;
   using T = TileLds<KV, NT>;
   constexpr uint32_t CAP = NT * kTileItems;
   __shared__ U sk[T::SLOTS];
   __shared__ uint32_t sv[KV ? T::SLOTS : 1];
   const uint32_t tid = threadIdx.x;
-  const uint32_t no = ctr->rest < max_rest ? ctr->rest : max_rest;
+  const uint32_t no = ctr->rest;
+  if (ctr->failed) return;
   for (uint32_t oi = blockIdx.x; oi < no; oi += gridDim.x) {
     const uint32_t off = (uint32_t)rest[oi], len = (uint32_t)(rest[oi] >> 32);
     const bool one = len <= CAP;
@@ -1486,8 +1601,15 @@ const uint32_t *level_vsrc(const DistPlan &d, const DistBufs &b, int level) {
   return level == 1 ? b.vin : level_to_out(d, level - 1) ? b.vout : b.vws;
 }
 
-Level level_args(int kt, const DistPlan &d, int level, char *w) {
-  Level L{};
+hipError_t level_error_word(uint32_t **err) {
+  int device = 0;
+  const hipError_t e = hipGetDevice(&device);
+  return e != hipSuccess ? e : error_word(device, err);
+}
+
+hipError_t level_args(int kt, const DistPlan &d, int level, char *w, Level &L) {
+  const hipError_t e = level_error_word(&L.err);
+  if (e != hipSuccess) return e;
   L.ctr = (DistCounters *)(w + d.off_ctr);
   L.nodes = (DistNode *)(w + d.off_nodes[level]);
   L.ranges = (DistRange *)(w + d.off_ranges[level]);
@@ -1501,8 +1623,6 @@ Level level_args(int kt, const DistPlan &d, int level, char *w) {
   L.gather = d.gather && level == d.levels;
   L.kv = d.cap == kDistCapKV;
   L.max_copies = d.max_copies;
-  L.max_ranges = d.max_ranges[level];
-  L.max_nodes = d.max_nodes[level];
   L.leaves = (DistLeaf *)(w + d.off_leaves);
   L.rest = (uint64_t *)(w + d.off_rest);
   L.level = (uint32_t)level;
@@ -1523,7 +1643,7 @@ Level level_args(int kt, const DistPlan &d, int level, char *w) {
     L.max_next_ranges = d.max_ranges[level + 1];
     L.max_next_table = d.max_table[level + 1];
   }
-  return L;
+  return hipSuccess;
 }
 
 // Level 1 reads raw keys of type kt; later levels read mapped keys, which are
@@ -1544,9 +1664,41 @@ template <typename F> hipError_t with_type(int kt, F &&f) {
 
 }  // namespace
 
+hipError_t launch_dist_segments(const DistPlan &d, const uint64_t *seg_off, uint64_t n,
+                                uint32_t small0, uint32_t small1, uint64_t longest, char *w,
+                                hipStream_t s) {
+  SegDistArgs a{};
+  if (const hipError_t e = level_error_word(&a.err); e != hipSuccess) return e;
+  a.off = seg_off;
+  a.n_segs = d.n_segs;
+  a.n = n;
+  a.longest = longest;
+  a.small0 = small0;
+  a.small1 = small1;
+  a.cap = d.cap;
+  a.target = d.target;
+  a.rl = d.rl[1];
+  a.root_p = d.root_p;
+  a.levels = (uint32_t)d.levels;
+  a.tiled = d.tiled(1) ? 1u : 0u;
+  a.ctr = (DistCounters *)(w + d.off_ctr);
+  a.nodes = (DistNode *)(w + d.off_nodes[1]);
+  a.ranges = (DistRange *)(w + d.off_ranges[1]);
+  a.leaves = (DistLeaf *)(w + d.off_leaves);
+  a.small = (uint32_t *)(w + d.off_small);
+  a.max_nodes = d.max_nodes[1];
+  a.max_ranges = d.max_ranges[1];
+  a.max_cols = d.max_cols;
+  a.max_table = d.max_table[1];
+  a.max_leaves = d.max_leaves;
+  hipLaunchKernelGGL(seg_dist_plan_kernel, dim3(1), dim3(1024), 0, s, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_dist_sample(int kt, const DistPlan &d, int level, const DistBufs &b, uint64_t n,
                               char *w, hipStream_t s) {
-  Level L = level_args(kt, d, level, w);
+  Level L{};
+  if (const hipError_t e = level_args(kt, d, level, w, L); e != hipSuccess) return e;
   if (level == 1 && !d.n_segs) {
     L.root_len = (uint32_t)n;
     L.root_p = d.root_p;
@@ -1581,7 +1733,8 @@ hipError_t launch_dist_sample(int kt, const DistPlan &d, int level, const DistBu
 
 hipError_t launch_dist_count(int kt, const DistPlan &d, int level, const DistBufs &b, char *w,
                              hipStream_t s) {
-  const Level L = level_args(kt, d, level, w);
+  Level L{};
+  if (const hipError_t e = level_args(kt, d, level, w, L); e != hipSuccess) return e;
   return with_type(level_type(kt, level), [&](auto c) {
     constexpr int KT = decltype(c)::value;
     using U = typename Key<KT>::U;
@@ -1592,7 +1745,8 @@ hipError_t launch_dist_count(int kt, const DistPlan &d, int level, const DistBuf
 }
 
 hipError_t launch_dist_scan(int kt, const DistPlan &d, int level, char *w, hipStream_t s) {
-  const Level L = level_args(kt, d, level, w);
+  Level L{};
+  if (const hipError_t e = level_args(kt, d, level, w, L); e != hipSuccess) return e;
   const int columns = level == 1 && d.levels > 1 && !d.n_segs && !d.tiled(level);
   const int summed = columns || (d.tiled(level) && level < d.levels);
   if (columns) {
@@ -1611,7 +1765,8 @@ hipError_t launch_dist_scan(int kt, const DistPlan &d, int level, char *w, hipSt
 
 hipError_t launch_dist_scatter(int kt, bool kv, const DistPlan &d, int level, const DistBufs &b,
                                char *w, hipStream_t s) {
-  const Level L = level_args(kt, d, level, w);
+  Level L{};
+  if (const hipError_t e = level_args(kt, d, level, w, L); e != hipSuccess) return e;
   const uint32_t *vsrc = level_vsrc(d, b, level);
   void *dst = level_to_out(d, level) ? b.out : b.ws;
   uint32_t *vdst = level_to_out(d, level) ? b.vout : b.vws;
@@ -1631,7 +1786,8 @@ hipError_t launch_dist_scatter(int kt, bool kv, const DistPlan &d, int level, co
 
 hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, int level, const DistBufs &b,
                                  char *w, hipStream_t s) {
-  const Level L = level_args(kt, d, level, w);
+  Level L{};
+  if (const hipError_t e = level_args(kt, d, level, w, L); e != hipSuccess) return e;
   const uint32_t *vsrc = level_vsrc(d, b, level);
   void *dst = level_to_out(d, level) ? b.out : b.ws;
   uint32_t *vdst = level_to_out(d, level) ? b.vout : b.vws;
@@ -1655,7 +1811,8 @@ hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, int level, 
 }
 
 hipError_t launch_dist_pieces(int kt, const DistPlan &d, int level, char *w, hipStream_t s) {
-  const Level L = level_args(kt, d, level, w);
+  Level L{};
+  if (const hipError_t e = level_args(kt, d, level, w, L); e != hipSuccess) return e;
   // a workgroup a bucket for one array; segments are shorter
   hipLaunchKernelGGL(dist_pieces_kernel, dim3(d.max_nodes[level], d.max_nodes[level] > 1 ? 16 : kDistSlots),
                      dim3(kPiecesThreads), 0, s, L);
@@ -1664,7 +1821,8 @@ hipError_t launch_dist_pieces(int kt, const DistPlan &d, int level, char *w, hip
 
 hipError_t launch_dist_leaves(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
                               hipStream_t s) {
-  const Level L = level_args(kt, d, d.levels, w);
+  Level L{};
+  if (const hipError_t e = level_args(kt, d, d.levels, w, L); e != hipSuccess) return e;
   const dim3 grid(d.leaf_grid);
   return with_type(kt, [&](auto c) {
     constexpr int KT = decltype(c)::value;
@@ -1694,10 +1852,10 @@ hipError_t launch_dist_rest(int kt, bool kv, const DistPlan &d, const DistBufs &
     using U = typename Key<KT>::U;
     if (kv)
       hipLaunchKernelGGL((dist_rest_kernel<KT, true, 256>), grid, dim3(256), 0, s, (U *)b.ws, b.vws,
-                         (U *)b.out, b.vout, rest, ctr, d.max_rest);
+                         (U *)b.out, b.vout, rest, ctr);
     else
       hipLaunchKernelGGL((dist_rest_kernel<KT, false, 512>), grid, dim3(512), 0, s, (U *)b.ws, b.vws,
-                         (U *)b.out, b.vout, rest, ctr, d.max_rest);
+                         (U *)b.out, b.vout, rest, ctr);
     return hipGetLastError();
   });
 }

@@ -75,6 +75,7 @@ struct DistCounters {
   // ranges of one that is
   uint32_t copies, most_ranges;
   uint32_t small[2];  // segments of the two smallest classes
+  uint32_t failed;    // a bound of the plan did not hold
 };
 
 // DistLeaf::len_flags

@@ -149,11 +149,15 @@ constexpr uint32_t kErrBracket = 2u;     // splitter search: target outside brac
 constexpr uint32_t kErrSplitRow = 4u;    // merge: split row not inside its run
 constexpr uint32_t kErrPartSize = 8u;    // merge: segments do not add up to the partition
 constexpr uint32_t kErrSegments = 16u;   // segmented sort: offsets invalid or too many passes
+constexpr uint32_t kErrPlan = 32u;       // distribution: a bound of the plan did not hold
 
 // Largest number of merge passes of one segment (n < 2^31: 2^18 tiles, 5
 // doublings per pass).
 constexpr uint32_t kMaxSegPasses = 4;
 
+// Device address of the error word, with `device` current; looked up once per
+// device (pss_create does it, so that no lookup falls into a stream capture).
+hipError_t error_word(int device, uint32_t **word);
 // Synchronous read (and optional clear) of the device error word.
 hipError_t read_device_error(uint32_t *code, bool clear);
 // Copy of the device error word into host memory (pinned, for the copy to

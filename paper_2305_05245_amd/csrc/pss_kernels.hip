@@ -15,6 +15,7 @@
 // Keys are compared only as unsigned integers after the K0 map (signed ints:
 // sign bit flipped; floats: IEEE totalOrder map), so every comparison is an
 // integer comparison and the output is bit-exact.
+#include <mutex>
 #include <type_traits>
 
 #include "pss_device.hpp"
@@ -1995,92 +1996,6 @@ __global__ __launch_bounds__(1024) void seg_plan_kernel(const uint64_t *__restri
   }
 }
 
-// Segmented distribution sort: one workgroup reads the segment offsets, checks
-// them, and lists every segment by its length: the two classes of short
-// segments, leaves (at most cap keys), first-level nodes.  Invalid offsets (not
-// starting at 0, decreasing, or ending beyond n) give empty lists and an error
-// bit; segments above `longest` (what the caller's bound on the segment length
-// allows) are left out and give it too.
-struct SegDistArgs {
-  const uint64_t *off;
-  uint32_t n_segs;
-  uint64_t n, longest;
-  uint32_t small0, small1, cap, target, rl, root_p, levels, tiled;
-  DistCounters *ctr;
-  DistNode *nodes;
-  DistRange *ranges;
-  DistLeaf *leaves;
-  uint32_t *small;  // [2][n_segs]
-  uint32_t max_nodes, max_ranges, max_cols, max_table, max_leaves;
-};
-
-__global__ __launch_bounds__(1024) void seg_dist_plan_kernel(SegDistArgs a) {
-  // two words: `bad` is read while another wave may already set `over`
-  __shared__ uint32_t bad, over;
-  __shared__ uint32_t n_small[2], n_leaves, n_nodes, n_ranges, n_cols, n_table;
-  const uint32_t tid = threadIdx.x;
-  uint32_t *c = (uint32_t *)a.ctr;
-  for (uint32_t i = tid; i < sizeof(DistCounters) / 4; i += 1024) c[i] = 0;
-  if (tid == 0) {
-    bad = (a.off[0] != 0 || a.off[a.n_segs] > a.n) ? 1u : 0u;
-    over = 0;
-    n_small[0] = n_small[1] = n_leaves = n_nodes = n_ranges = n_cols = n_table = 0;
-  }
-  __syncthreads();
-  for (uint32_t s = tid; s < a.n_segs; s += 1024)
-    if (a.off[s + 1] < a.off[s]) atomicOr(&bad, 1u);
-  __syncthreads();
-  const bool ok = bad == 0;
-  if (tid == 0 && !ok) report(kErrSegments);
-  if (!ok) return;
-  bool left_out = false;
-  for (uint32_t s = tid; s < a.n_segs; s += 1024) {
-    const uint64_t len64 = a.off[s + 1] - a.off[s];
-    const uint32_t off = (uint32_t)a.off[s], len = (uint32_t)len64;
-    if (len64 == 0) continue;
-    if (len64 > a.longest) {
-      left_out = true;
-    } else if (len <= a.small1) {
-      const int cls = len <= a.small0 ? 0 : 1;
-      a.small[(uint64_t)cls * a.n_segs + atomicAdd(&n_small[cls], 1u)] = s;
-    } else if (len <= a.cap) {
-      const uint32_t to = atomicAdd(&n_leaves, 1u);
-      if (to < a.max_leaves) a.leaves[to] = DistLeaf{off, len | kSrcIn << kLeafSrcShift, 0, 0, 0, 0, 0, 0, 0, 0};
-    } else {
-      DistNode d;
-      d.off = off;
-      d.len = len;
-      d.p = node_picks(len, a.target, (int)a.levels);
-      d.p = d.p < a.root_p ? d.p : a.root_p;
-      d.nr = (len + a.rl - 1) / a.rl;
-      d.cols = node_cols(d.p);
-      d.stride = node_stride(len, d.nr, a.tiled != 0);
-      d.nb = 0;
-      d.poff = d.plen = d.prow = d.pnext = 0;
-      const uint32_t at = atomicAdd(&n_nodes, 1u), r0 = atomicAdd(&n_ranges, d.nr);
-      d.sbase = atomicAdd(&n_cols, d.cols);
-      d.tbase = atomicAdd(&n_table, d.cols * d.stride);
-      if (at < a.max_nodes && r0 + d.nr <= a.max_ranges && d.sbase + d.cols <= a.max_cols &&
-          d.tbase + d.cols * d.stride <= a.max_table) {
-        a.nodes[at] = d;
-        for (uint32_t r = 0; r < d.nr; ++r) a.ranges[r0 + r] = DistRange{at, r};
-      }
-    }
-  }
-  if (left_out) atomicOr(&over, 1u);
-  __syncthreads();
-  if (tid == 0) {
-    if (over) report(kErrSegments);
-    a.ctr->nodes[1] = n_nodes;
-    a.ctr->ranges[1] = n_ranges;
-    a.ctr->cols[1] = n_cols;
-    a.ctr->table[1] = n_table;
-    a.ctr->leaves = n_leaves;
-    a.ctr->small[0] = n_small[0];
-    a.ctr->small[1] = n_small[1];
-  }
-}
-
 template <typename F>
 hipError_t dispatch_kt(int kt, F &&f) {
   switch (kt) {
@@ -2196,36 +2111,6 @@ hipError_t launch_seg_tile_sorts(int kt, bool kv, const void *in, const uint32_t
     return kv ? go_tile<KT, true, kTileThreads>(in, vin, ta, grid, s)
               : go_tile<KT, false, kTileThreads>(in, vin, ta, grid, s);
   });
-}
-
-hipError_t launch_dist_segments(const DistPlan &d, const uint64_t *seg_off, uint64_t n,
-                                uint32_t small0, uint32_t small1, uint64_t longest, char *w,
-                                hipStream_t s) {
-  SegDistArgs a{};
-  a.off = seg_off;
-  a.n_segs = d.n_segs;
-  a.n = n;
-  a.longest = longest;
-  a.small0 = small0;
-  a.small1 = small1;
-  a.cap = d.cap;
-  a.target = d.target;
-  a.rl = d.rl[1];
-  a.root_p = d.root_p;
-  a.levels = (uint32_t)d.levels;
-  a.tiled = d.tiled(1) ? 1u : 0u;
-  a.ctr = (DistCounters *)(w + d.off_ctr);
-  a.nodes = (DistNode *)(w + d.off_nodes[1]);
-  a.ranges = (DistRange *)(w + d.off_ranges[1]);
-  a.leaves = (DistLeaf *)(w + d.off_leaves);
-  a.small = (uint32_t *)(w + d.off_small);
-  a.max_nodes = d.max_nodes[1];
-  a.max_ranges = d.max_ranges[1];
-  a.max_cols = d.max_cols;
-  a.max_table = d.max_table[1];
-  a.max_leaves = d.max_leaves;
-  hipLaunchKernelGGL(seg_dist_plan_kernel, dim3(1), dim3(1024), 0, s, a);
-  return hipGetLastError();
 }
 
 hipError_t launch_dist_small(int kt, bool kv, const DistPlan &d, const DistBufs &b,
@@ -2525,6 +2410,25 @@ hipError_t launch_record_gather(const void *in, void *out, const uint32_t *perm,
   if (align % 8 == 0) return go(uint2{});
   if (align % 4 == 0) return go(uint32_t{});
   return hipErrorInvalidValue;
+}
+
+namespace {
+constexpr int kMaxDevices = 64;
+std::mutex g_error_mu;
+uint32_t *g_error_word[kMaxDevices] = {};
+}  // namespace
+
+hipError_t error_word(int device, uint32_t **word) {
+  if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
+  std::lock_guard<std::mutex> lk(g_error_mu);
+  if (!g_error_word[device]) {
+    void *p = nullptr;
+    const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(g_device_error));
+    if (e != hipSuccess) return e;
+    g_error_word[device] = (uint32_t *)p;
+  }
+  *word = g_error_word[device];
+  return hipSuccess;
 }
 
 hipError_t read_device_error(uint32_t *code, bool clear) {

@@ -40,6 +40,9 @@ hipError_t scratch_setup(int device) {
     g_lookup[device] = e;
     g_scratch[device] = e == hipSuccess ? p : nullptr;
     g_looked_up[device] = true;
+    // likewise the address of the error word, for the kernels that are given it
+    uint32_t *word = nullptr;
+    (void)error_word(device, &word);
   }
   return g_lookup[device];
 }

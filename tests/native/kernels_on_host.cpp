@@ -8,6 +8,7 @@
 #include <random>
 #include <string>
 
+#include "../../paper_2305_05245_amd/csrc/pss_dist.hpp"
 #include "pss.h"
 
 namespace {
@@ -90,13 +91,79 @@ void segment_left_out() {
   }
 }
 
+// One distribution sort of uint64 keys by the launches of plan d (whose arrays
+// end at byte `bytes` of the workspace, after keys and values); true if the
+// output is sorted.
+bool distribution(const pss::DistPlan &d, size_t bytes, uint64_t n, bool kv, uint64_t distinct) {
+  std::vector<uint64_t> keys(n), out(n);
+  std::vector<uint32_t> vals(n), vout(n);
+  for (uint64_t i = 0; i < n; ++i) {
+    keys[i] = distinct ? rng() % distinct * 0x9E3779B97F4A7C15ull : rng();
+    vals[i] = (uint32_t)i;
+  }
+  Buffer ws(bytes), kws(n * 8), vws(n * 4);
+  const pss::DistBufs b{keys.data(), vals.data(), kws.p, (uint32_t *)vws.p, out.data(), vout.data()};
+  const int kt = PSS_U64;
+  for (int l = 1; l <= d.levels; ++l) {
+    CHECK(pss::launch_dist_sample(kt, d, l, b, n, ws.p, nullptr) == hipSuccess, "sample");
+    if (!d.tiled(l)) {
+      CHECK(pss::launch_dist_count(kt, d, l, b, ws.p, nullptr) == hipSuccess, "count");
+      CHECK(pss::launch_dist_scan(kt, d, l, ws.p, nullptr) == hipSuccess, "scan");
+      CHECK(pss::launch_dist_scatter(kt, kv, d, l, b, ws.p, nullptr) == hipSuccess, "scatter");
+    } else {
+      CHECK(pss::launch_dist_partition(kt, kv, d, l, b, ws.p, nullptr) == hipSuccess, "partition");
+      if (l < d.levels) CHECK(pss::launch_dist_pieces(kt, d, l, ws.p, nullptr) == hipSuccess, "pieces");
+      CHECK(pss::launch_dist_scan(kt, d, l, ws.p, nullptr) == hipSuccess, "scan");
+    }
+  }
+  CHECK(pss::launch_dist_leaves(kt, kv, d, b, ws.p, nullptr) == hipSuccess, "leaves");
+  CHECK(pss::launch_dist_rest(kt, kv, d, b, ws.p, nullptr) == hipSuccess, "rest");
+  std::vector<uint32_t> at(vals);
+  std::stable_sort(at.begin(), at.end(), [&](uint32_t x, uint32_t y) { return keys[x] < keys[y]; });
+  for (uint64_t i = 0; i < n; ++i)
+    if (out[i] != keys[at[i]] || (kv && vout[i] != at[i])) return false;
+  return true;
+}
+
+// A plan with too little room for its buckets: nothing is written past its
+// arrays, and the error word says so.
+void plan_bounds() {
+  const uint64_t n = 150001;
+  for (int shape = 0; shape < 3; ++shape)  // one level, two that scatter, two that gather
+    for (bool kv : {false, true}) {
+      const uint64_t len = shape == 0 ? n : shape == 1 ? 1 << 22 : 1 << 25;
+      pss::DistPlan d = pss::dist_plan(n, len, 0, 8, kv, 0, shape == 2);
+      CHECK(d.levels == (shape == 0 ? 1 : 2) && d.gather == (shape == 2), "shape %d", shape);
+      if (shape) d.root_p = 6;  // (keys for a second level)
+      const size_t bytes = d.end;
+      CHECK(distribution(d, bytes, n, kv, 0) && device_error() == 0, "shape %d as planned", shape);
+      // (few values: buckets of the first level that are not cut again)
+      CHECK(distribution(d, bytes, n, kv, 3) && device_error() == 0, "shape %d, three values", shape);
+      auto lowered = [&](const char *what, uint64_t distinct, auto change) {
+        pss::DistPlan low = d;
+        change(low);
+        (void)distribution(low, bytes, n, kv, distinct);
+        CHECK(device_error() == 32, "shape %d, %s, %s", shape, kv ? "values" : "keys", what);
+      };
+      lowered("leaves", 0, [](pss::DistPlan &p) { p.max_leaves = 3; });
+      if (shape == 0) lowered("rest", 0, [](pss::DistPlan &p) { p.root_p = 2, p.max_rest = 0; });
+      if (shape == 0) continue;
+      lowered("nodes", 0, [](pss::DistPlan &p) { p.max_nodes[2] = 2; });
+      lowered("columns", 0, [](pss::DistPlan &p) { p.max_cols = 13; });
+      lowered("table", 0, [](pss::DistPlan &p) { p.max_table[2] = 100; });
+      if (shape == 1) lowered("ranges", 0, [](pss::DistPlan &p) { p.max_ranges[2] = 2; });
+      if (shape == 2 && kv) lowered("copies", 3, [](pss::DistPlan &p) { p.max_copies = 1; });
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
   const std::string name = argc > 1 ? argv[1] : "";
   emu::seed = argc > 2 ? (uint32_t)std::atoi(argv[2]) : 0;
   if (pss_create(0, &ctx) != PSS_OK) return 2;
-  const struct { const char *name; void (*run)(); } cases[] = {{"segment_left_out", segment_left_out}};
+  const struct { const char *name; void (*run)(); } cases[] = {
+      {"segment_left_out", segment_left_out}, {"plan_bounds", plan_bounds}};
   bool found = false;
   for (const auto &c : cases) {
     if (name != c.name) continue;

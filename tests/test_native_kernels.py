@@ -57,3 +57,8 @@ def run(program, case, seed):
 @pytest.mark.parametrize("seed", [0, 1, 2, 3])
 def test_segment_left_out(program, seed):
     run(program, "segment_left_out", seed)
+
+
+@pytest.mark.parametrize("seed", [0, 1])
+def test_plan_bounds(program, seed):
+    run(program, "plan_bounds", seed)

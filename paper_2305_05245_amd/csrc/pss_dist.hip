@@ -15,7 +15,7 @@
 //              left, for which "pieces" counts the keys before every 8 tiles
 //   scan       where the buckets start; they become leaves (fit one workgroup,
 //              or hold one key value only), nodes of the next level, or - if the
-//              last level left one too large - entries of the rest list
+//              last level left one too large - big buckets
 //
 // and a leaf is sorted by one workgroup, which gathers it from its piece of
 // every tile of the node.  The last two levels leave their tiles in place;
@@ -29,7 +29,7 @@
 // Samples are taken at hashed positions, so the order of the input does not
 // matter, and any distribution of keys gives buckets of about the same size.
 // Nothing depends on the sizes being met: a bucket left too large is sorted by
-// merging through memory.
+// all workgroups together, merging through memory.
 //
 // At 2^28 int64 uniform keys (ms): samples 0.21, first partition 0.86, gathered
 // partition 1.24, leaves 1.50; the sort 3.85.  With a count (0.44) and a
@@ -62,10 +62,11 @@ struct Level {
   void *table;
   DistLeaf *leaves;
   uint64_t *rest;  // offset | length << 32, mapped keys in the output
+  DistBig *big;
   uint32_t level, levels, cap, target, rl, next_rl;
   uint32_t src;  // kSrc* of this level's leaves
   uint32_t node_tiles;  // most tiles of a last-level node
-  uint32_t max_next_nodes, max_next_ranges, max_cols, max_next_table, max_leaves, max_rest;
+  uint32_t max_next_nodes, max_next_ranges, max_cols, max_next_table, max_leaves, max_rest, max_big;
   uint32_t root_len, root_p;  // level 1 of a single array (0: nodes are given)
   uint32_t tiled, next_tiled;  // its tiles are left in place
   uint32_t gather;  // its keys are gathered from the tiles of the level before
@@ -623,7 +624,7 @@ __global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summ
   const uint32_t ns = nd.nb - 1;
   const bool next_last = L.level + 1 == L.levels;
   bool equal = false;  // the bucket can hold one key value only
-  bool node = false, rest = false, copy = false, known = false;
+  bool node = false, big = false, copy = false, known = false;
   uint32_t pieces = 0;
   U lo = 0, hi = 0;
   if (b < nd.nb && len) {
@@ -633,9 +634,9 @@ __global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summ
     equal = b < ns ? hi - lo == 1 : lo == key_max<U>();
     const bool fits = len <= L.cap;
     node = !last && !equal && !fits && !(next_last && len > L.node_tiles * kDistTile);
-    rest = !equal && !fits && !node;
-    // (after a scatter a rest entry already lies in the output)
-    pieces = node || (rest && !L.tiled) ? 0u : (len + L.cap - 1) / L.cap;
+    big = !equal && !fits && !node;
+    // (after a scatter a big bucket already lies in the output)
+    pieces = node || (big && !L.tiled) ? 0u : (len + L.cap - 1) / L.cap;
     // in place before the last level: the last level's workgroups bring it to
     // its place in the workspace (keys of one value need not be read)
     known = equal && !L.kv;
@@ -652,16 +653,16 @@ __global__ __launch_bounds__(kDistSlots) void dist_scan_kernel(Level L, int summ
       const uint32_t row = nd.tbase + b * nd.stride;
       L.leaves[to] = DistLeaf{off + o,
                               l | (copy ? kSrcWs : L.tiled ? kSrcPieces : L.src) << kLeafSrcShift | (equal ? kLeafEqual : 0u) |
-                                  (rest ? kLeafMove : 0u) | (b > 0 && b < ns ? kLeafInner : 0u),
+                                  (big ? kLeafMove : 0u) | (b > 0 && b < ns ? kLeafInner : 0u),
                               nd.off, nd.len, o, row, b < ns ? row + nd.stride : ~0u, 0u, (uint64_t)lo,
                               (uint64_t)hi};
     } else {
       plan_failed(L.ctr, L.err);
     }
   }
-  if (rest) {
-    const uint32_t to = atomicAdd(&L.ctr->rest, 1u);
-    if (to < L.max_rest) L.rest[to] = (uint64_t)off | (uint64_t)len << 32;
+  if (big) {
+    const uint32_t to = atomicAdd(&L.ctr->big, 1u);
+    if (to < L.max_big) L.big[to] = DistBig{off, len, 0u, 0u};
     else plan_failed(L.ctr, L.err);
   }
   if (node) {
@@ -1496,95 +1497,170 @@ __global__ __launch_bounds__(NT, WAVES) void dist_leaf_kernel(
 }
 
 // ----------------------------------------------------------------- rest ---
+// Sorts m mapped keys (and values) from a to b, which may be the same; unmapped
+// if they are final.  The tile sort's network and merge rounds.
+template <int KT, bool KV, int NT>
+__device__ __forceinline__ void sort_tile(const typename Key<KT>::U *a, const uint32_t *va,
+                                          typename Key<KT>::U *b, uint32_t *vb, uint32_t m, bool final,
+                                          typename Key<KT>::U *sk, uint32_t *sv) {
+  using U = typename Key<KT>::U;
+  constexpr uint32_t CAP = NT * kTileItems;
+  const uint32_t tid = threadIdx.x;
+  U k[kTileItems];
+  uint32_t v[kTileItems];
+  __syncthreads();  // the tile before is read no more
+  if constexpr (KV) {
+    for (uint32_t i = tid; i < CAP; i += NT) {
+      sk[pad16(i)] = i < m ? a[i] : key_max<U>();
+      sv[pad16(i)] = i < m ? va[i] : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kTileItems; ++i) {
+      k[i] = sk[pad16(tid * kTileItems + i)];
+      v[i] = sv[pad16(tid * kTileItems + i)];
+    }
+    lds_sort_pairs<U, NT>(k, v, sk, sv);
+  } else {
+#pragma unroll
+    for (int i = 0; i < kTileItems; ++i) {
+      const uint32_t idx = i * NT + tid;
+      const U x = a[idx < m ? idx : m - 1];
+      k[i] = idx < m ? x : key_max<U>();
+    }
+    lds_sort_keys<U, NT>(k, sk);
+  }
+  for (uint32_t i = tid; i < m; i += NT) {
+    b[i] = final ? Key<KT>::unmap(sk[i]) : sk[i];
+    if constexpr (KV) vb[i] = sv[i];
+  }
+}
+
+// How many of the first d keys of the merge of a[0, la) and b[0, lb) (ties to a)
+// come from a; by one wave, 64 candidates at a time.
+template <typename U>
+__device__ __forceinline__ uint32_t wave_merge_path(const U *a, uint32_t la, const U *b, uint32_t lb,
+                                                    uint32_t d) {
+  const uint32_t lane = threadIdx.x & 63;
+  uint32_t lo = d > lb ? d - lb : 0, hi = d < la ? d : la;
+  while (lo < hi) {
+    const uint32_t step = (hi - lo + 63) / 64, x = lo + lane * step;
+    const uint32_t y = x < hi ? x : lo;
+    // (true for a prefix of the candidates)
+    const uint32_t c = (uint32_t)__popcll(__ballot(x < hi && a[y] <= b[d - 1 - y]));
+    hi = lo + c * step < hi ? lo + c * step : hi;
+    lo = c ? lo + (c - 1) * step + 1 : hi;
+  }
+  return lo;
+}
+
 // What the leaf kernel left, as mapped keys at their place in the output:
-// leaves with a crowded bin, which go through the tile sort's network and merge
-// rounds, and buckets the last level left larger than CAP, which one workgroup
-// sorts tile by tile and merges pairwise between the output and the workspace.
-// The latter are rare (see kDistTarget), so their loop is short rather than
-// fast.
+// leaves with a crowded bin, which are sorted like tiles, and big buckets, above
+// the cap.
+//
+// Big buckets come from samples that missed much of a node: about one bucket of
+// ten thousand by chance, and then of two tiles, but the sampled positions can
+// be computed, and an input that holds one key there has its whole array in
+// two.  So their sorts are tasks that all workgroups share (1500000 uint64 keys
+// of that kind: 521 us, by one workgroup a bucket 14611; random ones 92).  A bucket of T tiles has T tile sorts and
+// then, for every doubling of the sorted runs, T merges of one tile's length,
+// between the output and the workspace.  Workgroups claim the tasks of all
+// buckets in one order, round by round, and a task waits until the rounds before
+// its own have ended: every task it waits for has a lower number, so some
+// workgroup already works on it, and the lowest unfinished task never waits.
+// (One thread's fences stand for the workgroup, between its barriers: fences of
+// all waves write back and invalidate the L2 each, 1397 us.)
 template <int KT, bool KV, int NT>
 __global__ __launch_bounds__(NT) void dist_rest_kernel(typename Key<KT>::U *ws, uint32_t *vws,
                                                        typename Key<KT>::U *out, uint32_t *vout,
                                                        const uint64_t *__restrict__ rest,
-                                                       const DistCounters *__restrict__ ctr) {
+                                                       DistBig *big, DistCounters *ctr) {
   using U = typename Key<KT>::U;
   using T = TileLds<KV, NT>;
   constexpr uint32_t CAP = NT * kTileItems;
   __shared__ U sk[T::SLOTS];
   __shared__ uint32_t sv[KV ? T::SLOTS : 1];
+  __shared__ uint32_t claimed, path[2];
   const uint32_t tid = threadIdx.x;
-  const uint32_t no = ctr->rest;
+  const uint32_t no = ctr->rest, nbig = ctr->big;
   if (ctr->failed) return;
   for (uint32_t oi = blockIdx.x; oi < no; oi += gridDim.x) {
     const uint32_t off = (uint32_t)rest[oi], len = (uint32_t)(rest[oi] >> 32);
-    const bool one = len <= CAP;
-    U *a = out + off, *c = ws + off;
-    uint32_t *va = KV ? vout + off : nullptr, *vc = KV ? vws + off : nullptr;
-    for (uint32_t base = 0; base < len; base += CAP) {
-      const uint32_t m = len - base < CAP ? len - base : CAP;
-      U k[kTileItems];
-      uint32_t v[kTileItems];
-      __syncthreads();
-      if constexpr (KV) {
-        for (uint32_t i = tid; i < CAP; i += NT) {
-          sk[pad16(i)] = i < m ? a[base + i] : key_max<U>();
-          sv[pad16(i)] = i < m ? va[base + i] : 0u;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kTileItems; ++i) {
-          k[i] = sk[pad16(tid * kTileItems + i)];
-          v[i] = sv[pad16(tid * kTileItems + i)];
-        }
-        lds_sort_pairs<U, NT>(k, v, sk, sv);
-      } else {
-#pragma unroll
-        for (int i = 0; i < kTileItems; ++i) {
-          const uint32_t idx = i * NT + tid;
-          const U x = a[base + (idx < m ? idx : m - 1)];
-          k[i] = idx < m ? x : key_max<U>();
-        }
-        lds_sort_keys<U, NT>(k, sk);
-      }
-      for (uint32_t i = tid; i < m; i += NT) {
-        a[base + i] = one ? Key<KT>::unmap(sk[i]) : sk[i];
-        if constexpr (KV) va[base + i] = sv[i];
-      }
+    sort_tile<KT, KV, NT>(out + off, KV ? vout + off : nullptr, out + off, KV ? vout + off : nullptr, len,
+                          true, sk, sv);
+  }
+  uint32_t e = 0, base = 0;  // a bucket, and its first task
+  while (e < nbig) {
+    __syncthreads();
+    if (tid == 0) claimed = atomicAdd(&ctr->next_task, 1u);
+    __syncthreads();
+    const uint32_t task = claimed;
+    uint32_t off, len, tiles, rounds;
+    for (;;) {
+      off = big[e].off;
+      len = big[e].len;
+      tiles = (len + CAP - 1) / CAP;
+      rounds = 32 - __clz(tiles - 1);
+      if (task < base + tiles * (1 + rounds)) break;
+      base += tiles * (1 + rounds);
+      if (++e == nbig) return;
     }
-    if (one) continue;
-    for (uint32_t w = CAP; w < len; w *= 2) {  // (len < 2^31)
+    const uint32_t r = (task - base) / tiles, o = (task - base) % tiles * CAP;
+    const uint32_t m = len - o < CAP ? len - o : CAP;
+    // round r leaves its runs in the output if the number of rounds to come is even
+    const bool here = ((rounds - r) & 1) == 0;
+    U *dst = (here ? out : ws) + off;
+    uint32_t *vdst = KV ? (here ? vout : vws) + off : nullptr;
+    if (r == 0) {
+      sort_tile<KT, KV, NT>(out + off + o, KV ? vout + off + o : nullptr, dst + o, KV ? vdst + o : nullptr, m,
+                            false, sk, sv);
+    } else {
+      const U *src = (here ? ws : out) + off;
+      const uint32_t *vsrc = KV ? (here ? vws : vout) + off : nullptr;
+      if (tid == 0) {
+        while (__hip_atomic_load(&big[e].done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < tiles * r)
+          __builtin_amdgcn_s_sleep(8);
+        __threadfence();
+      }
       __syncthreads();
-      for (uint32_t t = tid * kTileItems; t < len; t += CAP) {
-        // outputs t .. t+15 of this width's pairs (which start at multiples of 16)
-        const uint32_t a0 = t / (2 * w) * (2 * w);
-        const uint32_t a1 = len - a0 < w ? len : a0 + w;
-        const uint32_t b1 = len - a1 < w ? len : a1 + w;
-        const uint32_t d = t - a0, la = a1 - a0, lb = b1 - a1;
-        uint32_t lo = d > lb ? d - lb : 0, hi = d < la ? d : la;
-        while (lo < hi) {
-          const uint32_t mid = (lo + hi) >> 1;
-          if (a[a0 + mid] <= a[a1 + d - 1 - mid]) lo = mid + 1;
-          else hi = mid;
-        }
-        uint32_t pa = a0 + lo, pb = a1 + (d - lo);
-        for (uint32_t o = t; o < t + kTileItems && o < b1; ++o) {
-          const bool left = pa < a1 && (pb >= b1 || a[pa] <= a[pb]);
-          const uint32_t from = left ? pa++ : pb++;
-          c[o] = a[from];
-          if constexpr (KV) vc[o] = va[from];
+      // outputs o .. o+m-1 of the runs' pairs (whose lengths are whole tiles)
+      const uint32_t w = CAP << (r - 1), a0 = o / (2 * w) * (2 * w);
+      const uint32_t la = len - a0 < w ? len - a0 : w, b0 = a0 + la;
+      const uint32_t lb = len - b0 < w ? len - b0 : w;
+      if (tid < 128) {  // (two waves)
+        const uint32_t p = wave_merge_path(src + a0, la, src + b0, lb, o - a0 + (tid < 64 ? 0u : m));
+        if ((tid & 63) == 0) path[tid >> 6] = p;
+      }
+      __syncthreads();
+      const uint32_t pa = path[0], na = path[1] - pa, pb = o - a0 - pa;
+      for (uint32_t i = tid; i < m; i += NT) {
+        const uint32_t from = i < na ? a0 + pa + i : b0 + pb + (i - na);
+        sk[i] = src[from];
+        if constexpr (KV) sv[i] = vsrc[from];
+      }
+      __syncthreads();
+      U k[kTileItems];
+      uint32_t v[KV ? kTileItems : 1];
+      const uint32_t at = tid * kTileItems;
+      if (at < m) merge_chunk<U, KV, kTileItems, false>(sk, sv, 0u, na, m, at, k, v);
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < kTileItems; ++i) {
+        if (at + i < m) {
+          sk[at + i] = k[i];
+          if constexpr (KV) sv[at + i] = v[i];
         }
       }
-      U *x = a;
-      a = c;
-      c = x;
-      uint32_t *y = va;
-      va = vc;
-      vc = y;
+      __syncthreads();
+      for (uint32_t i = tid; i < m; i += NT) {
+        dst[o + i] = r == rounds ? Key<KT>::unmap(sk[i]) : sk[i];
+        if constexpr (KV) vdst[o + i] = sv[i];
+      }
     }
     __syncthreads();
-    for (uint32_t i = tid; i < len; i += NT) {
-      out[off + i] = Key<KT>::unmap(a[i]);
-      if constexpr (KV) vout[off + i] = va[i];
+    if (tid == 0) {
+      __threadfence();
+      atomicAdd(&big[e].done, 1u);
     }
   }
 }
@@ -1625,6 +1701,7 @@ hipError_t level_args(int kt, const DistPlan &d, int level, char *w, Level &L) {
   L.max_copies = d.max_copies;
   L.leaves = (DistLeaf *)(w + d.off_leaves);
   L.rest = (uint64_t *)(w + d.off_rest);
+  L.big = (DistBig *)(w + d.off_big);
   L.level = (uint32_t)level;
   L.levels = (uint32_t)d.levels;
   L.cap = d.cap;
@@ -1635,6 +1712,7 @@ hipError_t level_args(int kt, const DistPlan &d, int level, char *w, Level &L) {
   L.max_cols = d.max_cols;
   L.max_leaves = d.max_leaves;
   L.max_rest = d.max_rest;
+  L.max_big = d.max_big;
   if (level < d.levels) {
     L.next_nodes = (DistNode *)(w + d.off_nodes[level + 1]);
     L.next_ranges = (DistRange *)(w + d.off_ranges[level + 1]);
@@ -1843,8 +1921,9 @@ hipError_t launch_dist_leaves(int kt, bool kv, const DistPlan &d, const DistBufs
 
 hipError_t launch_dist_rest(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
                             hipStream_t s) {
-  const DistCounters *ctr = (const DistCounters *)(w + d.off_ctr);
+  DistCounters *ctr = (DistCounters *)(w + d.off_ctr);
   const uint64_t *rest = (const uint64_t *)(w + d.off_rest);
+  DistBig *big = (DistBig *)(w + d.off_big);
   // workgroups loop over the list: usually nearly empty
   const dim3 grid(std::min<uint32_t>(d.max_rest, 768));
   return with_type(kt, [&](auto c) {
@@ -1852,10 +1931,10 @@ hipError_t launch_dist_rest(int kt, bool kv, const DistPlan &d, const DistBufs &
     using U = typename Key<KT>::U;
     if (kv)
       hipLaunchKernelGGL((dist_rest_kernel<KT, true, 256>), grid, dim3(256), 0, s, (U *)b.ws, b.vws,
-                         (U *)b.out, b.vout, rest, ctr);
+                         (U *)b.out, b.vout, rest, big, ctr);
     else
       hipLaunchKernelGGL((dist_rest_kernel<KT, false, 512>), grid, dim3(512), 0, s, (U *)b.ws, b.vws,
-                         (U *)b.out, b.vout, rest, ctr);
+                         (U *)b.out, b.vout, rest, big, ctr);
     return hipGetLastError();
   });
 }

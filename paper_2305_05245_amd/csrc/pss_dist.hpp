@@ -67,10 +67,17 @@ struct DistLeaf {
   uint32_t pad;
   uint64_t below, above;  // kLeafInner: below <= key < above
 };
+// A bucket the last level left above the cap, moved to its place in the output.
+struct DistBig {
+  uint32_t off, len;
+  uint32_t done;  // tasks of its sort that have ended
+  uint32_t pad;
+};
 struct DistCounters {
   uint32_t nodes[kDistMaxLevels + 1], ranges[kDistMaxLevels + 1];
   uint32_t cols[kDistMaxLevels + 1], table[kDistMaxLevels + 1];
-  uint32_t leaves, rest;
+  uint32_t leaves, rest, big;
+  uint32_t next_task;  // of the big buckets' sorts
   // gathered: buckets of the level before that are not cut again, and the most
   // ranges of one that is
   uint32_t copies, most_ranges;
@@ -81,7 +88,7 @@ struct DistCounters {
 // DistLeaf::len_flags
 constexpr uint32_t kLeafLenMask = 0xffffu;
 constexpr uint32_t kLeafEqual = 1u << 16;  // one key value: unmapped, not sorted
-constexpr uint32_t kLeafMove = 1u << 17;   // part of a rest entry: moved to the output
+constexpr uint32_t kLeafMove = 1u << 17;   // part of a big bucket: moved to the output
 constexpr uint32_t kLeafInner = 1u << 18;  // the splitters around it bound its keys
 constexpr int kLeafSrcShift = 19;          // where its keys are:
 constexpr uint32_t kSrcWs = 0, kSrcOut = 1, kSrcPieces = 2, kSrcIn = 3;  // (kSrcIn: not mapped)
@@ -100,12 +107,12 @@ struct DistPlan {
   bool tiled(int level) const { return level == levels || (gather && level == levels - 1); }
   uint32_t rl[kDistMaxLevels + 1] = {};  // keys of a range (whole tiles)
   uint32_t max_nodes[kDistMaxLevels + 1] = {}, max_ranges[kDistMaxLevels + 1] = {};
-  uint32_t max_cols = 0, max_table[kDistMaxLevels + 1] = {}, max_leaves = 0, max_rest = 0;
+  uint32_t max_cols = 0, max_table[kDistMaxLevels + 1] = {}, max_leaves = 0, max_rest = 0, max_big = 0;
   uint32_t max_copies = 0;
   uint32_t leaf_grid = 0;  // workgroups of the leaf kernel: the leaves to expect
   size_t off_ctr = 0, off_nodes[kDistMaxLevels + 1] = {}, off_ranges[kDistMaxLevels + 1] = {};
   size_t off_ptable = 0, off_pre = 0;  // gathered: the level before's table, keys before every 8 tiles
-  size_t off_spl = 0, off_start = 0, off_table = 0, off_leaves = 0, off_rest = 0, off_small = 0;
+  size_t off_spl = 0, off_start = 0, off_table = 0, off_leaves = 0, off_rest = 0, off_big = 0, off_small = 0;
   size_t end = 0;  // first byte after the distribution's arrays
 };
 
@@ -171,7 +178,8 @@ inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb,
   d.max_leaves = (uint32_t)(leaves + n / d.cap + 1);
   const uint64_t expect = n / d.target + n / d.target / 8 + d.max_nodes[d.levels] + n_segs + 64;
   d.leaf_grid = (uint32_t)((std::min<uint64_t>(d.max_leaves, expect) + 7) / 8 * 8);
-  d.max_rest = d.max_leaves;  // every leaf, or buckets above cap (fewer)
+  d.max_rest = d.max_leaves;
+  d.max_big = (uint32_t)(n / d.cap);
   auto take = [&](size_t bytes) {
     const size_t o = off;
     off += (bytes + 255) / 256 * 256;
@@ -189,6 +197,7 @@ inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb,
   d.off_pre = take((size_t)ptable_bytes / 4);  // a uint32 for every 8 entries
   d.off_leaves = take((size_t)d.max_leaves * sizeof(DistLeaf));
   d.off_rest = take((size_t)d.max_rest * 8);
+  d.off_big = take((size_t)d.max_big * sizeof(DistBig));
   d.off_small = take((size_t)n_segs * 8);
   d.end = off;
   return d;

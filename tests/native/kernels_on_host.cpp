@@ -146,7 +146,8 @@ void plan_bounds() {
         CHECK(device_error() == 32, "shape %d, %s, %s", shape, kv ? "values" : "keys", what);
       };
       lowered("leaves", 0, [](pss::DistPlan &p) { p.max_leaves = 3; });
-      if (shape == 0) lowered("rest", 0, [](pss::DistPlan &p) { p.root_p = 2, p.max_rest = 0; });
+      if (shape == 0) lowered("big buckets", 0, [](pss::DistPlan &p) { p.root_p = 2, p.max_big = 1; });
+      if (shape == 0) lowered("crowded leaves", 2000, [](pss::DistPlan &p) { p.max_rest = 1; });
       if (shape == 0) continue;
       lowered("nodes", 0, [](pss::DistPlan &p) { p.max_nodes[2] = 2; });
       lowered("columns", 0, [](pss::DistPlan &p) { p.max_cols = 13; });
@@ -156,6 +157,21 @@ void plan_bounds() {
     }
 }
 
+// Buckets far above the cap: of two tiles to all of the array, with lengths at
+// the edges of tiles and of pairs of runs.
+void big_buckets() {
+  for (uint64_t n : {30001, 65536, 65537, 81921, 150001})
+    for (bool kv : {false, true})
+      for (uint64_t distinct : {0, 300, 20000}) {
+        pss::DistPlan d = pss::dist_plan(n, n, 0, 8, kv, 0, false);
+        d.root_p = 2;
+        const size_t bytes = d.end;
+        CHECK(distribution(d, bytes, n, kv, distinct), "%llu keys, %s, %llu values", (unsigned long long)n,
+              kv ? "values" : "keys", (unsigned long long)distinct);
+        CHECK(device_error() == 0, "device error word");
+      }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -163,7 +179,7 @@ int main(int argc, char **argv) {
   emu::seed = argc > 2 ? (uint32_t)std::atoi(argv[2]) : 0;
   if (pss_create(0, &ctx) != PSS_OK) return 2;
   const struct { const char *name; void (*run)(); } cases[] = {
-      {"segment_left_out", segment_left_out}, {"plan_bounds", plan_bounds}};
+      {"segment_left_out", segment_left_out}, {"plan_bounds", plan_bounds}, {"big_buckets", big_buckets}};
   bool found = false;
   for (const auto &c : cases) {
     if (name != c.name) continue;

@@ -62,3 +62,8 @@ def test_segment_left_out(program, seed):
 @pytest.mark.parametrize("seed", [0, 1])
 def test_plan_bounds(program, seed):
     run(program, "plan_bounds", seed)
+
+
+@pytest.mark.parametrize("seed", [0, 1, 2])
+def test_big_buckets(program, seed):
+    run(program, "big_buckets", seed)

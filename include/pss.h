@@ -260,10 +260,13 @@ pss_status pss_sort_records(pss_ctx *ctx, pss_key_t key, const void *records_in,
  * segment), all segments in one fixed sequence of launches with no host round
  * trip, so the sequence can be captured once into a hipGraph and replayed.
  * The segments' shapes are read on the device: a planning kernel classifies
- * every segment (one small tile, or tiles of 8192 keys (4096 with values) plus
- * merge passes of fan-in 32 or 64 with exact splitting, the paper's steps 2-4
- * applied per segment),
- * and every later kernel finds its segment through the plan's prefix tables.
+ * every segment (one small tile; tiles of 8192 keys (4096 with values) plus a
+ * merge pass of fan-in 32 or 64 with exact splitting, the paper's steps 2-4
+ * applied per segment; or, above one pass's worth and 2^18 keys, buckets cut by
+ * sampled splitters as in pss_sort), and every later kernel finds its segment
+ * through the plan's tables.  Without a bound on the length (tuning->max_seg_len
+ * = 0), batches whose mean segment (n / n_segs) is at most that long take as many
+ * merge passes as n keys need instead.
  *
  *   seg_offsets: DEVICE array of n_segs + 1 uint64, seg_offsets[0] = 0,
  *     non-decreasing, seg_offsets[n_segs] <= n (keys past the last offset are
@@ -271,8 +274,8 @@ pss_status pss_sort_records(pss_ctx *ctx, pss_key_t key, const void *records_in,
  *     unused trailing segments empty).  Invalid offsets leave the output
  *     unspecified and set bit 16 of the device error word (pss_device_check).
  *   tuning (host, may be NULL = defaults): which segments go to the smaller
- *     tile sorts, and a bound on the longest segment that bounds the number
- *     of merge passes launched.  Chosen by the project's autotuner per
+ *     tile sorts, the runs of a merge pass, and a bound on the longest segment,
+ *     which decides what is launched.  Chosen by the project's autotuner per
  *     workload; any valid tuning gives the same output.
  *   Other arguments as pss_sort (n keys in total, out of place, caller-owned
  *   workspace of pss_segmented_workspace_bytes bytes).
@@ -282,8 +285,9 @@ typedef struct {
   uint32_t small_max_4k; /* segments with <= this many keys: 4096-key tiles, 256 threads (<= 4096) */
   uint64_t max_seg_len;  /* upper bound on any segment's length; 0 = n */
   uint32_t fan_log2;     /* runs merged per pass, as a power of two: 5 (32 runs) or 6 (64 runs,
-                            fewer passes for segments of 33-64 tiles and 1025-4096 tiles, each
-                            pass with one more merge round); 0 = 5 */
+                            one merge round more); 0 = 5.  Segments of more tiles than one
+                            pass's runs, or of more than 2^18 keys, are not merged but cut
+                            into buckets (see above) */
   uint32_t reserved;     /* 0 */
 } pss_tuning;
 

@@ -131,10 +131,10 @@ struct Plan {
 
 // The distribution plan whose arrays fit between `off` and `total`, gathered
 // if they do.
-pss::DistPlan plan_dist(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb, bool kv, size_t off,
-                        size_t total) {
-  pss::DistPlan d = pss::dist_plan(n, max_len, n_segs, kb, kv, off, true);
-  if (d.end > total) d = pss::dist_plan(n, max_len, n_segs, kb, kv, off, false);
+pss::DistPlan plan_dist(uint64_t n, uint64_t max_len, uint32_t n_segs, uint64_t min_len, int kb, bool kv,
+                        size_t off, size_t total) {
+  pss::DistPlan d = pss::dist_plan(n, max_len, n_segs, min_len, kb, kv, off, true);
+  if (d.end > total) d = pss::dist_plan(n, max_len, n_segs, min_len, kb, kv, off, false);
   d.on = d.end <= total;
   return d;
 }
@@ -235,7 +235,7 @@ pss_status make_plan(pss_key_t key, pss_val_t val, uint64_t n, uint32_t n_blocks
   }
   p->total = off;
   if (!p->paper && n >= dist_min_keys(key) && pss::launch_dist_sample) {
-    p->dist = plan_dist(n, n, 0, p->kb, p->kv, p->off_table, p->total);
+    p->dist = plan_dist(n, n, 0, 0, p->kb, p->kv, p->off_table, p->total);
   }
   return PSS_OK;
 }
@@ -1020,11 +1020,24 @@ struct SegPlan {
   uint64_t ns = 0;                  // bound on samples
   size_t off_keys = 0, off_vals = 0, off_plan = 0, off_samples = 0, off_skeys = 0;
   size_t off_sruns = 0, off_table = 0, off_stable = 0, off_prefix = 0, total = 0;
-  // segments above one tile: the distribution sort, whose arrays take the
-  // place of the merge passes' tables (used when they fit there)
+  // Segments of at most `merged` keys are sorted by tiles and merge passes (one,
+  // if there is a distribution sort); longer ones by the distribution sort, whose
+  // arrays then take the place of the merge pass's tables.  Segments above
+  // `longest` (what the merge passes of the bound would reach) are left out and
+  // reported.
+  uint32_t merge_passes = 0;
+  uint64_t merged = 0, longest = 0;
   pss::DistPlan dist;
-  uint64_t longest = 0;  // longest segment the merge passes reach
 };
+
+// Longest segment merged: one pass's worth, and at most this many keys.  Its time
+// does not depend on the keys, and up to here one pass costs less than
+// distributing crowded leaves does, more than distributing random keys (16
+// million keys in segments of 100003, us merged / distributed: int64 289 / 194, of
+// 1000 values 289 / 378; uint64 with values 470 / 270 and 470 / 565).  A second
+// pass costs more than either (segments of 300007: 450 / 198 and 450 / 375, 634 /
+// 284 and 634 / 551).
+constexpr uint64_t kMaxMerged = (uint64_t)1 << 18;
 
 uint32_t passes_for(uint64_t L, uint32_t fan_log2, uint32_t tile) {
   if (L <= (uint64_t)tile) return 0;
@@ -1111,14 +1124,26 @@ pss_status make_seg_plan(const pss_ctx *ctx, pss_key_t key, pss_val_t val, uint6
   }
   sp->total = off;
   sp->longest = std::min<uint64_t>((uint64_t)sp->tile << (f * sp->max_passes), n);
-  if (sp->max_passes && pss::launch_dist_segments) {
-    sp->dist = plan_dist(n, max_len, n_segs, kb, kv, sp->off_plan, sp->total);
+  sp->merge_passes = std::min<uint32_t>(sp->max_passes, 1);
+  sp->merged = std::min<uint64_t>((uint64_t)sp->tile << f, kMaxMerged);
+  // Without a bound on the length the mean decides: short segments would pay for
+  // ten launches that find nothing to distribute (256 segments of 8192 int64: 79 us,
+  // 59 without), and the merge passes reach any longer ones among them.
+  const bool bounded = tu && tu->max_seg_len;
+  if (max_len > sp->merged && (bounded || n / std::max<uint64_t>(S, 1) > sp->merged) &&
+      pss::launch_dist_segments)
+    sp->dist = plan_dist(n, max_len, n_segs, sp->merged, kb, kv, sp->off_plan, sp->total);
+  if (!sp->dist.on) {
+    sp->merge_passes = sp->max_passes;
+    sp->merged = sp->longest;
   }
   return PSS_OK;
 }
 
 pss::SegPlanPtrs seg_plan_ptrs(char *w, const SegPlan &sp, uint32_t n_segs) {
   pss::SegPlanPtrs pp{};
+  pp.merged = sp.merged;
+  pp.longest = sp.longest;
   uint64_t *a = (uint64_t *)(w + sp.off_plan);
   const size_t stride = (size_t)n_segs + 1;
   for (int c = 0; c < 3; ++c) pp.tiles[c] = a + c * stride;
@@ -1182,21 +1207,6 @@ pss_status pss_segmented_sort(pss_ctx *ctx, pss_key_t key, pss_val_t val, const 
   hipStream_t s = (hipStream_t)stream;
   const int kt = (int)key;
   char *w = (char *)ws;
-  if (sp.dist.on) {
-    const pss::DistPlan &d = sp.dist;
-    const pss::DistBufs b{keys_in, vals_in, w + sp.off_keys, (uint32_t *)(w + sp.off_vals), keys_out,
-                          vals_out};
-    {
-      LaunchTimer t(ctx, "segment_plan", (uint64_t)n_segs * 16, s);
-      PSS_LAUNCH(pss::launch_dist_segments(d, seg_offsets, n, sp.small0, sp.small1, sp.longest, w, s),
-              "segment plan launch");
-    }
-    {
-      LaunchTimer t(ctx, "tile_sort", 0, s);
-      PSS_LAUNCH(pss::launch_dist_small(kt, kv, d, b, seg_offsets, w, s), "tile sort launch");
-    }
-    return run_dist_levels(ctx, d, kt, kv, b, n, w, s);
-  }
   const pss::SegPlanPtrs pp = seg_plan_ptrs(w, sp, n_segs);
   void *kws = w + sp.off_keys;
   uint32_t *vws = kv ? (uint32_t *)(w + sp.off_vals) : nullptr;
@@ -1209,7 +1219,7 @@ pss_status pss_segmented_sort(pss_ctx *ctx, pss_key_t key, pss_val_t val, const 
   const uint64_t sweep = 2 * n * (kbytes + (kv ? 4 : 0));
   {
     LaunchTimer t(ctx, "segment_plan", (uint64_t)n_segs * 16, s);
-    PSS_LAUNCH(pss::launch_seg_plan(seg_offsets, n_segs, n, pp, sp.small0, sp.small1, sp.max_passes,
+    PSS_LAUNCH(pss::launch_seg_plan(seg_offsets, n_segs, n, pp, sp.small0, sp.small1, sp.merge_passes,
                                     sp.fan_log2, sp.tile, sp.part, s),
             "segment plan launch");
   }
@@ -1219,7 +1229,7 @@ pss_status pss_segmented_sort(pss_ctx *ctx, pss_key_t key, pss_val_t val, const 
                                        samples, seg_offsets, pp, n_segs, n, sp.tile, s),
             "tile sort launch");
   }
-  for (uint32_t q = 1; q <= sp.max_passes; ++q) {
+  for (uint32_t q = 1; q <= sp.merge_passes; ++q) {
     pss::RunGeom g = sp.g[q - 1], gs = sp.gs[q - 1];
     g.seg = pss::SegTables{seg_offsets, pp.soff, pp.npass, pp.rows[q - 1], pp.parts[q - 1],
                            pp.sparts[q - 1], n_segs, q, 0};
@@ -1249,7 +1259,14 @@ pss_status pss_segmented_sort(pss_ctx *ctx, pss_key_t key, pss_val_t val, const 
               "merge launch");
     }
   }
-  return PSS_OK;
+  if (!sp.dist.on) return PSS_OK;
+  const pss::DistBufs b{keys_in, vals_in, kws, (uint32_t *)(w + sp.off_vals), keys_out, vals_out};
+  {
+    LaunchTimer t(ctx, "segment_plan", (uint64_t)n_segs * 16, s);
+    PSS_LAUNCH(pss::launch_dist_segments(sp.dist, seg_offsets, n, sp.merged, sp.longest, w, s),
+            "segment plan launch");
+  }
+  return run_dist_levels(ctx, sp.dist, kt, kv, b, n, w, s);
 }
 
 struct pss_graph {

@@ -370,48 +370,57 @@ template <bool KV> __device__ __forceinline__ uint32_t tile_slot(uint32_t idx) {
   return KV ? pad16(idx) : (idx >> 10) * TileLds<KV, 64>::RW + pad16(idx & 1023u);
 }
 
-// Stable sort of a key-value tile.  Thread t holds the tile's consecutive
-// positions 16t .. 16t+15, which it read from its own padded LDS slots; the
-// sorted tile is left in sk / sv at flat slots 0 .. TILE-1 (all threads past a
-// barrier).
-template <typename U, int THREADS>
-__device__ __forceinline__ void lds_sort_pairs(U (&rk)[kTileItems], uint32_t (&rv)[kTileItems], U *sk,
-                                               uint32_t *sv) {
-  constexpr uint32_t TILE = THREADS * kTileItems;
-  const uint32_t tid = threadIdx.x;
-  register_sort<U, true, kTileItems>(rk, rv);
-  // every wave writes back the keys it read (its own 1024 positions)
-  wave_sync();
+// Stable sort of a key-value tile of ITEMS (16 or 8) keys a thread.  Thread t holds
+// the tile's consecutive positions from ITEMS t on, which it read from its own
+// padded LDS slots; the sorted tile is left in sk / sv at flat slots 0 .. TILE-1
+// (all threads past a barrier).
+//
+// SHORT (here and below): the tile holds len keys only, and waves whose 64 ITEMS
+// positions all lie past them do nothing but wait; the tile is left sorted up to
+// the last position of the last wave that has keys.  tid: the thread's index, for
+// a caller that hides it from the optimiser (see dist_rest_kernel).
+template <typename U, int THREADS, bool SHORT = false, int ITEMS = kTileItems>
+__device__ __forceinline__ void lds_sort_pairs(U (&rk)[ITEMS], uint32_t (&rv)[ITEMS], U *sk,
+                                               uint32_t *sv, uint32_t len = THREADS * ITEMS,
+                                               uint32_t tid = threadIdx.x) {
+  constexpr uint32_t TILE = THREADS * ITEMS;
+  constexpr uint32_t WKEYS = 64 * ITEMS;  // keys per wave
+  const uint32_t end = SHORT ? (len + WKEYS - 1) / WKEYS * WKEYS : TILE;
+  const bool on = !SHORT || (tid >> 6) * WKEYS < end;
+  if (on) {
+    register_sort<U, true, ITEMS>(rk, rv);
+    // every wave writes back the keys it read (its own positions)
+    wave_sync();
 #pragma unroll
-  for (int i = 0; i < kTileItems; ++i) {
-    const uint32_t idx = tid * kTileItems + i;
-    sk[pad16(idx)] = rk[i];
-    sv[pad16(idx)] = rv[i];
+    for (int i = 0; i < ITEMS; ++i) {
+      const uint32_t idx = tid * ITEMS + i;
+      sk[pad16(idx)] = rk[i];
+      sv[pad16(idx)] = rv[i];
+    }
+    wave_sync();
   }
-  wave_sync();
 
   // Rounds of pairwise merges of runs of L keys.  Each pair's output is cut
   // into chunks of CI keys (never crossing into the next pair), one chunk per
   // thread: at most THREADS chunks per round.  The first round reads the
   // padded layout; every round writes the flat one (CI is odd, so the
   // threads' chunk stores do not collide in LDS banks).  While a pair fits in
-  // the 1024 keys that one wave's threads sorted, each wave merges only its
+  // the keys that one wave's threads sorted, each wave merges only its
   // own keys and, after the first round, synchronises only with itself.
-  constexpr int CI = kRoundItems;
-  constexpr uint32_t WKEYS = 64 * kTileItems;  // keys per wave
+  constexpr int CI = ITEMS + 1;
   U mk[CI];
   uint32_t mv[CI];
   const uint32_t lane = tid & 63, wbase = (tid >> 6) * WKEYS;
-  uint32_t L = kTileItems;
+  uint32_t L = ITEMS;
   for (; L < TILE && 2 * L <= WKEYS; L *= 2) {
     const uint32_t cpp = (2 * L + CI - 1) / CI;  // chunks per pair
     const uint32_t q = lane / cpp, c = lane - q * cpp;
-    const bool active = q < WKEYS / (2 * L);
+    const bool active = on && q < WKEYS / (2 * L);
     const uint32_t A0 = wbase + q * 2 * L;
     const uint32_t cs = A0 + c * CI;  // this thread's first output
     const uint32_t count = active ? (A0 + 2 * L - cs < (uint32_t)CI ? A0 + 2 * L - cs : CI) : 0;
     if (active) {
-      if (L == kTileItems)
+      if (L == ITEMS)
         merge_chunk<U, true, CI, true>(sk, sv, A0, A0 + L, A0 + 2 * L, cs, mk, mv);
       else
         merge_chunk<U, true, CI, false>(sk, sv, A0, A0 + L, A0 + 2 * L, cs, mk, mv);
@@ -420,7 +429,7 @@ __device__ __forceinline__ void lds_sort_pairs(U (&rk)[kTileItems], uint32_t (&r
     // flat one, whose slots overlap the previous wave's padded ones: all
     // waves must finish reading first.  Later rounds stay in the wave's own
     // flat slots.
-    if (L == kTileItems) __syncthreads();
+    if (L == ITEMS) __syncthreads();
     else wave_sync();
 #pragma unroll
     for (int i = 0; i < CI; ++i) {
@@ -432,14 +441,16 @@ __device__ __forceinline__ void lds_sort_pairs(U (&rk)[kTileItems], uint32_t (&r
     wave_sync();
   }
   __syncthreads();
-  for (; L < TILE; L *= 2) {
+  for (; L < end; L *= 2) {
     const uint32_t cpp = (2 * L + CI - 1) / CI;  // chunks per pair
     const uint32_t q = tid / cpp, c = tid - q * cpp;
     const uint32_t A0 = q * 2 * L;
-    const bool active = A0 < TILE;
     const uint32_t cs = A0 + c * CI;  // this thread's first output
-    const uint32_t count = active ? (A0 + 2 * L - cs < (uint32_t)CI ? A0 + 2 * L - cs : CI) : 0;
-    if (active) merge_chunk<U, true, CI, false>(sk, sv, A0, A0 + L, A0 + 2 * L, cs, mk, mv);
+    // (SHORT: a run with no other one to merge with stays where it is)
+    const uint32_t B1 = SHORT && end < A0 + 2 * L ? end : A0 + 2 * L;
+    const bool active = SHORT ? A0 + L < end && cs < B1 : A0 < TILE;
+    const uint32_t count = active ? (B1 - cs < (uint32_t)CI ? B1 - cs : CI) : 0;
+    if (active) merge_chunk<U, true, CI, false>(sk, sv, A0, A0 + L, B1, cs, mk, mv);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < CI; ++i) {
@@ -455,20 +466,26 @@ __device__ __forceinline__ void lds_sort_pairs(U (&rk)[kTileItems], uint32_t (&r
 // Sort of a keys-only tile: any 16 keys of the tile per thread in rk; the
 // sorted tile is left in sk at flat slots 0 .. TILE-1 (all threads past a
 // barrier).
-template <typename U, int THREADS>
-__device__ __forceinline__ void lds_sort_keys(U (&rk)[kTileItems], U *sk) {
+template <typename U, int THREADS, bool SHORT = false>
+__device__ __forceinline__ void lds_sort_keys(U (&rk)[kTileItems], U *sk,
+                                              uint32_t len = THREADS * kTileItems,
+                                              uint32_t tid = threadIdx.x) {
   using T = TileLds<false, THREADS>;
   constexpr uint32_t TILE = T::TILE;
-  const uint32_t tid = threadIdx.x;
-  uint32_t none[1];
-  register_sort<U, false, kTileItems>(rk, none);
-  // Keys only.  Runs of 128 are formed in registers (bitonic merges across
-  // lanes), written to the padded layout of each thread's own 16 slots.
-  lane_runs_to_128(rk, tid & 63);
-  wave_sync();
+  constexpr uint32_t WKEYS = 64 * kTileItems;  // keys per wave
+  const uint32_t end = SHORT ? (len + WKEYS - 1) / WKEYS * WKEYS : TILE;
+  const bool on = !SHORT || (tid >> 6) * WKEYS < end;
+  if (on) {
+    uint32_t none[1];
+    register_sort<U, false, kTileItems>(rk, none);
+    // Keys only.  Runs of 128 are formed in registers (bitonic merges across
+    // lanes), written to the padded layout of each thread's own 16 slots.
+    lane_runs_to_128(rk, tid & 63);
+    wave_sync();
 #pragma unroll
-  for (int i = 0; i < kTileItems; ++i) sk[tile_slot<false>(tid * kTileItems + i)] = rk[i];
-  wave_sync();
+    for (int i = 0; i < kTileItems; ++i) sk[tile_slot<false>(tid * kTileItems + i)] = rk[i];
+    wave_sync();
+  }
   // Then rounds of merge-path merges.  Round 128 reads the padded layout and
   // writes the gapped one, where every run is followed by kGap slots of the
   // largest key, so the later rounds use merge_chunk_keys (no bound
@@ -477,7 +494,7 @@ __device__ __forceinline__ void lds_sort_keys(U (&rk)[kTileItems], U *sk) {
   // synchronises only with itself; larger rounds use runs at j (L + G)
   // across the tile.
   constexpr int CI = kRoundItems;
-  constexpr uint32_t G = kGap, WKEYS = 64 * kTileItems;
+  constexpr uint32_t G = kGap;
   const uint32_t lane = tid & 63, wv = tid >> 6;
   U mk[CI];
   uint32_t dummy_v[1];
@@ -485,7 +502,7 @@ __device__ __forceinline__ void lds_sort_keys(U (&rk)[kTileItems], U *sk) {
   for (; L < TILE && 2 * L <= WKEYS; L *= 2) {
     const uint32_t cpp = (2 * L + CI - 1) / CI;  // chunks per pair
     const uint32_t q = lane / cpp, c = lane - q * cpp;
-    const bool active = q < WKEYS / (2 * L);
+    const bool active = on && q < WKEYS / (2 * L);
     const uint32_t o = c * CI;  // this chunk's first output within the pair
     const uint32_t count = active ? (2 * L - o < (uint32_t)CI ? 2 * L - o : CI) : 0u;
     const bool to_tile = 4 * L > WKEYS;  // the next round's pairs span waves
@@ -516,20 +533,28 @@ __device__ __forceinline__ void lds_sort_keys(U (&rk)[kTileItems], U *sk) {
     if (to_tile) __syncthreads();
     else wave_sync();
   }
-  for (; L < TILE; L *= 2) {
+  for (; L < end; L *= 2) {
     const uint32_t cpp = (2 * L + CI - 1) / CI;  // chunks per pair
     const uint32_t q = tid / cpp, c = tid - q * cpp;
-    const bool active = q < TILE / (2 * L);
     const uint32_t o = c * CI;
-    const uint32_t count = active ? (2 * L - o < (uint32_t)CI ? 2 * L - o : CI) : 0u;
+    // keys of the pair and of its second run (SHORT: of the last pair, and none
+    // if it has no second run, which then reads the largest keys after the first)
+    uint32_t pair = 2 * L, lb = L;
+    if constexpr (SHORT) {
+      const uint32_t left = 2 * q * L < end ? end - 2 * q * L : 0u;
+      pair = left < 2 * L ? left : 2 * L;
+      lb = pair > L ? pair - L : 0u;
+    }
+    const bool active = SHORT ? o < pair : q < TILE / (2 * L);
+    const uint32_t count = active ? (pair - o < (uint32_t)CI ? pair - o : CI) : 0u;
     const uint32_t A0 = 2 * q * (L + G), dst = q * (2 * L + G);
-    if (active) merge_chunk_keys<U, CI>(sk, A0, L, A0 + L + G, L, o, mk);
+    if (active) merge_chunk_keys<U, CI>(sk, A0, pair - lb, lb ? A0 + L + G : A0 + pair, lb, o, mk);
     __syncthreads();
     if (active) {
 #pragma unroll
       for (int i = 0; i < CI; ++i) sk[dst + o + i] = mk[i];
-      if (o + count == 2 * L && 2 * L < TILE)
-        for (uint32_t j = 0; j < G; ++j) sk[dst + 2 * L + j] = key_max<U>();
+      if (o + count == pair && (SHORT || 2 * L < TILE))
+        for (uint32_t j = 0; j < G; ++j) sk[dst + pair + j] = key_max<U>();
     }
     __syncthreads();
   }

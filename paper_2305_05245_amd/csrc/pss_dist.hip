@@ -61,7 +61,7 @@ struct Level {
   uint32_t *start;
   void *table;
   DistLeaf *leaves;
-  uint64_t *rest;  // offset | length << 32, mapped keys in the output
+  uint32_t *rest;  // leaves with a crowded bin
   DistBig *big;
   uint32_t level, levels, cap, target, rl, next_rl;
   uint32_t src;  // kSrc* of this level's leaves
@@ -73,7 +73,7 @@ struct Level {
   uint32_t kv, max_copies;
   const uint16_t *ptable;  // gathered: the table of the level before,
   uint32_t *pre;           // and per bucket the keys before every 8 tiles
-  uint32_t *err;           // device error word
+  uint32_t *err;  // device error word (kernels that report only)
 };
 
 // A bound of the plan does not hold: what would lie past it is not written, the
@@ -239,36 +239,29 @@ __global__ __launch_bounds__(kPiecesThreads) void dist_pieces_kernel(Level L) {
 
 // ------------------------------------------------------------- segments ---
 // Segmented distribution sort: one workgroup reads the segment offsets, checks
-// them, and lists every segment by its length: the two classes of short
-// segments, leaves (at most cap keys), first-level nodes.  Invalid offsets (not
-// starting at 0, decreasing, or ending beyond n) give empty lists and an error
-// bit; segments above `longest` (what the caller's bound on the segment length
-// allows) are left out and give it too.
+// them, and lists every segment of more than `merged` and at most `longest` keys
+// as a node of the first level.  Invalid offsets (not starting at 0, decreasing,
+// or ending beyond n) give no nodes and an error bit.
 struct SegDistArgs {
   const uint64_t *off;
   uint32_t n_segs;
-  uint64_t n, longest;
-  uint32_t small0, small1, cap, target, rl, root_p, levels, tiled;
+  uint64_t n, merged, longest;
+  uint32_t target, rl, root_p, levels, tiled;
   DistCounters *ctr;
   DistNode *nodes;
   DistRange *ranges;
-  DistLeaf *leaves;
-  uint32_t *small;  // [2][n_segs]
-  uint32_t max_nodes, max_ranges, max_cols, max_table, max_leaves;
+  uint32_t max_nodes, max_ranges, max_cols, max_table;
   uint32_t *err;  // device error word
 };
 
 __global__ __launch_bounds__(1024) void seg_dist_plan_kernel(SegDistArgs a) {
-  // two words: `bad` is read while another wave may already set `over`
-  __shared__ uint32_t bad, over;
-  __shared__ uint32_t n_small[2], n_leaves, n_nodes, n_ranges, n_cols, n_table;
+  __shared__ uint32_t bad, n_nodes, n_ranges, n_cols, n_table;
   const uint32_t tid = threadIdx.x;
   uint32_t *c = (uint32_t *)a.ctr;
   for (uint32_t i = tid; i < sizeof(DistCounters) / 4; i += 1024) c[i] = 0;
   if (tid == 0) {
     bad = (a.off[0] != 0 || a.off[a.n_segs] > a.n) ? 1u : 0u;
-    over = 0;
-    n_small[0] = n_small[1] = n_leaves = n_nodes = n_ranges = n_cols = n_table = 0;
+    n_nodes = n_ranges = n_cols = n_table = 0;
   }
   __syncthreads();
   for (uint32_t s = tid; s < a.n_segs; s += 1024)
@@ -277,54 +270,37 @@ __global__ __launch_bounds__(1024) void seg_dist_plan_kernel(SegDistArgs a) {
   const bool ok = bad == 0;
   if (tid == 0 && !ok) atomicOr(a.err, kErrSegments);
   if (!ok) return;
-  bool left_out = false;
   for (uint32_t s = tid; s < a.n_segs; s += 1024) {
     const uint64_t len64 = a.off[s + 1] - a.off[s];
-    const uint32_t off = (uint32_t)a.off[s], len = (uint32_t)len64;
-    if (len64 == 0) continue;
-    if (len64 > a.longest) {
-      left_out = true;
-    } else if (len <= a.small1) {
-      const int cls = len <= a.small0 ? 0 : 1;
-      a.small[(uint64_t)cls * a.n_segs + atomicAdd(&n_small[cls], 1u)] = s;
-    } else if (len <= a.cap) {
-      const uint32_t to = atomicAdd(&n_leaves, 1u);
-      if (to < a.max_leaves) a.leaves[to] = DistLeaf{off, len | kSrcIn << kLeafSrcShift, 0, 0, 0, 0, 0, 0, 0, 0};
-      else plan_failed(a.ctr, a.err);
+    if (len64 <= a.merged || len64 > a.longest) continue;
+    const uint32_t len = (uint32_t)len64;
+    DistNode d;
+    d.off = (uint32_t)a.off[s];
+    d.len = len;
+    d.p = node_picks(len, a.target, (int)a.levels);
+    d.p = d.p < a.root_p ? d.p : a.root_p;
+    d.nr = (len + a.rl - 1) / a.rl;
+    d.cols = node_cols(d.p);
+    d.stride = node_stride(len, d.nr, a.tiled != 0);
+    d.nb = 0;
+    d.poff = d.plen = d.prow = d.pnext = 0;
+    const uint32_t at = atomicAdd(&n_nodes, 1u), r0 = atomicAdd(&n_ranges, d.nr);
+    d.sbase = atomicAdd(&n_cols, d.cols);
+    d.tbase = atomicAdd(&n_table, d.cols * d.stride);
+    if (at < a.max_nodes && r0 + d.nr <= a.max_ranges && d.sbase + d.cols <= a.max_cols &&
+        d.tbase + d.cols * d.stride <= a.max_table) {
+      a.nodes[at] = d;
+      for (uint32_t r = 0; r < d.nr; ++r) a.ranges[r0 + r] = DistRange{at, r};
     } else {
-      DistNode d;
-      d.off = off;
-      d.len = len;
-      d.p = node_picks(len, a.target, (int)a.levels);
-      d.p = d.p < a.root_p ? d.p : a.root_p;
-      d.nr = (len + a.rl - 1) / a.rl;
-      d.cols = node_cols(d.p);
-      d.stride = node_stride(len, d.nr, a.tiled != 0);
-      d.nb = 0;
-      d.poff = d.plen = d.prow = d.pnext = 0;
-      const uint32_t at = atomicAdd(&n_nodes, 1u), r0 = atomicAdd(&n_ranges, d.nr);
-      d.sbase = atomicAdd(&n_cols, d.cols);
-      d.tbase = atomicAdd(&n_table, d.cols * d.stride);
-      if (at < a.max_nodes && r0 + d.nr <= a.max_ranges && d.sbase + d.cols <= a.max_cols &&
-          d.tbase + d.cols * d.stride <= a.max_table) {
-        a.nodes[at] = d;
-        for (uint32_t r = 0; r < d.nr; ++r) a.ranges[r0 + r] = DistRange{at, r};
-      } else {
-        plan_failed(a.ctr, a.err);
-      }
+      plan_failed(a.ctr, a.err);
     }
   }
-  if (left_out) atomicOr(&over, 1u);
   __syncthreads();
   if (tid == 0) {
-    if (over) atomicOr(a.err, kErrSegments);
     a.ctr->nodes[1] = n_nodes;
     a.ctr->ranges[1] = n_ranges;
     a.ctr->cols[1] = n_cols;
     a.ctr->table[1] = n_table;
-    a.ctr->leaves = n_leaves;
-    a.ctr->small[0] = n_small[0];
-    a.ctr->small[1] = n_small[1];
   }
 }
 
@@ -1103,7 +1079,7 @@ __device__ __forceinline__ DistLeaf uniform(const DistLeaf &f) {
 // Keys of the last level are gathered: the leaf's piece of every tile of the
 // node is found in the table, and a bit mask over the leaf's positions, set
 // where a piece starts, tells every position its piece.
-constexpr uint32_t kCrowded = 24;
+constexpr uint32_t kCrowded = 16;
 // Bins of one key value: keys-only they need no sorting, and the byte of their
 // count limits them; key-value every key counts the earlier ones of its bin.
 template <bool KV> constexpr uint32_t kCrowdedDirect = KV ? 96 : 255;
@@ -1167,9 +1143,63 @@ __device__ __forceinline__ void sort_bin(U *sk, uint16_t *sidx, uint32_t n) {
   }
 }
 
+// Where the keys of a leaf that lies in pieces are: use(i, address) of the key at
+// position at(i), for the steps i that are wanted (the same for a whole wave).
+// `piece` (one entry a tile of the node) and the tables `mask` (a bit a
+// position) and `row_piece` (an entry for 64) are scratch, free again on return.
+template <int NT, int NI, typename At, typename Wanted, typename Use>
+__device__ __forceinline__ void leaf_addresses(const Level &L, const DistLeaf &leaf, uint32_t *piece,
+                                               uint32_t *mask, uint16_t *row_piece, uint32_t *wsum,
+                                               At at, Wanted wanted, Use use) {
+  constexpr uint32_t CAP = NT * NI;
+  const uint32_t tid = threadIdx.x, len = leaf.len_flags & kLeafLenMask;
+  const uint16_t *table = (const uint16_t *)L.table;
+  const uint32_t tiles = (leaf.node_len + kDistTile - 1) / kDistTile;
+  for (uint32_t i = tid; i < CAP / 32; i += NT) mask[i] = 0;
+  uint32_t np = 0, run = 0;
+  for (uint32_t t0 = 0; t0 < tiles && run < leaf.first + len; t0 += NT) {
+    const uint32_t t = t0 + tid;
+    uint32_t s, c;
+    piece_of(table, leaf.row, leaf.next_row, leaf.node_len, t, s, c);
+    c -= s;
+    // keys (at most 512 tiles of 6144: 22 bits) and non-empty pieces before
+    uint32_t total;
+    const uint32_t x = block_scan<NT>(c | (c ? 1u << 22 : 0u), wsum, total);
+    const uint32_t first = run + (x & 0x3fffffu), pi = np + (x >> 22);
+    if (c) {
+      // position of the piece's first key in the leaf; a piece that starts
+      // before the leaf holds position 0
+      const uint32_t pos = first > leaf.first ? first - leaf.first : 0u;
+      const uint32_t stop = first + c > leaf.first ? first + c - leaf.first : 0u;
+      piece[pi] = leaf.node_off + t * kDistTile + s + leaf.first - first;  // modulo 2^32
+      if (stop && pos < len) {
+        if (pos & 63u) {
+          const uint32_t bit = (pos & 63u) - 1;
+          atomicOr(&mask[(pos >> 6) * 2 + (bit >> 5)], 1u << (bit & 31u));
+        }
+        for (uint32_t r = (pos + 63) / 64; r * 64 < stop && r * 64 < len; ++r)
+          row_piece[r] = (uint16_t)pi;
+      }
+    }
+    run += total & 0x3fffffu;
+    np += total >> 22;
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    if (wanted(i)) {  // (positions past the end: the last key)
+      const uint32_t j = at(i) < len ? at(i) : len - 1;
+      const uint32_t r = j >> 6;
+      const uint64_t m = (uint64_t)mask[r * 2] | (uint64_t)mask[r * 2 + 1] << 32;
+      const uint32_t started = __popcll(m & (((uint64_t)1 << (j & 63u)) - 1));
+      use(i, piece[row_piece[r] + started] + j);
+    }
+  }
+  __syncthreads();
+}
+
 template <int KT, bool KV, int NT, int NI>
 __device__ __forceinline__ void sort_leaf(
-    const typename Key<KT>::U *__restrict__ in, const uint32_t *__restrict__ vin,
     const typename Key<KT>::U *__restrict__ ws, const uint32_t *__restrict__ vws,
     typename Key<KT>::U *out, uint32_t *vout, const Level &L, uint32_t li) {
   using U = typename Key<KT>::U;
@@ -1194,16 +1224,21 @@ __device__ __forceinline__ void sort_leaf(
   static_assert(dist_node_tiles(sizeof(U), KV) * 4 <= sizeof(sk), "pieces fit the key area");
   static_assert(CAP / 8 + CAP / 32 <= sizeof(bins), "mask and rows fit the bins");
   const uint32_t tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const uint16_t *table = (const uint16_t *)L.table;
   const DistLeaf leaf = uniform(L.leaves[li]);
   const uint32_t off = leaf.off, len = leaf.len_flags & kLeafLenMask;
   const uint32_t from = (leaf.len_flags >> kLeafSrcShift) & 3u;
   const bool inner = from == kSrcPieces && (leaf.len_flags & kLeafInner);
-  const U *p = from == kSrcOut ? (const U *)out : from == kSrcIn ? in : ws;
-  const uint32_t *vp = from == kSrcOut ? (const uint32_t *)vout : from == kSrcIn ? vin : vws;
   U k[NI];
   uint32_t v[KV ? NI : 1];
-  uint32_t addr[NI];
+  // the loads are all issued before any is used: clamped, not conditional;
+  // steps of NT keys past the end are skipped throughout.  Keys in pieces are
+  // loaded as their addresses are found, before the barrier that ends the search
+  // (2^28 int64: 3.71 ms, after it 3.87; 2^27 uint64 with values 2.97 and 3.04).
+  auto load = [&](int i, const U *p, const uint32_t *vp, uint32_t addr) {
+    k[i] = __builtin_nontemporal_load(&p[addr]);
+    if constexpr (KV) v[i] = __builtin_nontemporal_load(&vp[addr]);
+  };
+  auto wanted = [&](int i) { return i * NT < len; };
   if (from == kSrcPieces) {
     if (!KV && (leaf.len_flags & kLeafEqual)) {
       // one key value, known from the splitters: nothing to read
@@ -1212,65 +1247,14 @@ __device__ __forceinline__ void sort_leaf(
         __builtin_nontemporal_store(Key<KT>::unmap(x), &out[off + i]);
       return;
     }
-    const uint32_t tiles = (leaf.node_len + kDistTile - 1) / kDistTile;
-    for (uint32_t i = tid; i < CAP / 32; i += NT) mask[i] = 0;
-    uint32_t np = 0, run = 0;
-    for (uint32_t t0 = 0; t0 < tiles && run < leaf.first + len; t0 += NT) {
-      const uint32_t t = t0 + tid;
-      uint32_t s, c;
-      piece_of(table, leaf.row, leaf.next_row, leaf.node_len, t, s, c);
-      c -= s;
-      // keys (at most 512 tiles of 6144: 22 bits) and non-empty pieces before
-      uint32_t total;
-      const uint32_t x = block_scan<NT>(c | (c ? 1u << 22 : 0u), wsum, total);
-      const uint32_t first = run + (x & 0x3fffffu), at = np + (x >> 22);
-      if (c) {
-        // position of the piece's first key in the leaf; a piece that starts
-        // before the leaf holds position 0
-        const uint32_t pos = first > leaf.first ? first - leaf.first : 0u;
-        const uint32_t stop = first + c > leaf.first ? first + c - leaf.first : 0u;
-        piece[at] = leaf.node_off + t * kDistTile + s + leaf.first - first;  // modulo 2^32
-        if (stop && pos < len) {
-          if (pos & 63u) {
-            const uint32_t bit = (pos & 63u) - 1;
-            atomicOr(&mask[(pos >> 6) * 2 + (bit >> 5)], 1u << (bit & 31u));
-          }
-          for (uint32_t r = (pos + 63) / 64; r * 64 < stop && r * 64 < len; ++r)
-            row_piece[r] = (uint16_t)at;
-        }
-      }
-      run += total & 0x3fffffu;
-      np += total >> 22;
-      __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      if (i * NT < len) {  // (positions past the end: the last key)
-        const uint32_t j = i * NT + tid < len ? i * NT + tid : len - 1;
-        const uint32_t r = j >> 6;
-        const uint64_t m = (uint64_t)mask[r * 2] | (uint64_t)mask[r * 2 + 1] << 32;
-        const uint32_t started = __popcll(m & (((uint64_t)1 << (j & 63u)) - 1));
-        addr[i] = piece[row_piece[r] + started] + j;
-      }
-    }
-    __syncthreads();
+    leaf_addresses<NT, NI>(L, leaf, piece, mask, row_piece, wsum, [&](int i) { return i * NT + tid; }, wanted,
+                           [&](int i, uint32_t addr) { load(i, ws, vws, addr); });
   } else {
-#pragma unroll
-    for (int i = 0; i < NI; ++i) addr[i] = off + (i * NT + tid < len ? i * NT + tid : len - 1);
-  }
-  // the loads are all issued before any is used: clamped, not conditional;
-  // steps of NT keys past the end are skipped throughout
-#pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    if (i * NT < len) {
-      k[i] = __builtin_nontemporal_load(&p[addr[i]]);
-      if constexpr (KV) v[i] = __builtin_nontemporal_load(&vp[addr[i]]);
-    }
-  }
-  if (from == kSrcIn) {
+    const U *p = from == kSrcOut ? (const U *)out : ws;
+    const uint32_t *vp = from == kSrcOut ? (const uint32_t *)vout : vws;
 #pragma unroll
     for (int i = 0; i < NI; ++i)
-      if (i * NT < len) k[i] = Key<KT>::map(k[i]);
+      if (wanted(i)) load(i, p, vp, off + (i * NT + tid < len ? i * NT + tid : len - 1));
   }
   if (leaf.len_flags & (kLeafEqual | kLeafMove)) {
     const bool equal = leaf.len_flags & kLeafEqual;
@@ -1346,17 +1330,26 @@ __device__ __forceinline__ void sort_leaf(
     }
   }
   if (__syncthreads_or(worst >= (direct ? kCrowdedDirect<KV> : kCrowded))) {
+    // one key value between two sampled ones: the keys (and values) are in order
+    if (tid == 0) smin[0] = k[0];
+    __syncthreads();
+    const U x = smin[0];
+    bool other = false;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const uint32_t idx = i * NT + tid;
-      if (idx < len) {
-        out[off + idx] = k[i];
-        if constexpr (KV) vout[off + idx] = v[i];
+    for (int i = 0; i < NI; ++i)
+      if (i * NT < len) other |= k[i] != x;
+    if (!__syncthreads_or(other)) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const uint32_t idx = i * NT + tid;
+        if (idx < len) {
+          out[off + idx] = Key<KT>::unmap(x);
+          if constexpr (KV) vout[off + idx] = v[i];
+        }
       }
-    }
-    if (tid == 0) {
+    } else if (tid == 0) {
       const uint32_t to = atomicAdd(&L.ctr->rest, 1u);
-      if (to < L.max_rest) L.rest[to] = (uint64_t)off | (uint64_t)len << 32;
+      if (to < L.max_rest) L.rest[to] = li;
       else plan_failed(L.ctr, L.err);
     }
     return;
@@ -1480,7 +1473,6 @@ __device__ __forceinline__ void sort_leaf(
 // a tile adjoin and share cache lines, which that XCD's L2 then reads once.
 template <int KT, bool KV, int NT, int NI, int WAVES>
 __global__ __launch_bounds__(NT, WAVES) void dist_leaf_kernel(
-    const typename Key<KT>::U *__restrict__ in, const uint32_t *__restrict__ vin,
     const typename Key<KT>::U *__restrict__ ws, const uint32_t *__restrict__ vws,
     typename Key<KT>::U *out, uint32_t *vout, Level L) {
   const uint32_t nl = L.ctr->leaves;
@@ -1492,48 +1484,51 @@ __global__ __launch_bounds__(NT, WAVES) void dist_leaf_kernel(
     const uint32_t li = x % kXcds * each + x / kXcds;
     if (li >= nl) continue;
     __syncthreads();  // the last leaf's LDS is read no more
-    sort_leaf<KT, KV, NT, NI>(in, vin, ws, vws, out, vout, L, li);
+    sort_leaf<KT, KV, NT, NI>(ws, vws, out, vout, L, li);
   }
 }
 
 // ----------------------------------------------------------------- rest ---
-// Sorts m mapped keys (and values) from a to b, which may be the same; unmapped
-// if they are final.  The tile sort's network and merge rounds.
-template <int KT, bool KV, int NT>
-__device__ __forceinline__ void sort_tile(const typename Key<KT>::U *a, const uint32_t *va,
-                                          typename Key<KT>::U *b, uint32_t *vb, uint32_t m, bool final,
-                                          typename Key<KT>::U *sk, uint32_t *sv) {
-  using U = typename Key<KT>::U;
-  constexpr uint32_t CAP = NT * kTileItems;
-  const uint32_t tid = threadIdx.x;
-  U k[kTileItems];
-  uint32_t v[kTileItems];
-  __syncthreads();  // the tile before is read no more
-  if constexpr (KV) {
-    for (uint32_t i = tid; i < CAP; i += NT) {
-      sk[pad16(i)] = i < m ? a[i] : key_max<U>();
-      sv[pad16(i)] = i < m ? va[i] : 0u;
-    }
-    __syncthreads();
+// The tile sort's network and merge rounds on len keys (and values) at p[addr[i]],
+// where a thread's i-th is position tile_pos(tid, i) (a position past the end: any
+// address of a key).  The sorted keys are left in sk (values in sv).
+template <int NI>
+__device__ __forceinline__ uint32_t tile_pos(uint32_t tid, int i) {  // (a wave's are consecutive)
+  return (tid >> 6) * (64 * NI) + i * 64 + (tid & 63);
+}
+
+template <typename U, bool KV, int NT, int NI>
+__device__ __forceinline__ void sort_tile(const U *p, const uint32_t *vp,
+                                          const uint32_t (&addr)[NI], uint32_t len,
+                                          U *sk, uint32_t *sv, uint32_t tid) {
+  U k[NI];
+  uint32_t v[NI];
+  if ((tid >> 6) * (64 * NI) < len) {
 #pragma unroll
-    for (int i = 0; i < kTileItems; ++i) {
-      k[i] = sk[pad16(tid * kTileItems + i)];
-      v[i] = sv[pad16(tid * kTileItems + i)];
+    for (int i = 0; i < NI; ++i) {
+      k[i] = p[addr[i]];
+      if constexpr (KV) v[i] = vp[addr[i]];
     }
-    lds_sort_pairs<U, NT>(k, v, sk, sv);
-  } else {
 #pragma unroll
-    for (int i = 0; i < kTileItems; ++i) {
-      const uint32_t idx = i * NT + tid;
-      const U x = a[idx < m ? idx : m - 1];
-      k[i] = idx < m ? x : key_max<U>();
+    for (int i = 0; i < NI; ++i) {
+      const bool ok = tile_pos<NI>(tid, i) < len;
+      k[i] = ok ? k[i] : key_max<U>();
+      if constexpr (KV) {  // consecutive positions a thread, through LDS
+        sk[pad16(tile_pos<NI>(tid, i))] = k[i];
+        sv[pad16(tile_pos<NI>(tid, i))] = ok ? v[i] : 0u;
+      }
     }
-    lds_sort_keys<U, NT>(k, sk);
+    if constexpr (KV) {
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        k[i] = sk[pad16(tid * NI + i)];
+        v[i] = sv[pad16(tid * NI + i)];
+      }
+    }
   }
-  for (uint32_t i = tid; i < m; i += NT) {
-    b[i] = final ? Key<KT>::unmap(sk[i]) : sk[i];
-    if constexpr (KV) vb[i] = sv[i];
-  }
+  if constexpr (KV) lds_sort_pairs<U, NT, true, NI>(k, v, sk, sv, len, tid);
+  else lds_sort_keys<U, NT, true>(k, sk, len, tid);
 }
 
 // How many of the first d keys of the merge of a[0, la) and b[0, lb) (ties to a)
@@ -1554,82 +1549,127 @@ __device__ __forceinline__ uint32_t wave_merge_path(const U *a, uint32_t la, con
   return lo;
 }
 
-// What the leaf kernel left, as mapped keys at their place in the output:
-// leaves with a crowded bin, which are sorted like tiles, and big buckets, above
-// the cap.
+// What the leaf kernel left: leaves with a crowded bin, each sorted like a tile by
+// one workgroup (16 million int64 of 1000 values in segments of 100003, all leaves
+// crowded: 378 us, uint64 with values 565; 438 and 766 when the leaf kernel wrote
+// such leaves out, and this one sorted them as whole tiles, with values 16 keys a
+// thread), and big buckets, above the cap.
 //
 // Big buckets come from samples that missed much of a node: about one bucket of
 // ten thousand by chance, and then of two tiles, but the sampled positions can
 // be computed, and an input that holds one key there has its whole array in
 // two.  So their sorts are tasks that all workgroups share (1500000 uint64 keys
-// of that kind: 521 us, by one workgroup a bucket 14611; random ones 92).  A bucket of T tiles has T tile sorts and
-// then, for every doubling of the sorted runs, T merges of one tile's length,
-// between the output and the workspace.  Workgroups claim the tasks of all
-// buckets in one order, round by round, and a task waits until the rounds before
-// its own have ended: every task it waits for has a lower number, so some
-// workgroup already works on it, and the lowest unfinished task never waits.
+// of that kind: 552 us, by one workgroup a bucket 14611; random ones 92).  A
+// bucket of T tiles has T tile sorts and then, for every doubling of the sorted
+// runs, T merges of one tile's length, between the output and the workspace.
+//
+// Workgroups claim the tasks of all in one order: the crowded leaves (which lie
+// in the workspace), then bucket by bucket, round by round.  A task waits until
+// all before its round have ended: every task it waits for has a lower number,
+// so some workgroup already works on it, and the lowest unfinished task never
+// waits.
 // (One thread's fences stand for the workgroup, between its barriers: fences of
 // all waves write back and invalidate the L2 each, 1397 us.)
-template <int KT, bool KV, int NT>
-__global__ __launch_bounds__(NT) void dist_rest_kernel(typename Key<KT>::U *ws, uint32_t *vws,
-                                                       typename Key<KT>::U *out, uint32_t *vout,
-                                                       const uint64_t *__restrict__ rest,
-                                                       DistBig *big, DistCounters *ctr) {
+template <int KT, bool KV, int NT, int NI, int WAVES>
+__global__ __launch_bounds__(NT, WAVES) void dist_rest_kernel(
+    typename Key<KT>::U *ws, uint32_t *vws, typename Key<KT>::U *out, uint32_t *vout, Level L) {
   using U = typename Key<KT>::U;
-  using T = TileLds<KV, NT>;
-  constexpr uint32_t CAP = NT * kTileItems;
+  constexpr uint32_t CAP = NT * NI;
+  using T = TileLds<KV, CAP / kTileItems>;
   __shared__ U sk[T::SLOTS];
   __shared__ uint32_t sv[KV ? T::SLOTS : 1];
+  __shared__ uint32_t mask[CAP / 32], wsum[NT / 64];
+  __shared__ uint16_t row_piece[CAP / 64];
   __shared__ uint32_t claimed, path[2];
-  const uint32_t tid = threadIdx.x;
+  static_assert(dist_node_tiles(sizeof(U), KV) * 4 <= sizeof(sk), "pieces fit the key area");
+  DistCounters *ctr = L.ctr;
+  DistBig *big = L.big;
   const uint32_t no = ctr->rest, nbig = ctr->big;
-  if (ctr->failed) return;
-  for (uint32_t oi = blockIdx.x; oi < no; oi += gridDim.x) {
-    const uint32_t off = (uint32_t)rest[oi], len = (uint32_t)(rest[oi] >> 32);
-    sort_tile<KT, KV, NT>(out + off, KV ? vout + off : nullptr, out + off, KV ? vout + off : nullptr, len,
-                          true, sk, sv);
-  }
-  uint32_t e = 0, base = 0;  // a bucket, and its first task
-  while (e < nbig) {
-    __syncthreads();
+  if (ctr->failed || no + nbig == 0) return;
+  uint32_t e = 0, base = no;  // a bucket, and its first task
+  for (;;) {
+    // hidden from the optimiser, which otherwise computes every LDS address of the
+    // sort before the loop and keeps it (240 registers, one workgroup a CU)
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    __syncthreads();  // the task before has no more use for the LDS
     if (tid == 0) claimed = atomicAdd(&ctr->next_task, 1u);
     __syncthreads();
     const uint32_t task = claimed;
-    uint32_t off, len, tiles, rounds;
-    for (;;) {
-      off = big[e].off;
-      len = big[e].len;
-      tiles = (len + CAP - 1) / CAP;
-      rounds = 32 - __clz(tiles - 1);
-      if (task < base + tiles * (1 + rounds)) break;
-      base += tiles * (1 + rounds);
-      if (++e == nbig) return;
-    }
-    const uint32_t r = (task - base) / tiles, o = (task - base) % tiles * CAP;
-    const uint32_t m = len - o < CAP ? len - o : CAP;
-    // round r leaves its runs in the output if the number of rounds to come is even
-    const bool here = ((rounds - r) & 1) == 0;
-    U *dst = (here ? out : ws) + off;
-    uint32_t *vdst = KV ? (here ? vout : vws) + off : nullptr;
-    if (r == 0) {
-      sort_tile<KT, KV, NT>(out + off + o, KV ? vout + off + o : nullptr, dst + o, KV ? vdst + o : nullptr, m,
-                            false, sk, sv);
+    // the m keys of the task come from p (a merge's from o in the runs of src) and
+    // go to dst, final or still mapped
+    const U *p = out, *src = nullptr;
+    const uint32_t *vp = vout, *vsrc = nullptr;
+    U *dst = out;
+    uint32_t *vdst = vout, *count = &ctr->rest_done;
+    uint32_t m, o = 0, r = 0, len = 0, addr[NI];
+    bool final = true;
+    if (task < no) {
+      const DistLeaf leaf = uniform(L.leaves[L.rest[task]]);
+      const uint32_t from = (leaf.len_flags >> kLeafSrcShift) & 3u;
+      m = leaf.len_flags & kLeafLenMask;
+      p = from == kSrcOut ? out : ws;
+      vp = from == kSrcOut ? vout : vws;
+      dst += leaf.off;
+      if constexpr (KV) vdst += leaf.off;
+      if (from == kSrcPieces)
+        leaf_addresses<NT, NI>(L, leaf, reinterpret_cast<uint32_t *>(sk), mask, row_piece, wsum,
+                               [&](int i) { return tile_pos<NI>(tid, i); },
+                               [&](int) { return tile_pos<NI>(tid, 0) - (tid & 63) < m; },
+                               [&](int i, uint32_t at) { addr[i] = at; });
+      else
+#pragma unroll
+        for (int i = 0; i < NI; ++i) addr[i] = leaf.off + (tile_pos<NI>(tid, i) < m ? tile_pos<NI>(tid, i) : 0u);
     } else {
-      const U *src = (here ? ws : out) + off;
-      const uint32_t *vsrc = KV ? (here ? vws : vout) + off : nullptr;
+      if (nbig == 0) return;
+      uint32_t tiles, rounds;
+      for (;;) {
+        len = big[e].len;
+        tiles = (len + CAP - 1) / CAP;
+        rounds = 32 - __clz(tiles - 1);
+        if (task < base + tiles * (1 + rounds)) break;
+        base += tiles * (1 + rounds);
+        if (++e == nbig) return;
+      }
+      const uint32_t off = big[e].off;
+      r = (task - base) / tiles;
+      o = (task - base) % tiles * CAP;
+      m = len - o < CAP ? len - o : CAP;
+      final = r == rounds;
+      // round r leaves its runs in the output if the number of rounds to come is even
+      const bool here = ((rounds - r) & 1) == 0;
+      src = (here ? ws : out) + off;
+      dst = (here ? out : ws) + off + o;
+      if constexpr (KV) {
+        vsrc = (here ? vws : vout) + off;
+        vdst = (here ? vout : vws) + off + o;
+      }
+      count = &big[e].done;
+      const uint32_t *before = r ? count : &ctr->rest_done;
+      const uint32_t n = r ? tiles * r : no;
       if (tid == 0) {
-        while (__hip_atomic_load(&big[e].done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < tiles * r)
+        while (__hip_atomic_load(before, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n)
           __builtin_amdgcn_s_sleep(8);
         __threadfence();
       }
       __syncthreads();
+#pragma unroll
+      for (int i = 0; i < NI; ++i) addr[i] = off + o + (tile_pos<NI>(tid, i) < m ? tile_pos<NI>(tid, i) : 0u);
+    }
+    if (r == 0) {
+      sort_tile<typename Key<KT>::U, KV, NT, NI>(p, vp, addr, m, sk, sv, tid);
+      for (uint32_t i = tid; i < m; i += NT) {
+        dst[i] = final ? Key<KT>::unmap(sk[i]) : sk[i];
+        if constexpr (KV) vdst[i] = sv[i];
+      }
+    } else {
       // outputs o .. o+m-1 of the runs' pairs (whose lengths are whole tiles)
       const uint32_t w = CAP << (r - 1), a0 = o / (2 * w) * (2 * w);
       const uint32_t la = len - a0 < w ? len - a0 : w, b0 = a0 + la;
       const uint32_t lb = len - b0 < w ? len - b0 : w;
       if (tid < 128) {  // (two waves)
-        const uint32_t p = wave_merge_path(src + a0, la, src + b0, lb, o - a0 + (tid < 64 ? 0u : m));
-        if ((tid & 63) == 0) path[tid >> 6] = p;
+        const uint32_t x = wave_merge_path(src + a0, la, src + b0, lb, o - a0 + (tid < 64 ? 0u : m));
+        if ((tid & 63) == 0) path[tid >> 6] = x;
       }
       __syncthreads();
       const uint32_t pa = path[0], na = path[1] - pa, pb = o - a0 - pa;
@@ -1639,28 +1679,29 @@ __global__ __launch_bounds__(NT) void dist_rest_kernel(typename Key<KT>::U *ws, 
         if constexpr (KV) sv[i] = vsrc[from];
       }
       __syncthreads();
-      U k[kTileItems];
-      uint32_t v[KV ? kTileItems : 1];
-      const uint32_t at = tid * kTileItems;
-      if (at < m) merge_chunk<U, KV, kTileItems, false>(sk, sv, 0u, na, m, at, k, v);
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < kTileItems; ++i) {
-        if (at + i < m) {
-          sk[at + i] = k[i];
-          if constexpr (KV) sv[at + i] = v[i];
-        }
+      // NI outputs a thread, stored one by one (in registers until all are merged
+      // they would not fit beside the sort's)
+      const uint32_t at = tid * NI;
+      uint32_t lo = at > m - na ? at - (m - na) : 0, hi = at < na ? at : na;
+      while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (sk[mid] <= sk[na + at - 1 - mid]) lo = mid + 1;
+        else hi = mid;
       }
-      __syncthreads();
-      for (uint32_t i = tid; i < m; i += NT) {
-        dst[o + i] = r == rounds ? Key<KT>::unmap(sk[i]) : sk[i];
-        if constexpr (KV) vdst[o + i] = sv[i];
+      uint32_t xa = lo, xb = na + (at - lo);
+#pragma unroll 1
+      for (uint32_t i = at; i < at + NI && i < m; ++i) {
+        const uint32_t x = xa < na && (xb >= m || sk[xa] <= sk[xb]) ? xa++ : xb++;
+        dst[i] = final ? Key<KT>::unmap(sk[x]) : sk[x];
+        if constexpr (KV) vdst[i] = sv[x];
       }
     }
-    __syncthreads();
-    if (tid == 0) {
-      __threadfence();
-      atomicAdd(&big[e].done, 1u);
+    if (nbig) {  // (else no task waits)
+      __syncthreads();
+      if (tid == 0) {
+        __threadfence();
+        atomicAdd(count, 1u);
+      }
     }
   }
 }
@@ -1683,9 +1724,8 @@ hipError_t level_error_word(uint32_t **err) {
   return e != hipSuccess ? e : error_word(device, err);
 }
 
-hipError_t level_args(int kt, const DistPlan &d, int level, char *w, Level &L) {
-  const hipError_t e = level_error_word(&L.err);
-  if (e != hipSuccess) return e;
+Level level_args(int kt, const DistPlan &d, int level, char *w) {
+  Level L{};
   L.ctr = (DistCounters *)(w + d.off_ctr);
   L.nodes = (DistNode *)(w + d.off_nodes[level]);
   L.ranges = (DistRange *)(w + d.off_ranges[level]);
@@ -1700,7 +1740,7 @@ hipError_t level_args(int kt, const DistPlan &d, int level, char *w, Level &L) {
   L.kv = d.cap == kDistCapKV;
   L.max_copies = d.max_copies;
   L.leaves = (DistLeaf *)(w + d.off_leaves);
-  L.rest = (uint64_t *)(w + d.off_rest);
+  L.rest = (uint32_t *)(w + d.off_rest);
   L.big = (DistBig *)(w + d.off_big);
   L.level = (uint32_t)level;
   L.levels = (uint32_t)d.levels;
@@ -1721,7 +1761,7 @@ hipError_t level_args(int kt, const DistPlan &d, int level, char *w, Level &L) {
     L.max_next_ranges = d.max_ranges[level + 1];
     L.max_next_table = d.max_table[level + 1];
   }
-  return hipSuccess;
+  return L;
 }
 
 // Level 1 reads raw keys of type kt; later levels read mapped keys, which are
@@ -1742,18 +1782,15 @@ template <typename F> hipError_t with_type(int kt, F &&f) {
 
 }  // namespace
 
-hipError_t launch_dist_segments(const DistPlan &d, const uint64_t *seg_off, uint64_t n,
-                                uint32_t small0, uint32_t small1, uint64_t longest, char *w,
-                                hipStream_t s) {
+hipError_t launch_dist_segments(const DistPlan &d, const uint64_t *seg_off, uint64_t n, uint64_t merged,
+                                uint64_t longest, char *w, hipStream_t s) {
   SegDistArgs a{};
   if (const hipError_t e = level_error_word(&a.err); e != hipSuccess) return e;
   a.off = seg_off;
   a.n_segs = d.n_segs;
   a.n = n;
+  a.merged = merged;
   a.longest = longest;
-  a.small0 = small0;
-  a.small1 = small1;
-  a.cap = d.cap;
   a.target = d.target;
   a.rl = d.rl[1];
   a.root_p = d.root_p;
@@ -1762,21 +1799,17 @@ hipError_t launch_dist_segments(const DistPlan &d, const uint64_t *seg_off, uint
   a.ctr = (DistCounters *)(w + d.off_ctr);
   a.nodes = (DistNode *)(w + d.off_nodes[1]);
   a.ranges = (DistRange *)(w + d.off_ranges[1]);
-  a.leaves = (DistLeaf *)(w + d.off_leaves);
-  a.small = (uint32_t *)(w + d.off_small);
   a.max_nodes = d.max_nodes[1];
   a.max_ranges = d.max_ranges[1];
   a.max_cols = d.max_cols;
   a.max_table = d.max_table[1];
-  a.max_leaves = d.max_leaves;
   hipLaunchKernelGGL(seg_dist_plan_kernel, dim3(1), dim3(1024), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_dist_sample(int kt, const DistPlan &d, int level, const DistBufs &b, uint64_t n,
                               char *w, hipStream_t s) {
-  Level L{};
-  if (const hipError_t e = level_args(kt, d, level, w, L); e != hipSuccess) return e;
+  Level L = level_args(kt, d, level, w);
   if (level == 1 && !d.n_segs) {
     L.root_len = (uint32_t)n;
     L.root_p = d.root_p;
@@ -1811,8 +1844,7 @@ hipError_t launch_dist_sample(int kt, const DistPlan &d, int level, const DistBu
 
 hipError_t launch_dist_count(int kt, const DistPlan &d, int level, const DistBufs &b, char *w,
                              hipStream_t s) {
-  Level L{};
-  if (const hipError_t e = level_args(kt, d, level, w, L); e != hipSuccess) return e;
+  Level L = level_args(kt, d, level, w);
   return with_type(level_type(kt, level), [&](auto c) {
     constexpr int KT = decltype(c)::value;
     using U = typename Key<KT>::U;
@@ -1823,8 +1855,8 @@ hipError_t launch_dist_count(int kt, const DistPlan &d, int level, const DistBuf
 }
 
 hipError_t launch_dist_scan(int kt, const DistPlan &d, int level, char *w, hipStream_t s) {
-  Level L{};
-  if (const hipError_t e = level_args(kt, d, level, w, L); e != hipSuccess) return e;
+  Level L = level_args(kt, d, level, w);
+  if (const hipError_t e = level_error_word(&L.err); e != hipSuccess) return e;
   const int columns = level == 1 && d.levels > 1 && !d.n_segs && !d.tiled(level);
   const int summed = columns || (d.tiled(level) && level < d.levels);
   if (columns) {
@@ -1843,8 +1875,7 @@ hipError_t launch_dist_scan(int kt, const DistPlan &d, int level, char *w, hipSt
 
 hipError_t launch_dist_scatter(int kt, bool kv, const DistPlan &d, int level, const DistBufs &b,
                                char *w, hipStream_t s) {
-  Level L{};
-  if (const hipError_t e = level_args(kt, d, level, w, L); e != hipSuccess) return e;
+  Level L = level_args(kt, d, level, w);
   const uint32_t *vsrc = level_vsrc(d, b, level);
   void *dst = level_to_out(d, level) ? b.out : b.ws;
   uint32_t *vdst = level_to_out(d, level) ? b.vout : b.vws;
@@ -1864,8 +1895,7 @@ hipError_t launch_dist_scatter(int kt, bool kv, const DistPlan &d, int level, co
 
 hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, int level, const DistBufs &b,
                                  char *w, hipStream_t s) {
-  Level L{};
-  if (const hipError_t e = level_args(kt, d, level, w, L); e != hipSuccess) return e;
+  Level L = level_args(kt, d, level, w);
   const uint32_t *vsrc = level_vsrc(d, b, level);
   void *dst = level_to_out(d, level) ? b.out : b.ws;
   uint32_t *vdst = level_to_out(d, level) ? b.vout : b.vws;
@@ -1889,8 +1919,7 @@ hipError_t launch_dist_partition(int kt, bool kv, const DistPlan &d, int level, 
 }
 
 hipError_t launch_dist_pieces(int kt, const DistPlan &d, int level, char *w, hipStream_t s) {
-  Level L{};
-  if (const hipError_t e = level_args(kt, d, level, w, L); e != hipSuccess) return e;
+  Level L = level_args(kt, d, level, w);
   // a workgroup a bucket for one array; segments are shorter
   hipLaunchKernelGGL(dist_pieces_kernel, dim3(d.max_nodes[level], d.max_nodes[level] > 1 ? 16 : kDistSlots),
                      dim3(kPiecesThreads), 0, s, L);
@@ -1899,8 +1928,8 @@ hipError_t launch_dist_pieces(int kt, const DistPlan &d, int level, char *w, hip
 
 hipError_t launch_dist_leaves(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
                               hipStream_t s) {
-  Level L{};
-  if (const hipError_t e = level_args(kt, d, d.levels, w, L); e != hipSuccess) return e;
+  Level L = level_args(kt, d, d.levels, w);
+  if (const hipError_t e = level_error_word(&L.err); e != hipSuccess) return e;
   const dim3 grid(d.leaf_grid);
   return with_type(kt, [&](auto c) {
     constexpr int KT = decltype(c)::value;
@@ -1910,31 +1939,29 @@ hipError_t launch_dist_leaves(int kt, bool kv, const DistPlan &d, const DistBufs
       // threads of 16 keys left it 12 waves; 1069 against 1001 us at 2^27 u64.
       // Keys-only leaves fill two workgroups' LDS, and 1024 threads of 8 keys
       // measured slower there, 1632 against 1487 us at 2^28 int64.)
-      hipLaunchKernelGGL((dist_leaf_kernel<KT, true, 512, 8, 6>), grid, dim3(512), 0, s, (const U *)b.in,
-                         b.vin, (const U *)b.ws, b.vws, (U *)b.out, b.vout, L);
+      hipLaunchKernelGGL((dist_leaf_kernel<KT, true, 512, 8, 6>), grid, dim3(512), 0, s, (const U *)b.ws,
+                         b.vws, (U *)b.out, b.vout, L);
     else
-      hipLaunchKernelGGL((dist_leaf_kernel<KT, false, 512, 16, 4>), grid, dim3(512), 0, s, (const U *)b.in,
-                         b.vin, (const U *)b.ws, b.vws, (U *)b.out, b.vout, L);
+      hipLaunchKernelGGL((dist_leaf_kernel<KT, false, 512, 16, 4>), grid, dim3(512), 0, s, (const U *)b.ws,
+                         b.vws, (U *)b.out, b.vout, L);
     return hipGetLastError();
   });
 }
 
 hipError_t launch_dist_rest(int kt, bool kv, const DistPlan &d, const DistBufs &b, char *w,
                             hipStream_t s) {
-  DistCounters *ctr = (DistCounters *)(w + d.off_ctr);
-  const uint64_t *rest = (const uint64_t *)(w + d.off_rest);
-  DistBig *big = (DistBig *)(w + d.off_big);
-  // workgroups loop over the list: usually nearly empty
+  Level L = level_args(kt, d, d.levels, w);
+  // workgroups claim tasks as long as there are any: usually none
   const dim3 grid(std::min<uint32_t>(d.max_rest, 768));
   return with_type(kt, [&](auto c) {
     constexpr int KT = decltype(c)::value;
     using U = typename Key<KT>::U;
     if (kv)
-      hipLaunchKernelGGL((dist_rest_kernel<KT, true, 256>), grid, dim3(256), 0, s, (U *)b.ws, b.vws,
-                         (U *)b.out, b.vout, rest, big, ctr);
+      hipLaunchKernelGGL((dist_rest_kernel<KT, true, 512, 8, 6>), grid, dim3(512), 0, s, (U *)b.ws, b.vws,
+                         (U *)b.out, b.vout, L);
     else
-      hipLaunchKernelGGL((dist_rest_kernel<KT, false, 512>), grid, dim3(512), 0, s, (U *)b.ws, b.vws,
-                         (U *)b.out, b.vout, rest, big, ctr);
+      hipLaunchKernelGGL((dist_rest_kernel<KT, false, 512, 16, 4>), grid, dim3(512), 0, s, (U *)b.ws, b.vws,
+                         (U *)b.out, b.vout, L);
     return hipGetLastError();
   });
 }

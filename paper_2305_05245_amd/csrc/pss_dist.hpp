@@ -77,11 +77,11 @@ struct DistCounters {
   uint32_t nodes[kDistMaxLevels + 1], ranges[kDistMaxLevels + 1];
   uint32_t cols[kDistMaxLevels + 1], table[kDistMaxLevels + 1];
   uint32_t leaves, rest, big;
-  uint32_t next_task;  // of the big buckets' sorts
+  // the last kernel's: crowded leaves sorted, and tasks claimed
+  uint32_t rest_done, next_task;
   // gathered: buckets of the level before that are not cut again, and the most
   // ranges of one that is
   uint32_t copies, most_ranges;
-  uint32_t small[2];  // segments of the two smallest classes
   uint32_t failed;    // a bound of the plan did not hold
 };
 
@@ -91,7 +91,7 @@ constexpr uint32_t kLeafEqual = 1u << 16;  // one key value: unmapped, not sorte
 constexpr uint32_t kLeafMove = 1u << 17;   // part of a big bucket: moved to the output
 constexpr uint32_t kLeafInner = 1u << 18;  // the splitters around it bound its keys
 constexpr int kLeafSrcShift = 19;          // where its keys are:
-constexpr uint32_t kSrcWs = 0, kSrcOut = 1, kSrcPieces = 2, kSrcIn = 3;  // (kSrcIn: not mapped)
+constexpr uint32_t kSrcWs = 0, kSrcOut = 1, kSrcPieces = 2;
 
 // Host bounds and workspace layout (byte offsets) of one distribution sort.
 struct DistPlan {
@@ -112,7 +112,7 @@ struct DistPlan {
   uint32_t leaf_grid = 0;  // workgroups of the leaf kernel: the leaves to expect
   size_t off_ctr = 0, off_nodes[kDistMaxLevels + 1] = {}, off_ranges[kDistMaxLevels + 1] = {};
   size_t off_ptable = 0, off_pre = 0;  // gathered: the level before's table, keys before every 8 tiles
-  size_t off_spl = 0, off_start = 0, off_table = 0, off_leaves = 0, off_rest = 0, off_big = 0, off_small = 0;
+  size_t off_spl = 0, off_start = 0, off_table = 0, off_leaves = 0, off_rest = 0, off_big = 0;
   size_t end = 0;  // first byte after the distribution's arrays
 };
 
@@ -129,12 +129,13 @@ inline uint32_t dist_root(uint64_t units, int levels) {
 }
 
 // Plan of n keys in arrays of at most max_len > cap keys (one array: max_len =
-// n and n_segs = 0), laid out from byte offset `off` on.  One level reaches
+// n and n_segs = 0; of n_segs segments, those above min_len >= cap keys), laid
+// out from byte offset `off` on.  One level reaches
 // kDistMaxPicks buckets of the target size; two levels are kept up to the
 // count where a first-level bucket half as large again as the mean still gets
 // its share of second-level buckets.
-inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb, bool kv, size_t off,
-                          bool gather) {
+inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, uint64_t min_len, int kb, bool kv,
+                          size_t off, bool gather) {
   DistPlan d;
   d.cap = kv ? kDistCapKV : kDistCap;
   d.target = kv ? kDistTargetKV : kDistTarget;
@@ -144,10 +145,9 @@ inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb,
   d.gather = gather && d.levels > 1 && max_len >= kDistGatherMin;
   d.root_p = std::max<uint32_t>(2, std::min(kDistMaxPicks, dist_root(units, d.levels)));
   auto tiles = [](uint64_t x) { return (x + kDistTile - 1) / kDistTile; };
-  // (segments up to cap keys are no nodes)
-  uint64_t nodes = n_segs ? std::min<uint64_t>(n_segs, n / d.cap + 1) : 1;
+  uint64_t nodes = n_segs ? std::min<uint64_t>(n_segs, n / min_len + 1) : 1;
   uint64_t cols = n_segs ? 2 * (n / d.target) + 4 * nodes : std::min(kDistSlots, 2 * d.root_p);
-  uint64_t leaves = n_segs, max_cols = 0, table_bytes = 0, ptable_bytes = 0;
+  uint64_t leaves = 0, max_cols = 0, table_bytes = 0, ptable_bytes = 0;
   for (int l = 1; l <= d.levels; ++l) {
     const bool tiled = d.tiled(l);
     // A first level that scatters covers the array with two ranges a CU
@@ -176,7 +176,7 @@ inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb,
   }
   d.max_cols = (uint32_t)max_cols;
   d.max_leaves = (uint32_t)(leaves + n / d.cap + 1);
-  const uint64_t expect = n / d.target + n / d.target / 8 + d.max_nodes[d.levels] + n_segs + 64;
+  const uint64_t expect = n / d.target + n / d.target / 8 + d.max_nodes[d.levels] + 64;
   d.leaf_grid = (uint32_t)((std::min<uint64_t>(d.max_leaves, expect) + 7) / 8 * 8);
   d.max_rest = d.max_leaves;
   d.max_big = (uint32_t)(n / d.cap);
@@ -196,9 +196,8 @@ inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, int kb,
   d.off_ptable = take((size_t)ptable_bytes);
   d.off_pre = take((size_t)ptable_bytes / 4);  // a uint32 for every 8 entries
   d.off_leaves = take((size_t)d.max_leaves * sizeof(DistLeaf));
-  d.off_rest = take((size_t)d.max_rest * 8);
+  d.off_rest = take((size_t)d.max_rest * 4);
   d.off_big = take((size_t)d.max_big * sizeof(DistBig));
-  d.off_small = take((size_t)n_segs * 8);
   d.end = off;
   return d;
 }
@@ -214,16 +213,13 @@ struct DistBufs {
 };
 
 // Segmented: reads the segment offsets, and writes the first level's nodes and
-// ranges, the leaves of segments of at most cap keys above small1, and the
-// lists of those up to small0 and small1 (sorted by launch_dist_small).  The
-// steps of a level and the two kernels that end the sort follow.  Declared weak
-// so that a host-only program can link the plan without the device code.
+// ranges, of the segments above `merged` keys; those above `longest` are left out
+// (the merge passes' planner reports them).  The steps of a level and the two
+// kernels that end the sort follow.  Declared weak so that a host-only program can
+// link the plan without the device code.
 #define PSS_WEAK __attribute__((weak))
 PSS_WEAK hipError_t launch_dist_segments(const DistPlan &d, const uint64_t *seg_off, uint64_t n,
-                                         uint32_t small0, uint32_t small1, uint64_t longest, char *w,
-                                         hipStream_t s);
-PSS_WEAK hipError_t launch_dist_small(int kt, bool kv, const DistPlan &d, const DistBufs &b,
-                                      const uint64_t *seg_off, char *w, hipStream_t s);
+                                         uint64_t merged, uint64_t longest, char *w, hipStream_t s);
 PSS_WEAK hipError_t launch_dist_sample(int kt, const DistPlan &d, int level, const DistBufs &b,
                                        uint64_t n, char *w, hipStream_t s);
 // before the last level

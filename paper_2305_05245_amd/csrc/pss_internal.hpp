@@ -212,6 +212,8 @@ struct SegPlanPtrs {
   uint32_t *npass;
   uint64_t *rows[kMaxSegPasses], *parts[kMaxSegPasses];
   uint64_t *srows[kMaxSegPasses], *sparts[kMaxSegPasses];
+  // segments above `merged` are left out, and reported if above `longest`
+  uint64_t merged, longest;
 };
 
 // Second buffer set of a segmented merge (X_j not in the primary buffers).

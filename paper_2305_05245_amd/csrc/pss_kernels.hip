@@ -53,8 +53,6 @@ template <typename U> struct TileArgs {
   const uint64_t *seg_off, *tiles, *soff;
   const uint32_t *npass;
   uint32_t n_segs;
-  // a list of whole segments of at most one tile each, and its length
-  const uint32_t *list, *count;
 };
 
 template <int KT, bool KV, int THREADS>
@@ -74,14 +72,7 @@ __global__ __launch_bounds__(THREADS) void tile_sort_kernel(
   U *out = ta.out, *samples = ta.samples;
   uint32_t *vout = ta.vout;
   int final_pass = ta.final_pass;
-  if (ta.list) {
-    if (t >= *ta.count) return;
-    const uint32_t sg = ta.list[t];
-    start = ta.seg_off[sg];
-    len = (uint32_t)(ta.seg_off[sg + 1] - start);
-    final_pass = 1;
-    samples = nullptr;
-  } else if (ta.seg_off) {
+  if (ta.seg_off) {
     if (t >= ta.tiles[ta.n_segs]) return;
     const uint32_t sg = seg_find(ta.tiles, ta.n_segs, t);
     const uint64_t j = t - ta.tiles[sg];
@@ -1915,6 +1906,7 @@ __global__ __launch_bounds__(1024) void seg_plan_kernel(const uint64_t *__restri
                                                         uint32_t n_segs, uint64_t n,
                                                         SegPlanArrays pa, uint32_t small0,
                                                         uint32_t small1, uint32_t max_passes,
+                                                        uint64_t merged, uint64_t longest,
                                                         uint32_t fan_log2, uint32_t tile,
                                                         uint32_t part) {
   __shared__ uint64_t wsum[17];
@@ -1953,8 +1945,8 @@ __global__ __launch_bounds__(1024) void seg_plan_kernel(const uint64_t *__restri
       while (((uint64_t)1 << bits) < tiles) ++bits;
       np = (bits + fan_log2 - 1) / fan_log2;
     }
-    if (np > max_passes) {  // the host bound on passes was too small
-      atomicOr(&over, 1u);
+    if (L > merged) {  // the distribution sort's, or above the host's bound
+      if (L > longest) atomicOr(&over, 1u);
       np = 0;
       cls = -1;
     }
@@ -2072,7 +2064,7 @@ hipError_t launch_seg_plan(const uint64_t *seg_off, uint32_t n_segs, uint64_t n,
     pa.sparts[q] = pp.sparts[q];
   }
   hipLaunchKernelGGL(seg_plan_kernel, dim3(1), dim3(1024), 0, s, seg_off, n_segs, n, pa, small0,
-                     small1, max_passes, fan_log2, tile, part);
+                     small1, max_passes, pp.merged, pp.longest, fan_log2, tile, part);
   return hipGetLastError();
 }
 
@@ -2110,28 +2102,6 @@ hipError_t launch_seg_tile_sorts(int kt, bool kv, const void *in, const uint32_t
     if (kv && tile == (uint32_t)kTileKV) return go_tile<KT, true, kTileKVThreads>(in, vin, ta, grid, s);
     return kv ? go_tile<KT, true, kTileThreads>(in, vin, ta, grid, s)
               : go_tile<KT, false, kTileThreads>(in, vin, ta, grid, s);
-  });
-}
-
-hipError_t launch_dist_small(int kt, bool kv, const DistPlan &d, const DistBufs &b,
-                             const uint64_t *seg_off, char *w, hipStream_t s) {
-  const DistCounters *ctr = (const DistCounters *)(w + d.off_ctr);
-  return dispatch_kt(kt, [&](auto ktc) {
-    constexpr int KT = decltype(ktc)::value;
-    using U = typename Key<KT>::U;
-    TileArgs<U> ta{};
-    ta.out = (U *)b.out;
-    ta.vout = b.vout;
-    ta.seg_off = seg_off;
-    ta.list = (const uint32_t *)(w + d.off_small);
-    ta.count = &ctr->small[0];
-    hipError_t e = kv ? go_tile<KT, true, kSmallThreads0>(b.in, b.vin, ta, d.n_segs, s)
-                      : go_tile<KT, false, kSmallThreads0>(b.in, b.vin, ta, d.n_segs, s);
-    if (e != hipSuccess) return e;
-    ta.list += d.n_segs;
-    ta.count = &ctr->small[1];
-    return kv ? go_tile<KT, true, kSmallThreads1>(b.in, b.vin, ta, d.n_segs, s)
-              : go_tile<KT, false, kSmallThreads1>(b.in, b.vin, ta, d.n_segs, s);
   });
 }
 

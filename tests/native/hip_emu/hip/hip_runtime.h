@@ -195,13 +195,13 @@ template <typename T> T from_lane(T v, uint32_t lane) {
 
 inline void __syncthreads() { emu::yield(emu::kBlock); }
 inline int __syncthreads_or(int x) {
-  static uint32_t any[2];
-  static uint32_t turn = 0;
-  any[turn & 1] |= x != 0;
+  static int any;
+  any |= x != 0;
   __syncthreads();
-  const int r = any[turn & 1] != 0;
-  __syncthreads();  // all have read it
-  any[0] = any[1] = 0;
+  const int r = any;
+  __syncthreads();
+  any = 0;  // (all have read it, and none sets it again before the next barrier)
+  __syncthreads();
   return r;
 }
 inline uint32_t __lane() { return emu::cur % 64; }

@@ -82,25 +82,25 @@ void segments(const std::vector<uint64_t> &lens, uint64_t bound, bool kv, uint64
 // A segment longer than the bound on the segment length allows is left out and
 // reported; the others are sorted, whichever wave finds it first.
 void segment_left_out() {
-  for (uint64_t bound : {8192, 9000}) {  // no segment above one tile, and some
+  // no segment above one tile, some (merged), and one that is distributed
+  const uint64_t bounds[] = {4096, 9000, 140000}, left_out[] = {9000, 140000, 17000000};
+  for (int i = 0; i < 3; ++i) {
     std::vector<uint64_t> lens(200, 70);
-    for (size_t s = 0; s < lens.size(); s += 23) lens[s] = 5000;
-    lens[130] = bound;
-    lens[70] = 300000;
-    segments(lens, bound, false, 0, 16, [](size_t s) { return s != 70; });
+    for (size_t s = 0; s < lens.size(); s += 23) lens[s] = 3000;
+    lens[130] = bounds[i];
+    lens[70] = left_out[i];
+    segments(lens, bounds[i], true, 0, 16, [](size_t s) { return s != 70; });
   }
 }
 
 // One distribution sort of uint64 keys by the launches of plan d (whose arrays
 // end at byte `bytes` of the workspace, after keys and values); true if the
 // output is sorted.
-bool distribution(const pss::DistPlan &d, size_t bytes, uint64_t n, bool kv, uint64_t distinct) {
-  std::vector<uint64_t> keys(n), out(n);
+bool distribution(const pss::DistPlan &d, size_t bytes, const std::vector<uint64_t> &keys, bool kv) {
+  const uint64_t n = keys.size();
+  std::vector<uint64_t> out(n);
   std::vector<uint32_t> vals(n), vout(n);
-  for (uint64_t i = 0; i < n; ++i) {
-    keys[i] = distinct ? rng() % distinct * 0x9E3779B97F4A7C15ull : rng();
-    vals[i] = (uint32_t)i;
-  }
+  for (uint64_t i = 0; i < n; ++i) vals[i] = (uint32_t)i;
   Buffer ws(bytes), kws(n * 8), vws(n * 4);
   const pss::DistBufs b{keys.data(), vals.data(), kws.p, (uint32_t *)vws.p, out.data(), vout.data()};
   const int kt = PSS_U64;
@@ -125,6 +125,12 @@ bool distribution(const pss::DistPlan &d, size_t bytes, uint64_t n, bool kv, uin
   return true;
 }
 
+bool distribution(const pss::DistPlan &d, size_t bytes, uint64_t n, bool kv, uint64_t distinct) {
+  std::vector<uint64_t> keys(n);
+  for (auto &k : keys) k = distinct ? rng() % distinct * 0x9E3779B97F4A7C15ull : rng();
+  return distribution(d, bytes, keys, kv);
+}
+
 // A plan with too little room for its buckets: nothing is written past its
 // arrays, and the error word says so.
 void plan_bounds() {
@@ -132,7 +138,7 @@ void plan_bounds() {
   for (int shape = 0; shape < 3; ++shape)  // one level, two that scatter, two that gather
     for (bool kv : {false, true}) {
       const uint64_t len = shape == 0 ? n : shape == 1 ? 1 << 22 : 1 << 25;
-      pss::DistPlan d = pss::dist_plan(n, len, 0, 8, kv, 0, shape == 2);
+      pss::DistPlan d = pss::dist_plan(n, len, 0, 0, 8, kv, 0, shape == 2);
       CHECK(d.levels == (shape == 0 ? 1 : 2) && d.gather == (shape == 2), "shape %d", shape);
       if (shape) d.root_p = 6;  // (keys for a second level)
       const size_t bytes = d.end;
@@ -163,13 +169,75 @@ void big_buckets() {
   for (uint64_t n : {30001, 65536, 65537, 81921, 150001})
     for (bool kv : {false, true})
       for (uint64_t distinct : {0, 300, 20000}) {
-        pss::DistPlan d = pss::dist_plan(n, n, 0, 8, kv, 0, false);
+        pss::DistPlan d = pss::dist_plan(n, n, 0, 0, 8, kv, 0, false);
         d.root_p = 2;
         const size_t bytes = d.end;
         CHECK(distribution(d, bytes, n, kv, distinct), "%llu keys, %s, %llu values", (unsigned long long)n,
               kv ? "values" : "keys", (unsigned long long)distinct);
         CHECK(device_error() == 0, "device error word");
       }
+}
+
+// Segments on both sides of the longest that is merged, in calls with a bound on
+// the length and without, where their mean length decides.
+void segment_routes() {
+  const std::vector<uint64_t> shorter = {100, 4096, 4097, 131071, 0, 131072, 5000, 9000};
+  const std::vector<uint64_t> some = {100, 4096, 4097, 131071, 0, 131072, 131073, 9000};
+  const std::vector<uint64_t> longer = {131073, 131072, 270000};
+  for (uint64_t distinct : {0, 900}) {
+    segments(shorter, 131072, true, distinct, 0, [](size_t) { return true; });
+    segments(some, 131073, true, distinct, 0, [](size_t) { return true; });
+    segments(some, 0, true, distinct, 0, [](size_t) { return true; });
+    segments(longer, 0, true, distinct, 0, [](size_t) { return true; });
+  }
+}
+
+// One leaf of n keys with `copies` of each: an array whose samples all fall on a
+// smaller key that is most of it, so that the n keys are one bucket.
+void one_leaf(uint64_t n, uint64_t copies, bool small, bool kv) {
+  std::vector<uint64_t> keys;
+  for (uint64_t i = 0; i < n; ++i) keys.push_back(1 + (small ? i / copies : i / copies * 0x9E3779B97F4A7C15ull >> 1));
+  keys.resize(5 * n, 0);
+  std::shuffle(keys.begin(), keys.end(), rng);
+  pss::DistPlan d = pss::dist_plan(keys.size(), keys.size(), 0, 0, 8, kv, 0, false);
+  const size_t bytes = d.end;
+  d.root_p = 2;
+  CHECK(distribution(d, bytes, keys, kv), "leaf of %llu keys, %llu copies, %s, %s", (unsigned long long)n,
+        (unsigned long long)copies, small ? "small" : "wide", kv ? "values" : "keys");
+  CHECK(device_error() == 0, "device error word");
+}
+
+// Leaves at the limits of a bin's keys and of the list of bins.
+void leaf_bins() {
+  for (uint64_t copies : {1, 2, 3, 6, 15, 16, 17, 96, 97, 255, 256})
+    for (bool small : {false, true})
+      for (bool kv : {false, true})
+        for (uint64_t n : kv ? std::vector<uint64_t>{4093, 4096} : std::vector<uint64_t>{8191, 8192})
+          one_leaf(n, copies, small, kv);
+}
+
+// Leaves whose bins are crowded by values of many copies, of all lengths: in
+// pieces, in the output and in the workspace (buckets of a first level that
+// scatters or gathers); and with big buckets among them.
+void crowded_leaves() {
+  for (uint64_t copies : {25, 50, 300, 3000})
+    for (bool kv : {false, true}) {
+      for (uint64_t l : {1023, 1024, 1025, 2500, 4096, 5000, 7169})
+        if (!kv || l <= 4096) one_leaf(l, copies, false, kv);
+      const uint64_t n = 100003;
+      for (int shape = 0; shape < 3; ++shape) {
+        const uint64_t len = shape == 0 ? n : shape == 1 ? 1 << 22 : 1 << 25;
+        for (uint32_t root : {3u, 45u}) {
+          pss::DistPlan d = pss::dist_plan(n, len, 0, 0, 8, kv, 0, shape == 2);
+          const size_t bytes = d.end;
+          d.root_p = root;
+          if (shape == 0 && root > 3) continue;
+          CHECK(distribution(d, bytes, n, kv, n / copies), "shape %d, root %u, %s, %llu copies", shape, root,
+                kv ? "values" : "keys", (unsigned long long)copies);
+          CHECK(device_error() == 0, "device error word");
+        }
+      }
+    }
 }
 
 }  // namespace
@@ -179,7 +247,8 @@ int main(int argc, char **argv) {
   emu::seed = argc > 2 ? (uint32_t)std::atoi(argv[2]) : 0;
   if (pss_create(0, &ctx) != PSS_OK) return 2;
   const struct { const char *name; void (*run)(); } cases[] = {
-      {"segment_left_out", segment_left_out}, {"plan_bounds", plan_bounds}, {"big_buckets", big_buckets}};
+      {"segment_left_out", segment_left_out}, {"plan_bounds", plan_bounds}, {"big_buckets", big_buckets},
+      {"crowded_leaves", crowded_leaves}, {"leaf_bins", leaf_bins}, {"segment_routes", segment_routes}};
   bool found = false;
   for (const auto &c : cases) {
     if (name != c.name) continue;

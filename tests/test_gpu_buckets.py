@@ -49,3 +49,48 @@ def test_time_of_missed_buckets(kv):
     if kv:
         assert np.array_equal(vout, vals[perm])
     assert t < 20 * base
+
+
+@pytest.mark.parametrize("key", ["i64", "f32"])
+@pytest.mark.parametrize("kv", [False, True], ids=["keys", "kv"])
+def test_time_of_crowded_leaves(key, kv):
+    """Segments of 100003 keys of 1000 widely spaced values: every leaf has bins of
+    many equal keys.  Over the time of random keys each leaf may cost what a tile
+    sort of as many keys costs, measured on segments of one short tile, and a
+    tenth more."""
+    import torch
+
+    import paper_2305_05245_amd as pss
+
+    n, seg = 160 * 100_003, 100_003
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    if key == "i64":
+        random = torch.randint(-2**63, 2**63 - 1, (n,), dtype=torch.int64, device="cuda", generator=g)
+    else:
+        random = torch.rand(n, dtype=torch.float32, device="cuda", generator=g)
+    some = random[:1000].clone()
+    crowded = some[torch.randint(0, 1000, (n,), device="cuda", generator=g)].contiguous()
+    vals = torch.arange(n, dtype=torch.int32, device="cuda") if kv else None
+
+    def seconds(keys, length):
+        offs = torch.arange(0, n // length * length + 1, length, dtype=torch.int64, device="cuda")
+        times = []
+        for _ in range(9):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            out, vout = pss.segmented_sort(keys, offs, vals, key_type=key, tuning={}, max_seg_len=length)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return sorted(times)[4], out, vout
+
+    announce("crowded leaves", key, "kv" if kv else "keys")
+    tiles, base = seconds(random, 4096)[0], seconds(random, seg)[0]
+    t, out, vout = seconds(crowded, seg)
+    print(f"random {base * 1e3:.0f} us, crowded {t * 1e3:.0f} us, tile sorts {tiles * 1e3:.0f} us")
+    want, at = torch.sort(crowded.view(-1, seg), dim=1, stable=True)
+    assert torch.equal(out, want.view(-1))
+    if kv:
+        assert torch.equal(vout, torch.gather(vals.view(-1, seg), 1, at).view(-1))
+    assert t < 1.1 * (base + tiles)

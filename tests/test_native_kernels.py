@@ -67,3 +67,9 @@ def test_plan_bounds(program, seed):
 @pytest.mark.parametrize("seed", [0, 1, 2])
 def test_big_buckets(program, seed):
     run(program, "big_buckets", seed)
+
+
+@pytest.mark.parametrize("case", ["crowded_leaves", "leaf_bins", "segment_routes"])
+@pytest.mark.parametrize("seed", [0, 1])
+def test_leaves_and_segments(program, case, seed):
+    run(program, case, seed)

@@ -131,10 +131,10 @@ struct Plan {
 
 // The distribution plan whose arrays fit between `off` and `total`, gathered
 // if they do.
-pss::DistPlan plan_dist(uint64_t n, uint64_t max_len, uint32_t n_segs, uint64_t min_len, int kb, bool kv,
-                        size_t off, size_t total) {
-  pss::DistPlan d = pss::dist_plan(n, max_len, n_segs, min_len, kb, kv, off, true);
-  if (d.end > total) d = pss::dist_plan(n, max_len, n_segs, min_len, kb, kv, off, false);
+pss::DistPlan plan_dist(uint64_t n, uint64_t max_len, uint32_t n_segs, uint64_t min_len, uint64_t longest,
+                        int kb, bool kv, size_t off, size_t total) {
+  pss::DistPlan d = pss::dist_plan(n, max_len, n_segs, min_len, longest, kb, kv, off, true);
+  if (d.end > total) d = pss::dist_plan(n, max_len, n_segs, min_len, longest, kb, kv, off, false);
   d.on = d.end <= total;
   return d;
 }
@@ -235,7 +235,7 @@ pss_status make_plan(pss_key_t key, pss_val_t val, uint64_t n, uint32_t n_blocks
   }
   p->total = off;
   if (!p->paper && n >= dist_min_keys(key) && pss::launch_dist_sample) {
-    p->dist = plan_dist(n, n, 0, 0, p->kb, p->kv, p->off_table, p->total);
+    p->dist = plan_dist(n, n, 0, 0, n, p->kb, p->kv, p->off_table, p->total);
   }
   return PSS_OK;
 }
@@ -1132,7 +1132,7 @@ pss_status make_seg_plan(const pss_ctx *ctx, pss_key_t key, pss_val_t val, uint6
   const bool bounded = tu && tu->max_seg_len;
   if (max_len > sp->merged && (bounded || n / std::max<uint64_t>(S, 1) > sp->merged) &&
       pss::launch_dist_segments)
-    sp->dist = plan_dist(n, max_len, n_segs, sp->merged, kb, kv, sp->off_plan, sp->total);
+    sp->dist = plan_dist(n, max_len, n_segs, sp->merged, sp->longest, kb, kv, sp->off_plan, sp->total);
   if (!sp->dist.on) {
     sp->merge_passes = sp->max_passes;
     sp->merged = sp->longest;

@@ -130,12 +130,13 @@ inline uint32_t dist_root(uint64_t units, int levels) {
 
 // Plan of n keys in arrays of at most max_len > cap keys (one array: max_len =
 // n and n_segs = 0; of n_segs segments, those above min_len >= cap keys), laid
-// out from byte offset `off` on.  One level reaches
+// out from byte offset `off` on.  Arrays of up to `longest` keys are sorted too,
+// with as many first-level buckets as they need, or kDistMaxPicks.  One level reaches
 // kDistMaxPicks buckets of the target size; two levels are kept up to the
 // count where a first-level bucket half as large again as the mean still gets
 // its share of second-level buckets.
-inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, uint64_t min_len, int kb, bool kv,
-                          size_t off, bool gather) {
+inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, uint64_t min_len,
+                          uint64_t longest, int kb, bool kv, size_t off, bool gather) {
   DistPlan d;
   d.cap = kv ? kDistCapKV : kDistCap;
   d.target = kv ? kDistTargetKV : kDistTarget;
@@ -143,7 +144,8 @@ inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, uint64_
   const uint64_t units = (max_len + d.target - 1) / d.target;
   d.levels = units <= kDistMaxPicks ? 1 : units <= 144000 ? 2 : 3;
   d.gather = gather && d.levels > 1 && max_len >= kDistGatherMin;
-  d.root_p = std::max<uint32_t>(2, std::min(kDistMaxPicks, dist_root(units, d.levels)));
+  d.root_p = std::max<uint32_t>(
+      2, std::min(kDistMaxPicks, dist_root((longest + d.target - 1) / d.target, d.levels)));
   auto tiles = [](uint64_t x) { return (x + kDistTile - 1) / kDistTile; };
   uint64_t nodes = n_segs ? std::min<uint64_t>(n_segs, n / min_len + 1) : 1;
   uint64_t cols = n_segs ? 2 * (n / d.target) + 4 * nodes : std::min(kDistSlots, 2 * d.root_p);

@@ -138,7 +138,7 @@ void plan_bounds() {
   for (int shape = 0; shape < 3; ++shape)  // one level, two that scatter, two that gather
     for (bool kv : {false, true}) {
       const uint64_t len = shape == 0 ? n : shape == 1 ? 1 << 22 : 1 << 25;
-      pss::DistPlan d = pss::dist_plan(n, len, 0, 0, 8, kv, 0, shape == 2);
+      pss::DistPlan d = pss::dist_plan(n, len, 0, 0, len, 8, kv, 0, shape == 2);
       CHECK(d.levels == (shape == 0 ? 1 : 2) && d.gather == (shape == 2), "shape %d", shape);
       if (shape) d.root_p = 6;  // (keys for a second level)
       const size_t bytes = d.end;
@@ -169,7 +169,7 @@ void big_buckets() {
   for (uint64_t n : {30001, 65536, 65537, 81921, 150001})
     for (bool kv : {false, true})
       for (uint64_t distinct : {0, 300, 20000}) {
-        pss::DistPlan d = pss::dist_plan(n, n, 0, 0, 8, kv, 0, false);
+        pss::DistPlan d = pss::dist_plan(n, n, 0, 0, n, 8, kv, 0, false);
         d.root_p = 2;
         const size_t bytes = d.end;
         CHECK(distribution(d, bytes, n, kv, distinct), "%llu keys, %s, %llu values", (unsigned long long)n,
@@ -199,7 +199,7 @@ void one_leaf(uint64_t n, uint64_t copies, bool small, bool kv) {
   for (uint64_t i = 0; i < n; ++i) keys.push_back(1 + (small ? i / copies : i / copies * 0x9E3779B97F4A7C15ull >> 1));
   keys.resize(5 * n, 0);
   std::shuffle(keys.begin(), keys.end(), rng);
-  pss::DistPlan d = pss::dist_plan(keys.size(), keys.size(), 0, 0, 8, kv, 0, false);
+  pss::DistPlan d = pss::dist_plan(keys.size(), keys.size(), 0, 0, keys.size(), 8, kv, 0, false);
   const size_t bytes = d.end;
   d.root_p = 2;
   CHECK(distribution(d, bytes, keys, kv), "leaf of %llu keys, %llu copies, %s, %s", (unsigned long long)n,
@@ -228,7 +228,7 @@ void crowded_leaves() {
       for (int shape = 0; shape < 3; ++shape) {
         const uint64_t len = shape == 0 ? n : shape == 1 ? 1 << 22 : 1 << 25;
         for (uint32_t root : {3u, 45u}) {
-          pss::DistPlan d = pss::dist_plan(n, len, 0, 0, 8, kv, 0, shape == 2);
+          pss::DistPlan d = pss::dist_plan(n, len, 0, 0, len, 8, kv, 0, shape == 2);
           const size_t bytes = d.end;
           d.root_p = root;
           if (shape == 0 && root > 3) continue;

@@ -94,3 +94,36 @@ def test_time_of_crowded_leaves(key, kv):
     if kv:
         assert torch.equal(vout, torch.gather(vals.view(-1, seg), 1, at).view(-1))
     assert t < 1.1 * (base + tiles)
+
+
+def test_time_of_a_segment_above_its_bound():
+    """A segment longer than the bound on the length, and no longer than the bound's
+    merge passes reach, takes as many buckets as it needs: it may cost half as much
+    again as with the right bound (one level of at most 384 buckets, where the right
+    bound takes two)."""
+    import torch
+
+    import paper_2305_05245_amd as pss
+
+    n = 8192 << 10
+    keys = torch.randint(-2**63, 2**63 - 1, (n,), dtype=torch.int64, device="cuda")
+    offs = torch.tensor([0, n // 8, n // 8 + 1_500_000, n // 8 + 1_500_000], device="cuda")
+    offs[3:] = n // 8 + 1_500_000
+    want = torch.sort(keys[n // 8:n // 8 + 1_500_000]).values
+
+    def seconds(bound):
+        times = []
+        for _ in range(9):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            out, _ = pss.segmented_sort(keys, offs, tuning={}, max_seg_len=bound)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        assert torch.equal(out[n // 8:n // 8 + 1_500_000], want)
+        return sorted(times)[4]
+
+    announce("segment above its bound")
+    right, low = seconds(1_500_000), seconds(263_000)
+    print(f"right bound {right * 1e3:.0f} us, too low {low * 1e3:.0f} us")
+    assert low < 1.5 * right

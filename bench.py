@@ -954,7 +954,7 @@ def main() -> int:
     # read and write every key once: 2 x 2 x 8 B per int64 key)
     algo_bytes = 2 * 2 * 8 * n
     step_s = wall / args.steps
-    sweeps = int(plan.get("hbm_passes", 0))
+    sweeps = float(plan["sweeps"])
     sort_roofline = {
         "bound": "hbm",
         "passes": 2,

@@ -111,14 +111,17 @@ pss_status pss_workspace_bytes(const pss_ctx *ctx, pss_key_t key, pss_val_t val,
 /* Plan of the launches pss_sort makes for these arguments, as a
  * NUL-terminated JSON object written to buf (host memory of buf_len bytes):
  *   {"mode": "auto"|"paper", "tile": T, "part": T_m, "passes": [fan-in, ...],
- *    "block_passes": [...], "n_blocks": n_B, "n_parts": n_P, "hbm_passes": h}
+ *    "block_passes": [...], "n_blocks": n_B, "n_parts": n_P, "hbm_passes": h,
+ *    "bucket_levels": l, "gathered": bool, "sweeps": s}
  * where "passes" are the merge passes after the tile sort and "hbm_passes"
- * the number of full read+write sweeps over the keys.  Keys-only sorts use
+ * the number of full read+write sweeps over the keys that they make.  Keys-only sorts use
  * tiles and merge partitions of 8192 keys and passes of at most 32 runs;
  * key-value sorts tiles and partitions of 4096 keys and passes of at most 64
- * runs (they hold 12 bytes a key in LDS).  Inputs cut into buckets by sampled
- * splitters (see pss_sort) are described by the merge plan whose workspace they
- * use.  Host-only. */
+ * runs (they hold 12 bytes a key in LDS).  "bucket_levels" > 0: the input is cut
+ * into buckets by sampled splitters instead (see pss_sort), in that many levels,
+ * the last of which gathers its keys or not; the merge passes are then those
+ * whose workspace it uses.  "sweeps" counts what the sort makes in either case (a
+ * read alone is half a sweep).  Host-only. */
 pss_status pss_plan_describe(pss_key_t key, pss_val_t val, uint64_t n, uint32_t n_blocks,
                              uint32_t n_parts, char *buf, size_t buf_len);
 

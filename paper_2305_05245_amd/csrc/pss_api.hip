@@ -938,7 +938,19 @@ pss_status pss_plan_describe(pss_key_t key, pss_val_t val, uint64_t n, uint32_t 
   }
   const size_t sweeps = (n ? 1 : 0) + p.passes.size() + (p.paper && n ? 1 : 0);
   j += ", \"n_blocks\": " + std::to_string(n_blocks) + ", \"n_parts\": " + std::to_string(n_parts);
-  j += ", \"hbm_passes\": " + std::to_string(sweeps) + ", \"workspace_bytes\": " + std::to_string(ws) + "}";
+  j += ", \"hbm_passes\": " + std::to_string(sweeps) + ", \"workspace_bytes\": " + std::to_string(ws);
+  // what runs: a level that scatters reads the keys once more, to count them
+  double made = (double)sweeps;
+  int levels = 0;
+  if (p.dist.on) {
+    levels = p.dist.levels;
+    made = 1;
+    for (int l = 1; l <= levels; ++l) made += p.dist.tiled(l) ? 1.0 : 1.5;
+  }
+  char run[96];
+  snprintf(run, sizeof run, ", \"bucket_levels\": %d, \"gathered\": %s, \"sweeps\": %.1f}", levels,
+           p.dist.on && p.dist.gather ? "true" : "false", made);
+  j += run;
   if (j.size() + 1 > buf_len) return fail(nullptr, PSS_ERR_INVALID, "buffer too small");
   memcpy(buf, j.c_str(), j.size() + 1);
   return PSS_OK;

@@ -234,9 +234,8 @@ pss_status make_plan(pss_key_t key, pss_val_t val, uint64_t n, uint32_t n_blocks
     p->off_offsets = take(((size_t)n_parts + 1) * sizeof(uint64_t));
   }
   p->total = off;
-  if (!p->paper && n >= dist_min_keys(key) && pss::launch_dist_sample) {
+  if (!p->paper && n >= dist_min_keys(key))
     p->dist = plan_dist(n, n, 0, 0, n, p->kb, p->kv, p->off_table, p->total);
-  }
   return PSS_OK;
 }
 
@@ -446,6 +445,8 @@ pss_status paper_partition_search(pss_ctx *ctx, const Plan &p, int kt, const voi
 // from wherever their level left them into the output.
 pss_status run_dist_levels(pss_ctx *ctx, const pss::DistPlan &d, int kt, bool kv,
                            const pss::DistBufs &b, uint64_t n, char *w, hipStream_t s) {
+  if (!pss::launch_dist_sample)  // (weak: see pss_dist.hpp)
+    return fail(ctx, PSS_ERR_UNSUPPORTED, "this library was linked without pss_dist.hip");
   const uint64_t kbytes = n * (uint64_t)pss::key_bytes(kt);
   const uint64_t sweep = 2 * (kbytes + (kv ? 4 * n : 0));
   for (int l = 1; l <= d.levels; ++l) {
@@ -1142,8 +1143,7 @@ pss_status make_seg_plan(const pss_ctx *ctx, pss_key_t key, pss_val_t val, uint6
   // ten launches that find nothing to distribute (256 segments of 8192 int64: 79 us,
   // 59 without), and the merge passes reach any longer ones among them.
   const bool bounded = tu && tu->max_seg_len;
-  if (max_len > sp->merged && (bounded || n / std::max<uint64_t>(S, 1) > sp->merged) &&
-      pss::launch_dist_segments)
+  if (max_len > sp->merged && (bounded || n / std::max<uint64_t>(S, 1) > sp->merged))
     sp->dist = plan_dist(n, max_len, n_segs, sp->merged, sp->longest, kb, kv, sp->off_plan, sp->total);
   if (!sp->dist.on) {
     sp->merge_passes = sp->max_passes;
@@ -1272,6 +1272,8 @@ pss_status pss_segmented_sort(pss_ctx *ctx, pss_key_t key, pss_val_t val, const 
     }
   }
   if (!sp.dist.on) return PSS_OK;
+  if (!pss::launch_dist_segments)
+    return fail(ctx, PSS_ERR_UNSUPPORTED, "this library was linked without pss_dist.hip");
   const pss::DistBufs b{keys_in, vals_in, kws, (uint32_t *)(w + sp.off_vals), keys_out, vals_out};
   {
     LaunchTimer t(ctx, "segment_plan", (uint64_t)n_segs * 16, s);

@@ -218,7 +218,8 @@ struct DistBufs {
 // ranges, of the segments above `merged` keys; those above `longest` are left out
 // (the merge passes' planner reports them).  The steps of a level and the two
 // kernels that end the sort follow.  Declared weak so that a host-only program can
-// link the plan without the device code.
+// link the plan without the device code; a sort then fails (pss_api.hip), and is
+// never run another way.
 #define PSS_WEAK __attribute__((weak))
 PSS_WEAK hipError_t launch_dist_segments(const DistPlan &d, const uint64_t *seg_off, uint64_t n,
                                          uint64_t merged, uint64_t longest, char *w, hipStream_t s);

@@ -277,8 +277,9 @@ __global__ __launch_bounds__(1024) void seg_dist_plan_kernel(SegDistArgs a) {
     DistNode d;
     d.off = (uint32_t)a.off[s];
     d.len = len;
-    d.p = node_picks(len, a.target, (int)a.levels);
-    d.p = d.p < a.root_p ? d.p : a.root_p;
+    const bool one = !a.tiled && len <= kDistOneLevel * a.target;
+    d.p = node_picks(len, a.target, one ? 1 : (int)a.levels);
+    d.p = one || d.p < a.root_p ? d.p : a.root_p;
     d.nr = (len + a.rl - 1) / a.rl;
     d.cols = node_cols(d.p);
     d.stride = node_stride(len, d.nr, a.tiled != 0);

@@ -31,6 +31,14 @@ constexpr uint32_t kDistRangeTiles = 11;
 // scattered; the kernels of 10^7 u64 with values: 397 and 340), less than those
 // of long ones (5*10^7 int64 mod 1000: 654 and 762; 2^28 int64: 3856 and 4504).
 constexpr uint64_t kDistGatherMin = (uint64_t)1 << 25;
+// Segments of up to as many buckets are cut by the first level alone where the
+// plan has more levels for longer ones and the first one scatters (by two levels
+// in brackets: 50 segments of 300007 int64 without a bound on the length, random
+// 251 us (339), of 1000 values 427 (515), with values 325 and 600 (435 and 721)).
+// Of wider ones it is slower where the segments are few, as a single workgroup
+// samples each: 4 of 700000 int64, 171 buckets, 153 and 238 us (153 and 202); 2 of
+// 900000, 220 buckets, 157 and 254 (146 and 187).
+constexpr uint32_t kDistOneLevel = 160;
 // Most tiles of a node of the last level: a leaf lists one piece a tile in the
 // LDS its keys take later.  Sampled nodes stay far below.
 inline constexpr uint32_t dist_node_tiles(int kb, bool kv) {
@@ -167,8 +175,10 @@ inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, uint64_
     d.max_ranges[l] = (uint32_t)(n / d.rl[l] + nodes + (l == d.levels ? d.max_copies : 0));
     max_cols = std::max(max_cols, cols);
     // rows of the table are its buckets: at most 2 root_p in the first level,
-    // kDistSlots later; tiles are padded to 8 entries
-    const uint64_t widest = l == 1 ? std::min(kDistSlots, 2 * d.root_p) : kDistSlots;
+    // unless it cuts some segments for good, and kDistSlots later; tiles are
+    // padded to 8 entries
+    const bool one = l == 1 && n_segs && !tiled && d.levels > 1;  // kDistOneLevel
+    const uint64_t widest = l == 1 && !one ? std::min(kDistSlots, 2 * d.root_p) : kDistSlots;
     const uint64_t table =
         tiled ? widest * (n / kDistTile) + 9 * cols : widest * (n / d.rl[l]) + cols;
     d.max_table[l] = (uint32_t)std::min<uint64_t>(table, 0xffffffffu);

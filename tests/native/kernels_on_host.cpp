@@ -184,7 +184,10 @@ void segment_routes() {
   const std::vector<uint64_t> shorter = {100, 4096, 4097, 131071, 0, 131072, 5000, 9000};
   const std::vector<uint64_t> some = {100, 4096, 4097, 131071, 0, 131072, 131073, 9000};
   const std::vector<uint64_t> longer = {131073, 131072, 270000};
+  // (more than one level can cut: the first one cuts those that it can)
+  const std::vector<uint64_t> levels = {327680, 131073, 327681, 150001, 7};
   for (uint64_t distinct : {0, 900}) {
+    segments(levels, 0, true, distinct, 0, [](size_t) { return true; });
     segments(shorter, 131072, true, distinct, 0, [](size_t) { return true; });
     segments(some, 131073, true, distinct, 0, [](size_t) { return true; });
     segments(some, 0, true, distinct, 0, [](size_t) { return true; });

@@ -127,3 +127,41 @@ def test_time_of_a_segment_above_its_bound():
     right, low = seconds(1_500_000), seconds(263_000)
     print(f"right bound {right * 1e3:.0f} us, too low {low * 1e3:.0f} us")
     assert low < 1.5 * right
+
+
+@pytest.mark.parametrize("kv", [False, True], ids=["keys", "kv"])
+def test_time_of_segments_without_a_bound(kv):
+    """Without a bound on the length the plan has the levels that one array would
+    take; segments that one level can cut do not pay for the others.  The launches
+    of a level without nodes take a few microseconds: a tenth of these sorts."""
+    import torch
+
+    import paper_2305_05245_amd as pss
+
+    n, seg = 50 * 300_007, 300_007
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    some = torch.randint(-2**63, 2**63 - 1, (1000,), dtype=torch.int64, device="cuda", generator=g)
+    keys = some[torch.randint(0, 1000, (n,), device="cuda", generator=g)].contiguous()
+    vals = torch.arange(n, dtype=torch.int32, device="cuda") if kv else None
+    offs = torch.arange(0, n + 1, seg, dtype=torch.int64, device="cuda")
+    want, at = torch.sort(keys.view(-1, seg), dim=1, stable=True)
+
+    def seconds(**bound):
+        times = []
+        for _ in range(9):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            out, vout = pss.segmented_sort(keys, offs, vals, tuning={}, **bound)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        assert torch.equal(out, want.view(-1))
+        if kv:
+            assert torch.equal(vout, torch.gather(vals.view(-1, seg), 1, at).view(-1))
+        return sorted(times)[4]
+
+    announce("segments without a bound", "kv" if kv else "keys")
+    exact, none = seconds(max_seg_len=seg), seconds()
+    print(f"bound given {exact * 1e3:.0f} us, none {none * 1e3:.0f} us")
+    assert none < 1.1 * exact

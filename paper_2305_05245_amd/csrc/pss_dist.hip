@@ -246,7 +246,7 @@ struct SegDistArgs {
   const uint64_t *off;
   uint32_t n_segs;
   uint64_t n, merged, longest;
-  uint32_t target, rl, root_p, levels, tiled;
+  uint32_t target, rl, root_p, one_p, levels, tiled;
   DistCounters *ctr;
   DistNode *nodes;
   DistRange *ranges;
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(1024) void seg_dist_plan_kernel(SegDistArgs a) {
     DistNode d;
     d.off = (uint32_t)a.off[s];
     d.len = len;
-    const bool one = !a.tiled && len <= kDistOneLevel * a.target;
+    const bool one = len <= a.one_p * a.target;
     d.p = node_picks(len, a.target, one ? 1 : (int)a.levels);
     d.p = one || d.p < a.root_p ? d.p : a.root_p;
     d.nr = (len + a.rl - 1) / a.rl;
@@ -1795,6 +1795,7 @@ hipError_t launch_dist_segments(const DistPlan &d, const uint64_t *seg_off, uint
   a.target = d.target;
   a.rl = d.rl[1];
   a.root_p = d.root_p;
+  a.one_p = d.one_p;
   a.levels = (uint32_t)d.levels;
   a.tiled = d.tiled(1) ? 1u : 0u;
   a.ctr = (DistCounters *)(w + d.off_ctr);

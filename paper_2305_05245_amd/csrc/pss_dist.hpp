@@ -39,6 +39,11 @@ constexpr uint64_t kDistGatherMin = (uint64_t)1 << 25;
 // samples each: 4 of 700000 int64, 171 buckets, 153 and 238 us (153 and 202); 2 of
 // 900000, 220 buckets, 157 and 254 (146 and 187).
 constexpr uint32_t kDistOneLevel = 160;
+// With a bound on the length some segment needs the levels, and the others take
+// one only if there are as many keys: sampling them for good adds to the chain of
+// launches (96 requests, 7.7*10^6 u64 with values, 768 us (733); 1000000 and 60
+// times 300000, 449 (539); 4096 arrays, 4.5*10^8 int64, 4643 (4856)).
+constexpr uint64_t kDistOneKeys = (uint64_t)1 << 24;
 // Most tiles of a node of the last level: a leaf lists one piece a tile in the
 // LDS its keys take later.  Sampled nodes stay far below.
 inline constexpr uint32_t dist_node_tiles(int kb, bool kv) {
@@ -108,6 +113,7 @@ struct DistPlan {
   uint32_t cap = 0, target = 0;
   uint32_t root_p = 0;    // most buckets aimed at in a first-level node
   uint32_t n_segs = 0;    // segmented: segments (0: one array)
+  uint32_t one_p = 0;     // the first level cuts segments of up to as many buckets for good
   // Two or more levels: the level before the last leaves its tiles in place
   // as well, and the last level gathers its keys from them, which takes the
   // place of a count and a scatter (if the tables fit the workspace).
@@ -152,6 +158,7 @@ inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, uint64_
   const uint64_t units = (max_len + d.target - 1) / d.target;
   d.levels = units <= kDistMaxPicks ? 1 : units <= 144000 ? 2 : 3;
   d.gather = gather && d.levels > 1 && max_len >= kDistGatherMin;
+  if (n_segs && d.levels > 1 && !d.tiled(1) && (max_len == n || n >= kDistOneKeys)) d.one_p = kDistOneLevel;
   d.root_p = std::max<uint32_t>(
       2, std::min(kDistMaxPicks, dist_root((longest + d.target - 1) / d.target, d.levels)));
   auto tiles = [](uint64_t x) { return (x + kDistTile - 1) / kDistTile; };
@@ -177,8 +184,7 @@ inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, uint64_
     // rows of the table are its buckets: at most 2 root_p in the first level,
     // unless it cuts some segments for good, and kDistSlots later; tiles are
     // padded to 8 entries
-    const bool one = l == 1 && n_segs && !tiled && d.levels > 1;  // kDistOneLevel
-    const uint64_t widest = l == 1 && !one ? std::min(kDistSlots, 2 * d.root_p) : kDistSlots;
+    const uint64_t widest = l == 1 && !d.one_p ? std::min(kDistSlots, 2 * d.root_p) : kDistSlots;
     const uint64_t table =
         tiled ? widest * (n / kDistTile) + 9 * cols : widest * (n / d.rl[l]) + cols;
     d.max_table[l] = (uint32_t)std::min<uint64_t>(table, 0xffffffffu);

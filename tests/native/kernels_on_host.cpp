@@ -184,7 +184,13 @@ void segment_routes() {
   const std::vector<uint64_t> shorter = {100, 4096, 4097, 131071, 0, 131072, 5000, 9000};
   const std::vector<uint64_t> some = {100, 4096, 4097, 131071, 0, 131072, 131073, 9000};
   const std::vector<uint64_t> longer = {131073, 131072, 270000};
-  // (more than one level can cut: the first one cuts those that it can)
+  // (more than one level can cut: the first one cuts those that it can, unless the
+  // length is bounded and the keys are few, or the level leaves its tiles in place)
+  const auto one_p = [](uint64_t n, uint64_t max_len) {
+    return pss::dist_plan(n, max_len, 96, 131072, max_len, 8, true, 0, true).one_p;
+  };
+  CHECK(one_p(10000000, 10000000) == pss::kDistOneLevel && one_p(10000000, 1 << 20) == 0, "one level, 10^7");
+  CHECK(one_p(1 << 24, 1 << 20) == pss::kDistOneLevel && one_p(1 << 25, 1 << 25) == 0, "one level, more");
   const std::vector<uint64_t> levels = {327680, 131073, 327681, 150001, 7};
   for (uint64_t distinct : {0, 900}) {
     segments(levels, 0, true, distinct, 0, [](size_t) { return true; });

@@ -366,11 +366,13 @@ __global__ __launch_bounds__(NT) void dist_sample_kernel(const typename Key<KT>:
     rk[i] = i * NT + tid < S ? Key<KT>::map(x) : key_max<U>();
   }
   lds_sort_keys<U, NT>(rk, sk);
-  // splitters of p picks; when frequent keys double them beyond the slots,
-  // half the picks do
+  // splitters of p picks; when frequent keys double them beyond the slots, those
+  // of as many picks as fit doubled.  (Half the picks, 186 of 372 with 4 to 6 of
+  // 1000 values between two, left 20 to 40 buckets above the cap: 1500000 int64 of
+  // 1000 values 170 us, now 128; 48 segments of 4.6*10^6 u64 with values 464, now 363.)
   U *spl = (U *)L.spl + nd.sbase;
   uint32_t ns = 0;
-  for (uint32_t p = nd.p;; p = (p + 1) / 2) {
+  for (uint32_t p = nd.p;; p = nd.cols / 2) {
     const uint32_t last_pick = p - 2;  // picks 0 .. p-2
     U v = 0;
     uint32_t e = 0;
@@ -389,7 +391,7 @@ __global__ __launch_bounds__(NT) void dist_sample_kernel(const typename Key<KT>:
     }
     uint32_t total;
     const uint32_t to = block_scan<NT>(e, wsum, total);
-    if (total < nd.cols || p <= 2) {
+    if (total < nd.cols) {  // (2 (p - 1) at most)
       if (first) spl[to] = v;
       if (next) spl[to + (first ? 1u : 0u)] = v + 1;
       ns = total;

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 #include <random>
 #include <string>
 
@@ -96,7 +97,8 @@ void segment_left_out() {
 // One distribution sort of uint64 keys by the launches of plan d (whose arrays
 // end at byte `bytes` of the workspace, after keys and values); true if the
 // output is sorted.
-bool distribution(const pss::DistPlan &d, size_t bytes, const std::vector<uint64_t> &keys, bool kv) {
+bool distribution(const pss::DistPlan &d, size_t bytes, const std::vector<uint64_t> &keys, bool kv,
+                  pss::DistCounters *ctr = nullptr) {
   const uint64_t n = keys.size();
   std::vector<uint64_t> out(n);
   std::vector<uint32_t> vals(n), vout(n);
@@ -118,6 +120,7 @@ bool distribution(const pss::DistPlan &d, size_t bytes, const std::vector<uint64
   }
   CHECK(pss::launch_dist_leaves(kt, kv, d, b, ws.p, nullptr) == hipSuccess, "leaves");
   CHECK(pss::launch_dist_rest(kt, kv, d, b, ws.p, nullptr) == hipSuccess, "rest");
+  if (ctr) std::memcpy(ctr, ws.p + d.off_ctr, sizeof(*ctr));
   std::vector<uint32_t> at(vals);
   std::stable_sort(at.begin(), at.end(), [&](uint32_t x, uint32_t y) { return keys[x] < keys[y]; });
   for (uint64_t i = 0; i < n; ++i)
@@ -249,6 +252,22 @@ void crowded_leaves() {
     }
 }
 
+// More buckets aimed at than half of the slots, and values so frequent that each
+// pick takes two splitters: as many picks as fit, so that few of the buckets
+// between (4 of 1000 values, 3000 keys, with every slot used) are above the cap.
+void doubled_splitters() {
+  for (uint64_t n : {700001, 760001}) {
+    const pss::DistPlan d = pss::dist_plan(n, n, 0, 0, n, 8, true, 0, false);
+    CHECK(d.levels == 1, "%d levels", d.levels);
+    std::vector<uint64_t> keys(n);
+    for (auto &k : keys) k = rng() % 1000 * 0x9E3779B97F4A7C15ull;
+    pss::DistCounters ctr;
+    CHECK(distribution(d, d.end, keys, true, &ctr), "%llu keys", (unsigned long long)n);
+    CHECK(ctr.big <= 4, "%llu keys: %u buckets above the cap", (unsigned long long)n, ctr.big);
+    CHECK(device_error() == 0, "device error word");
+  }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -257,7 +276,8 @@ int main(int argc, char **argv) {
   if (pss_create(0, &ctx) != PSS_OK) return 2;
   const struct { const char *name; void (*run)(); } cases[] = {
       {"segment_left_out", segment_left_out}, {"plan_bounds", plan_bounds}, {"big_buckets", big_buckets},
-      {"crowded_leaves", crowded_leaves}, {"leaf_bins", leaf_bins}, {"segment_routes", segment_routes}};
+      {"crowded_leaves", crowded_leaves}, {"leaf_bins", leaf_bins}, {"segment_routes", segment_routes},
+      {"doubled_splitters", doubled_splitters}};
   bool found = false;
   for (const auto &c : cases) {
     if (name != c.name) continue;

@@ -73,3 +73,8 @@ def test_big_buckets(program, seed):
 @pytest.mark.parametrize("seed", [0, 1])
 def test_leaves_and_segments(program, case, seed):
     run(program, case, seed)
+
+
+@pytest.mark.parametrize("seed", [0, 1])
+def test_doubled_splitters(program, seed):
+    run(program, "doubled_splitters", seed)

@@ -31,8 +31,8 @@
 // Nothing depends on the sizes being met: a bucket left too large is sorted by
 // all workgroups together, merging through memory.
 //
-// At 2^28 int64 uniform keys (ms): samples 0.21, first partition 0.86, gathered
-// partition 1.24, leaves 1.50; the sort 3.85.  With a count (0.44) and a
+// At 2^28 int64 uniform keys (ms): samples 0.21, first partition 0.85, gathered
+// partition 1.26, leaves 1.43; the sort 3.72.  With a count (0.44) and a
 // scatter (1.48) in place of the first partition, and 0.89 for a partition that
 // need not gather, it took 4.50, and the merge plan's tile sort (1.71) and three
 // merge passes (1.88 each with their searches) 7.31.  A piece is 24 keys of 8
@@ -1073,9 +1073,10 @@ __device__ __forceinline__ DistLeaf uniform(const DistLeaf &f) {
 // the bins of two keys or more (one in eleven at the target size) are listed
 // and sorted, one thread each (counting every key's place within its bin
 // instead looked at each bin as often as it has keys, in lockstep with the
-// fullest of 256: 1.77 against 1.52 ms at 2^28 int64).  VALU instructions (116
-// a key) and the latency of the gather bound it: 76 KB of LDS leave two
-// workgroups a CU.  A leaf with a crowded bin (a key of rank
+// fullest of 256: 1.77 against 1.52 ms at 2^28 int64).  VALU instructions (123
+// a key, 147 with values) and the latency of the gather bound it: 76 KB of LDS
+// leave two workgroups a CU.  The loads are issued as their addresses are found,
+// before the barrier that ends it: 1.52 -> 1.43 ms.  A leaf with a crowded bin (a key of rank
 // kCrowded or more: many equal keys, or keys spread over many magnitudes) is
 // left to the rest list.
 //

@@ -18,9 +18,11 @@ constexpr uint32_t kDistTile = kDistThreads * kDistItems;
 constexpr uint32_t kDistMaxPicks = 384;
 constexpr uint32_t kDistSlots = 512;
 constexpr int kDistMaxLevels = 3;
-// Keys one workgroup sorts in LDS, and the mean bucket the
-// splitters aim at: half of it, so that a bucket cut by 20 or more samples
-// overflows about once in 10^5.
+// Keys one workgroup sorts in LDS, and the mean bucket the splitters aim at:
+// half of it.  A bucket between every k-th of the samples then overflows with the
+// odds of a gamma variable of order k above twice its mean: 1.8e-4 at k = 20 (a
+// node of 384 buckets has 21 samples a bucket), 4e-6 at 32, 1e-10 at 64 (up to 128
+// buckets); it is sorted all the same, by all workgroups in the last kernel.
 constexpr uint32_t kDistCap = 8192, kDistCapKV = 4096;
 constexpr uint32_t kDistTarget = 4096, kDistTargetKV = 2048;
 // Most tiles of one range.
@@ -29,7 +31,8 @@ constexpr uint32_t kDistRangeTiles = 11;
 // and looking up their pieces costs more than the count and the scatter of
 // short arrays (96 requests of up to 2^20 u64 with values: 664 us gathered, 644
 // scattered; the kernels of 10^7 u64 with values: 397 and 340), less than those
-// of long ones (5*10^7 int64 mod 1000: 654 and 762; 2^28 int64: 3856 and 4504).
+// of long ones (5*10^7 int64 mod 1000: 654 and 762; 2^28 int64: 3856 and 4504); the
+// line lies between them.
 constexpr uint64_t kDistGatherMin = (uint64_t)1 << 25;
 // Segments of up to as many buckets are cut by the first level alone where the
 // plan has more levels for longer ones and the first one scatters (by two levels
@@ -146,9 +149,11 @@ inline uint32_t dist_root(uint64_t units, int levels) {
 // n and n_segs = 0; of n_segs segments, those above min_len >= cap keys), laid
 // out from byte offset `off` on.  Arrays of up to `longest` keys are sorted too,
 // with as many first-level buckets as they need, or kDistMaxPicks.  One level reaches
-// kDistMaxPicks buckets of the target size; two levels are kept up to the
-// count where a first-level bucket half as large again as the mean still gets
-// its share of second-level buckets.
+// kDistMaxPicks buckets of the target size; two levels are kept up to 144000
+// (380 x 380).  Up to 65536 (2^28 keys) a first-level bucket half as large again
+// as the mean still gets its share of second-level buckets; above, the larger ones
+// get fewer than the target size asks for, and larger leaves or big buckets, as a
+// third level would move every key once or twice more.
 inline DistPlan dist_plan(uint64_t n, uint64_t max_len, uint32_t n_segs, uint64_t min_len,
                           uint64_t longest, int kb, bool kv, size_t off, bool gather) {
   DistPlan d;

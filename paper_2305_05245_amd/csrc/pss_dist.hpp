@@ -44,9 +44,10 @@ constexpr uint64_t kDistGatherMin = (uint64_t)1 << 25;
 constexpr uint32_t kDistOneLevel = 160;
 // With a bound on the length some segment needs the levels, and the others take
 // one only if there are as many keys: sampling them for good adds to the chain of
-// launches (96 requests, 7.7*10^6 u64 with values, 768 us (733); 1000000 and 60
-// times 300000, 449 (539); 4096 arrays, 4.5*10^8 int64, 4643 (4856)).
-constexpr uint64_t kDistOneKeys = (uint64_t)1 << 24;
+// launches (96 requests, 1.7*10^7 u64 with values, most of them in requests that
+// need two levels: 768 us (733); 384 requests, 5.8*10^7, 1553 (1588); 4096 arrays,
+// 4.5*10^8 int64, 4630 (4856)).
+constexpr uint64_t kDistOneKeys = (uint64_t)1 << 25;
 // Most tiles of a node of the last level: a leaf lists one piece a tile in the
 // LDS its keys take later.  Sampled nodes stay far below.
 inline constexpr uint32_t dist_node_tiles(int kb, bool kv) {

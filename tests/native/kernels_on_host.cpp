@@ -193,7 +193,7 @@ void segment_routes() {
     return pss::dist_plan(n, max_len, 96, 131072, max_len, 8, true, 0, true).one_p;
   };
   CHECK(one_p(10000000, 10000000) == pss::kDistOneLevel && one_p(10000000, 1 << 20) == 0, "one level, 10^7");
-  CHECK(one_p(1 << 24, 1 << 20) == pss::kDistOneLevel && one_p(1 << 25, 1 << 25) == 0, "one level, more");
+  CHECK(one_p(1 << 24, 1 << 20) == 0 && one_p(1 << 25, 1 << 20) == pss::kDistOneLevel && one_p(1 << 25, 1 << 25) == 0, "one level, more");
   const std::vector<uint64_t> levels = {327680, 131073, 327681, 150001, 7};
   for (uint64_t distinct : {0, 900}) {
     segments(levels, 0, true, distinct, 0, [](size_t) { return true; });

@@ -334,7 +334,7 @@ void pss_graph_destroy(pss_graph *graph);
  * batching: the batch is whatever arrived while the workers were busy), and
  * sorts the batch with one segmented sort (one segment per request): a
  * gather kernel copies the requests' inputs into the batch buffer, the
- * segmented sort runs (step 1 in tiles, steps 2-4 per request), and a
+ * segmented sort runs (tiles, and a merge pass or buckets per request), and a
  * scatter kernel copies every sorted segment to its request's outputs.  The
  * workers' streams overlap one batch's work with the next.
  *

@@ -176,8 +176,10 @@ def segmented_sort(keys: torch.Tensor, seg_offsets, vals: torch.Tensor | None = 
     """Sort every segment [seg_offsets[i], seg_offsets[i+1]) of a 1-D device
     tensor independently (stable with `vals`).  seg_offsets: a device int64
     tensor of n_segs + 1 offsets, or a host sequence (copied to the device;
-    its longest segment then bounds the merge passes launched).  `tuning`
-    chooses the small-segment tile sorts (see autotune.py); None = defaults,
+    its longest segment is then the bound on the length: the merge passes and
+    levels of buckets launched are those it needs; without a bound, those that one
+    array of all keys would).  `tuning` chooses the small-segment tile sorts and
+    the runs of a merge pass (see autotune.py); None = defaults,
     or the autotuner's cached choice when one exists.  Returns (keys, vals)."""
     if not keys.is_cuda or keys.dim() != 1 or not keys.is_contiguous():
         raise ValueError("keys must be a contiguous 1-D device tensor")

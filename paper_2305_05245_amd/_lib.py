@@ -188,8 +188,8 @@ def plan(key: int, val: int, n: int, n_blocks: int = 0, n_parts: int = 0) -> dic
 
 class Tuning(ctypes.Structure):
     """pss_tuning: which segments use the 2048- and 4096-key tile sorts, a
-    bound on the longest segment (bounds the merge passes launched), and the
-    runs merged per pass (fan_log2: 5 or 6, 0 = 5)."""
+    bound on the longest segment (with it, the merge passes or levels of buckets
+    launched), and the runs merged per pass (fan_log2: 5 or 6, 0 = 5)."""
 
     _fields_ = [("small_max_2k", ctypes.c_uint32), ("small_max_4k", ctypes.c_uint32),
                 ("max_seg_len", ctypes.c_uint64), ("fan_log2", ctypes.c_uint32),

@@ -5,10 +5,12 @@ Two choices are tuned together:
 * the tile classes: a segment of at most `small_max_2k` keys is sorted by one
   128-thread workgroup (2048-key tile), one of at most `small_max_4k` keys by
   a 256-thread workgroup (4096-key tile), anything longer by 512-thread
-  workgroups on 8192-key tiles followed by merge passes;
+  workgroups on 8192-key tiles (4096 with values) and a merge pass, or, above
+  one pass's reach or 2^18 keys, cut into buckets;
 * the runs merged per pass (`fan_log2`): 32 runs (five merge rounds in LDS,
-  the keys-only merge with gap sentinels) or 64 runs (six rounds, one pass
-  fewer for segments of 33-64 tiles or 1025-4096 tiles).
+  the keys-only merge with gap sentinels) or 64 runs (six rounds; one pass
+  reaches twice as far, which moves segments of 33-64 tiles of 4096 from
+  buckets to a merge pass).
 
 Which choice is fastest depends on the size mix, so the tuner times every
 candidate on a synthetic batch shaped like the caller's (same key type,
@@ -112,8 +114,8 @@ def tune(kt: int, vt: int, n: int, n_segs: int, lo_log2: float = 6.0, hi_log2: f
 if __name__ == "__main__":
     # python -m paper_2305_05245_amd.autotune [cache.json]: tune two batch
     # shapes, int64 keys only and u64 keys with uint32 values: the 4096-array
-    # batch (sizes 2^6..2^20) and 1024 arrays of 2^17..2^19 keys (segments of
-    # 17-64 tiles, where 64 runs per pass save a whole pass)
+    # batch (sizes 2^6..2^20) and 1024 arrays of 2^17..2^19 keys (17-64 tiles,
+    # on both sides of the longest segment that is merged)
     import sys
 
     import workloads as W

@@ -53,12 +53,13 @@ constexpr uint64_t kMaxTableEntries = (uint64_t)1 << 28;
 
 // Shortest array the automatic plan distributes into buckets.  Below it the few
 // launches of one or two merge passes cost less than sampling.  Integers from
-// one tile on (9001 int32 merged and distributed: 43 and 37 us, with values 55
-// and 37, few values with values 55 and 44; 60001: 60 and 38, 74 and 42, 74 and
-// 70).  Floats of both signs have a bucket around zero that spans all small
-// magnitudes, and its crowded leaf takes the slow path, which shorter arrays
-// don't make up for (30011 normal f32: 51 and 54 us, with values 64 and 66;
-// 60001: 60 and 56, 74 and 69).
+// one tile on (us, merged and distributed; 9001 int32: 50 and 36, with values 61
+// and 37, of 1000 values 61 and 52; 65537: 65 and 38, 76 and 47, 76 and 66).  Keys
+// spread over all magnitudes crowd the leaf of the smallest, which the last kernel
+// sorts, and are the price of that (16384 int64: 58 and 63, int32 with values 62
+// and 89; 65537: 74 and 65, 78 and 91).  Floats of both signs always have such a
+// bucket around zero, which shorter arrays don't make up for (30011 normal f32: 51
+// and 54, with values 64 and 66; 40000: 63 and 57, 74 and 65).
 constexpr uint64_t dist_min_keys(pss_key_t key) {
   return key == PSS_F32 || key == PSS_F64 ? 40000 : 8193;
 }

@@ -29,10 +29,11 @@ constexpr uint32_t kDistTarget = 4096, kDistTargetKV = 2048;
 constexpr uint32_t kDistRangeTiles = 11;
 // Shortest array whose last level gathers its keys.  Sampling gathered nodes
 // and looking up their pieces costs more than the count and the scatter of
-// short arrays (96 requests of up to 2^20 u64 with values: 664 us gathered, 644
-// scattered; the kernels of 10^7 u64 with values: 397 and 340), less than those
-// of long ones (5*10^7 int64 mod 1000: 654 and 762; 2^28 int64: 3856 and 4504); the
-// line lies between them.
+// short arrays, less than those of long ones (us, scattered and gathered, random
+// keys; 2.4*10^7: int64 426 and 460, with values 654 and 666, int32 354 and 379, 508
+// and 549; 2^25: 561 and 569, 895 and 857, 451 and 466, 701 and 708; 10^8: 1633 and
+// 1421, 2543 and 2212, 1174 and 1123, 2032 and 1894; 5*10^7 is the one length above
+// the line where int32 keys are still faster scattered, 610 and 642).
 constexpr uint64_t kDistGatherMin = (uint64_t)1 << 25;
 // Segments of up to as many buckets are cut by the first level alone where the
 // plan has more levels for longer ones and the first one scatters (by two levels
